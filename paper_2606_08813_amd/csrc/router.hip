@@ -567,22 +567,54 @@ __global__ void standardize_kernel(const float* __restrict__ X, const int32_t* _
   xh[i] = to_bf16((X[src * d + j] - mean[j]) / stdv[j]);
 }
 
-// Column mean and standard deviation (FP64 accumulation) of n x d rows.
-__global__ void col_stats_kernel(const float* __restrict__ X, int64_t n, int d, float* __restrict__ mean,
-                                 float* __restrict__ stdv) {
+// Column mean and standard deviation (FP64 accumulation) of n x d rows, in two
+// passes over the rows: the rows are cut into STAT_SPLITS runs, a workgroup
+// sums 64 columns of one run (every wave its own rows, so a load is one
+// 256-byte segment), and col_combine_kernel adds the runs in order.  Bound by
+// the two reads of X.  A thread per column walking every row (three workgroups
+// at d = 768, one load in flight each) took 8.2 ms for 16,384 x 768; the four
+// launches of this take 0.03 ms.
+constexpr int STAT_SPLITS = 64;
+__global__ __launch_bounds__(256) void col_moment_kernel(const float* __restrict__ X, int64_t n, int d,
+                                                         const double* __restrict__ mu, double* __restrict__ part) {
+  __shared__ double red[4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int j = (int)blockIdx.x * 64 + lane;
+  const int64_t per = (n + STAT_SPLITS - 1) / STAT_SPLITS;
+  const int64_t r0 = (int64_t)blockIdx.y * per, r1 = r0 + per < n ? r0 + per : n;
+  double s = 0.0;
+  if (j < d) {
+    if (mu) {
+      const double m = mu[j];
+#pragma unroll 8
+      for (int64_t r = r0 + wave; r < r1; r += 4) {
+        const double t = X[r * d + j] - m;
+        s += t * t;
+      }
+    } else {
+#pragma unroll 8
+      for (int64_t r = r0 + wave; r < r1; r += 4) s += X[r * d + j];
+    }
+  }
+  red[wave][lane] = s;
+  __syncthreads();
+  if (wave == 0 && j < d) part[(size_t)blockIdx.y * d + j] = red[0][lane] + red[1][lane] + red[2][lane] + red[3][lane];
+}
+
+// mu (the mean) from the sums of the first pass, or stdv from those of the second.
+__global__ void col_combine_kernel(const double* __restrict__ part, int64_t n, int d, double* __restrict__ mu,
+                                   float* __restrict__ mean, float* __restrict__ stdv) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= d) return;
   double s = 0.0;
-  for (int64_t r = 0; r < n; ++r) s += X[r * d + j];
-  const double mu = s / (double)n;
-  double v = 0.0;
-  for (int64_t r = 0; r < n; ++r) {
-    const double t = X[r * d + j] - mu;
-    v += t * t;
+  for (int k = 0; k < STAT_SPLITS; ++k) s += part[(size_t)k * d + j];
+  if (mean) {
+    mu[j] = s / (double)n;
+    mean[j] = (float)mu[j];
+  } else {
+    const double sd = sqrt(s / (double)n);
+    stdv[j] = (float)(sd > 1e-12 ? sd : 1.0);
   }
-  mean[j] = (float)mu;
-  const double sd = sqrt(v / (double)n);
-  stdv[j] = (float)(sd > 1e-12 ? sd : 1.0);
 }
 
 // Softmax cross-entropy of one row of scores against the target distribution
@@ -635,13 +667,49 @@ __global__ __launch_bounds__(256) void softmax_ce_kernel(const float* __restrict
   }
 }
 
-// out[n] = sum over rows of X[r][n] (bias gradients).
-__global__ void col_sum_kernel(const float* __restrict__ X, int rows, int N, float* __restrict__ out) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= N) return;
+// out[n] = sum over rows of X[r][n] (bias gradients), added in row order: one
+// thread per column keeps the chain of additions, the workgroup's other
+// threads bring the rows.  A workgroup owns CS_COLS columns; chunks of CS_ROWS
+// rows go through registers into the LDS, the next chunk's loads in flight
+// while this one is summed.  Bound by the chain (4 cycles an addition, 2 us
+// for 1,024 rows) and one memory round trip per chunk.  16 columns and not 64
+// so that the 512 to 8,192 columns of a layer give a workgroup to most CUs.
+// A thread per column that also loaded its own rows took 235 us a call in
+// the training of a 768-512-512-1,024 router with batches of 1,024 (one load
+// in flight per thread); this takes 15 us.
+constexpr int CS_COLS = 16, CS_ROWS = 256, CS_PER = CS_ROWS * CS_COLS / 256;
+__global__ __launch_bounds__(256) void col_sum_kernel(const float* __restrict__ X, int rows, int N,
+                                                      float* __restrict__ out) {
+  __shared__ float tile[CS_ROWS][CS_COLS + 1];
+  const int c = threadIdx.x % CS_COLS, r0 = threadIdx.x / CS_COLS;
+  const int n = blockIdx.x * CS_COLS + c;
+  float v[CS_PER];
+  auto load = [&](int base) {
+#pragma unroll
+    for (int u = 0; u < CS_PER; ++u) {
+      const int r = base + r0 + u * (256 / CS_COLS);
+      v[u] = (r < rows && n < N) ? X[(size_t)r * N + n] : 0.f;
+    }
+  };
   float acc = 0.f;
-  for (int r = 0; r < rows; ++r) acc += X[(size_t)r * N + n];
-  out[n] = acc;
+  load(0);
+  for (int base = 0; base < rows; base += CS_ROWS) {
+#pragma unroll
+    for (int u = 0; u < CS_PER; ++u) tile[r0 + u * (256 / CS_COLS)][c] = v[u];
+    __syncthreads();
+    if (base + CS_ROWS < rows) load(base + CS_ROWS);
+    if (threadIdx.x < CS_COLS) {
+      const int m = min(CS_ROWS, rows - base);
+      if (m == CS_ROWS) {
+#pragma unroll 16
+        for (int r = 0; r < CS_ROWS; ++r) acc += tile[r][c];
+      } else {
+        for (int r = 0; r < m; ++r) acc += tile[r][c];
+      }
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x < CS_COLS && n < N) out[n] = acc;
 }
 
 // One Adam step of a tensor, and its BF16 copy when given.
@@ -1054,6 +1122,10 @@ struct Trainer {
     for (void* p : mem) (void)hipFree(p);
   }
 
+  void col_sum(const float* X, int rows, int N, float* out) {
+    hipLaunchKernelGGL(col_sum_kernel, dim3(blocks(N, CS_COLS)), dim3(256), 0, s, X, rows, N, out);
+  }
+
   // Loss and gradients of the batch X[rows[0..B)] against targets tg (B x kt).
   void grad(const float* X, const int32_t* d_rows, const int32_t* tg, int kt) {
     const int d = rt.d, H1 = rt.h1, H2 = rt.h2, G = rt.G;
@@ -1086,7 +1158,7 @@ struct Trainer {
     w.C = g[4];
     w.ldc = H2;
     gemm<true, true, EPI_F32>(dsb, G, h2, H2, G, H2, B, w, s);
-    hipLaunchKernelGGL(col_sum_kernel, dim3(blocks(G)), dim3(256), 0, s, ds, B, G, g[5]);
+    col_sum(ds, B, G, g[5]);
     Epi gg{};
     gg.Z = a2;
     gg.ldz = H2;
@@ -1099,7 +1171,7 @@ struct Trainer {
     w.C = g[2];
     w.ldc = H1;
     gemm<true, true, EPI_F32>(da2b, H2, h1, H1, H2, H1, B, w, s);
-    hipLaunchKernelGGL(col_sum_kernel, dim3(blocks(H2)), dim3(256), 0, s, da2, B, H2, g[3]);
+    col_sum(da2, B, H2, g[3]);
     gg.Z = a1;
     gg.ldz = H1;
     gg.D = da1;
@@ -1111,7 +1183,7 @@ struct Trainer {
     w.C = g[0];
     w.ldc = d;
     gemm<true, true, EPI_F32>(da1b, H1, xh, d, H1, d, B, w, s);
-    hipLaunchKernelGGL(col_sum_kernel, dim3(blocks(H1)), dim3(256), 0, s, da1, B, H1, g[1]);
+    col_sum(da1, B, H1, g[1]);
     HIP_TRY(hipGetLastError());
   }
 
@@ -1307,8 +1379,19 @@ hntl_status hntl_router_train(hntl_index* index, const float* Qtrain, uint32_t n
         HIP_TRY(hipMemcpy(rt.W[l], w.data(), sizeof(float) * w.size(), hipMemcpyHostToDevice));
         HIP_TRY(hipMemset(rt.b[l], 0, sizeof(float) * rt.bsize(l)));
       }
-      hipLaunchKernelGGL(col_stats_kernel, dim3(blocks(ix.d)), dim3(256), 0, s, Qtrain, (int64_t)n, (int)ix.d,
-                         rt.mean, rt.stdv);
+      Scratch sc(s);
+      double* part = sc.get<double>((size_t)STAT_SPLITS * ix.d);
+      double* mu = sc.get<double>(ix.d);
+      const dim3 grid(blocks(ix.d, 64), STAT_SPLITS);
+      hipLaunchKernelGGL(col_moment_kernel, grid, dim3(256), 0, s, Qtrain, (int64_t)n, (int)ix.d,
+                         (const double*)nullptr, part);
+      hipLaunchKernelGGL(col_combine_kernel, dim3(blocks(ix.d)), dim3(256), 0, s, part, (int64_t)n, (int)ix.d, mu,
+                         rt.mean, (float*)nullptr);
+      hipLaunchKernelGGL(col_moment_kernel, grid, dim3(256), 0, s, Qtrain, (int64_t)n, (int)ix.d, (const double*)mu,
+                         part);
+      hipLaunchKernelGGL(col_combine_kernel, dim3(blocks(ix.d)), dim3(256), 0, s, part, (int64_t)n, (int)ix.d, mu,
+                         (float*)nullptr, rt.stdv);
+      HIP_TRY(hipGetLastError());
       rt.refresh_bf16(s);
     }
     Router& rt = *ix.router;

@@ -713,7 +713,7 @@ extern "C" hntl_status hntl_build(const float* X, uint64_t N, uint32_t d, const 
       auto evaluate = [&](int Lc, int first_step) {
         hipLaunchKernelGGL(gather_rows_kernel, dim3(Lc), dim3(256), 0, s, Xt, (int)d, cand, (int64_t)Lc, cand_rows);
         launch_row_norms(cand_rows, Lc, (int)d, cand_norm, s);
-        launch_dist_matrix(Xt, xtn, n_seed, cand_rows, cand_norm, Lc, (int)d, dcand, s);
+        launch_dist_candidates(Xt, xtn, n_seed, cand_rows, cand_norm, Lc, (int)d, dcand, s);
         hipLaunchKernelGGL(kpp_pot_kernel, dim3(nblk), dim3(256), 0, s, n_seed, Lc, dcand, closest, first_step,
                            potpart);
       };

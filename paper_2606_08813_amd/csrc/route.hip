@@ -109,6 +109,174 @@ __device__ __forceinline__ void tile_dot(floatx4 (&acc)[2][2], float (*As)[LDT],
   }
 }
 
+// ---------------------------------- FP32 products from direct LDS loads
+// The products of tile_dot in another order of depths, for 16-byte aligned rows
+// with d % 4 == 0 and for callers that re-score what they pick (routing, kNN).
+// An RT x CT tile of A.B^T is shared by WR x WC waves of
+// (RT / WR) x (CT / WC) each.  Depth chunks of 32 go from global memory
+// straight into the LDS (global_load_lds_dwordx4), into two buffers: chunk
+// k + 1 is requested before chunk k is multiplied, one barrier per chunk.  The
+// buffers are two arrays and the loops are unrolled over them: with one array
+// indexed by k % 2 the compiler cannot tell the requested half from the read
+// one and waits for the request before the first LDS read (18.4 instead of
+// 13.5 ms for 1,024 x 1,000,000 x 768).  A
+// row of a chunk is 8 vectors of 4 depths; vector c of row r sits at position
+// c ^ (r % 8), so the 16 rows of one operand read spread over the banks.  Rows
+// past the end load the last row, vectors past d
+// the row's first (neither reaches a result).  Bound by the FP32 MFMA units:
+// 1,024 x 1,000,000 x 768 runs at the rates stated at the kernels below
+// against tile_dot's 94 TFLOP/s (64 x 64 tiles, one LDS buffer filled through
+// registers, two barriers per chunk).
+constexpr int FK = 32;
+typedef __attribute__((address_space(3))) void* lds_ptr_t;
+
+template <int ROWS, int NW>
+__device__ __forceinline__ void fetch_chunk(float* dst, const float* __restrict__ X, int64_t nrows, int d, int64_t r0,
+                                            int k0) {
+  const int lane = lane_id(), wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int h = 0; h < (ROWS / 8 + NW - 1) / NW; ++h) {
+    const int u = h * NW + wave;  // one instruction: 8 rows, LDS bytes 1024 u .. + 1023
+    if (ROWS / 8 % NW == 0 || u < ROWS / 8) {
+      const int row = u * 8 + (lane >> 3);
+      const int k = k0 + ((lane & 7) ^ (row & 7)) * 4;
+      const int64_t gr = r0 + row < nrows ? r0 + row : nrows - 1;
+      __builtin_amdgcn_global_load_lds((const void*)(X + gr * d + (k < d ? k : 0)), (lds_ptr_t)(dst + (size_t)u * 256),
+                                       16, 0, 0);
+    }
+  }
+}
+
+// One half (16 depths) of a chunk in a wave's registers: MT row and NT column
+// groups of 16.  Lane (i, kq) holds depths 16 h + 4 kq .. + 3 of row / column i,
+// one 16-byte LDS read each, free of bank conflicts, and feeds depth
+// 16 h + 4 kq + e in MFMA step e.  (Dword reads in MFMA order would be merged
+// by the compiler into two-address reads that lose the arrays' identity, and
+// with it the overlap with the requests.)
+template <int MT, int NT>
+struct HalfFrag {
+  floatx4 a[MT], b[NT];
+  __device__ __forceinline__ void load(const float* As, const float* Bs, int wr, int wc, int h) {
+    const int lane = lane_id(), i = lane & 15;
+    const int x = (((lane >> 4) + 4 * h) ^ (i & 7)) * 4;
+#pragma unroll
+    for (int m = 0; m < MT; ++m) a[m] = *reinterpret_cast<const floatx4*>(As + (wr + 16 * m + i) * FK + x);
+#pragma unroll
+    for (int n = 0; n < NT; ++n) b[n] = *reinterpret_cast<const floatx4*>(Bs + (wc + 16 * n + i) * FK + x);
+  }
+  // zeros from depth `valid` of the chunk on (valid % 4 == 0)
+  __device__ __forceinline__ void clip(int h, int valid) {
+    const bool in = 16 * h + 4 * (lane_id() >> 4) < valid;
+#pragma unroll
+    for (int m = 0; m < MT; ++m) a[m] = in ? a[m] : floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int n = 0; n < NT; ++n) b[n] = in ? b[n] : floatx4{0.f, 0.f, 0.f, 0.f};
+  }
+  __device__ __forceinline__ void mma(floatx4 (&acc)[MT][NT]) const {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) acc[m][n] = mfma16x16x4(a[m][e], b[n][e], acc[m][n]);
+  }
+};
+
+// One chunk of the stream, its first half already in f0: reads the second half
+// and multiplies the first; then, with `more`, waits for the next chunk
+// (requested one chunk earlier), calls request() (the chunk after it, into this
+// chunk's buffer, which every wave has read by then) and reads the next
+// chunk's first half; then multiplies the second half.  The barrier and the
+// LDS reads that follow it so have half a chunk of MFMAs to hide behind.
+// extra(): further reads of this chunk.
+template <int MT, int NT, class Request, class Extra>
+__device__ __forceinline__ void chunk_step(floatx4 (&acc)[MT][NT], HalfFrag<MT, NT>& f0, const float* As,
+                                           const float* Bs, const float* nAs, const float* nBs, int wr, int wc,
+                                           int valid, bool more, int next_valid, Request&& request, Extra&& extra) {
+  HalfFrag<MT, NT> f1;
+  f1.load(As, Bs, wr, wc, 1);
+  if (valid < FK) f1.clip(1, valid);
+  extra();
+  f0.mma(acc);
+  if (more) {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0);  // this wave's requests for the next chunk have landed, its reads of this one are done
+    __syncthreads();                // every wave's are
+    request();
+    f0.load(nAs, nBs, wr, wc, 0);
+    if (next_valid < FK) f0.clip(0, next_valid);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  f1.mma(acc);
+}
+
+// Distances on the tiles above: 10,000 x 1,024 x 768 in 155 us (101 TFLOP/s; 158 on
+// tile_dot), 300 x 2,048 x 768 in 22 us (31 on tile_dot), 16,384 x 8,192 x 768 in
+// 1.77 ms (117 TFLOP/s; 1.88).  Without the requests the loop runs at 137 to 143
+// TFLOP/s, without the stores of D 8% faster.
+template <int RT, int CT, int WR, int WC>
+__global__ __launch_bounds__(64 * WR * WC) void dist_tile_kernel(const float* __restrict__ A,
+                                                                 const float* __restrict__ an, int64_t rows,
+                                                                 const float* __restrict__ Bm,
+                                                                 const float* __restrict__ bn, int cols, int d,
+                                                                 float* __restrict__ D,
+                                                                 const int32_t* __restrict__ nlim, int64_t row_base) {
+  constexpr int NW = WR * WC, MT = RT / WR / 16, NT = CT / WC / 16;
+  __shared__ __align__(16) float buf0[(RT + CT) * FK], buf1[(RT + CT) * FK];
+  const int lane = lane_id(), wave = threadIdx.x >> 6;
+  const int64_t row0 = (int64_t)blockIdx.x * RT;
+  if (nlim) {  // rows from *nlim - row_base on are not part of this batch
+    const int64_t lim = (int64_t)*nlim - row_base;
+    if (row0 >= lim) return;
+    if (lim < rows) rows = lim;
+  }
+  const int col0 = blockIdx.y * CT;
+  const int wr = wave / WC * (RT / WR), wc = wave % WC * (CT / WC);
+  floatx4 acc[MT][NT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int n = 0; n < NT; ++n) acc[m][n] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const int nk = (d + FK - 1) / FK;
+  auto fetch = [&](float* dst, int k) {
+    if (k < nk) {
+      fetch_chunk<RT, NW>(dst, A, rows, d, row0, k * FK);
+      fetch_chunk<CT, NW>(dst + RT * FK, Bm, cols, d, col0, k * FK);
+    }
+  };
+  auto none = []() {};
+  HalfFrag<MT, NT> f0;
+  fetch(buf0, 0);
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  fetch(buf1, 1);
+  f0.load(buf0, buf0 + RT * FK, wr, wc, 0);
+  if (d < FK) f0.clip(0, d);
+  for (int k = 0; k < nk; k += 2) {
+    chunk_step(acc, f0, buf0, buf0 + RT * FK, buf1, buf1 + RT * FK, wr, wc, d - k * FK, k + 1 < nk,
+               d - (k + 1) * FK, [&]() { fetch(buf0, k + 2); }, none);
+    if (k + 1 >= nk) break;
+    chunk_step(acc, f0, buf1, buf1 + RT * FK, buf0, buf0 + RT * FK, wr, wc, d - (k + 1) * FK, k + 2 < nk,
+               d - (k + 2) * FK, [&]() { fetch(buf1, k + 3); }, none);
+  }
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t row = row0 + wr + m * 16 + 4 * (lane >> 4) + i;
+      if (row >= rows) continue;
+      const float ar = an[row];
+#pragma unroll
+      for (int n = 0; n < NT; ++n) {
+        const int col = col0 + wc + n * 16 + (lane & 15);
+        if (col < cols) D[row * cols + col] = fmaxf(ar + bn[col] - 2.f * acc[m][n][i], 0.f);
+      }
+    }
+}
+
+// The same distances on tile_dot: short rows, rows that allow no 16-byte loads
+// (odd depths, unaligned operands), and the k-means seeding, whose picks
+// follow the values' last bits.
 __global__ __launch_bounds__(256) void dist_matrix_kernel(const float* __restrict__ A, const float* __restrict__ an,
                                                           int64_t rows, const float* __restrict__ Bm,
                                                           const float* __restrict__ bn, int cols, int d,
@@ -494,20 +662,220 @@ __global__ __launch_bounds__(TOPK_ROWS * 64) void topk_rows_kernel(
 
 // ------------------------------------------------------- brute-force kNN
 // Exact k nearest rows of B for every row of A (the learned router's training
-// targets).  Pass 1, grid (row tiles of 64, column splits): a workgroup walks
-// its column range in 64-wide tiles of MFMA expansion distances, stages each
-// 64 x 64 tile in LDS, and every wave keeps, for its 16 rows, the KNN_SHORT
-// smallest (distance, column) keys in register lists.  Pass 2 merges the
-// splits' lists per row, re-scores the merged shortlist by direct
-// differences in FP32 and keeps the k smallest exact distances (ties: lower
-// column).
+// targets).  Pass 1: a workgroup walks a range of columns in tiles of MFMA
+// expansion distances and keeps, for each of its rows, the KNN_SHORT smallest
+// (distance, column) keys.  Pass 2 merges the ranges' lists per row, re-scores
+// the merged shortlist by direct differences in FP32 and keeps the k smallest
+// exact distances (ties: lower column).
+//
+// knn_tile_kernel is pass 1 for 16-byte aligned rows.  Tiles of RT rows x 128
+// columns by 8 waves, chunks of 32 depths by direct LDS loads, the chunks of
+// consecutive tiles in one stream (the next tile's first chunk loads while
+// this tile's candidates are taken).  A tile's values are tested in the
+// accumulator registers against their row's threshold (the value of its 32nd
+// best key) and the few that pass are appended to the row's stage in the LDS;
+// when a stage is full its row is sorted by one wave (32 kept + 32 staged keys,
+// one bitonic sort of 64) and the values that found no room are offered again.
+// The squared norms of B's rows are summed from the chunks in the LDS: a pass
+// of their own over B (3.1 GB at 1M x 768) cost 0.87 ms.  Bound by the FP32 MFMA
+// units at 64 and 128 rows, by reading B once at 16.  Whole call over
+// 1,000,000 x 768, before (64 x 64 tiles of tile_dot whose every value went
+// through the LDS to a list, 128 ranges a row) and now: 1 query 2.93 -> 0.83 ms
+// (3.7 TB/s), 16 3.19 -> 0.94, 64 3.33 -> 1.49, 300 6.87 -> 5.24, 1,024
+// 17.8 -> 13.9 (113 TFLOP/s).
 constexpr int KNN_SHORT = 32;
 
+constexpr int KNN_COLS = 128, KNN_WAVES = 8;
+
+// Staged keys of a row (RT = 64: 16, so that two workgroups fit a CU's LDS).
+template <int RT>
+constexpr int knn_stage = RT == 64 ? 16 : 32;
+// (the second bound: waves per SIMD, so that the CU's LDS is what limits its workgroups)
+template <int RT, int WR, int WC>
+__global__ __launch_bounds__(64 * KNN_WAVES, RT == 128 ? 2 : 4) void knn_tile_kernel(const float* __restrict__ A,
+                                                                  const float* __restrict__ an, int64_t rows,
+                                                                  const float* __restrict__ Bm, int64_t cols, int d,
+                                                                  int64_t per_split, int splits, int row_tiles,
+                                                                  uint64_t* __restrict__ part) {
+  constexpr int NW = KNN_WAVES, MT = RT / WR / 16, NT = KNN_COLS / WC / 16;
+  constexpr int STG = knn_stage<RT>, LK = KNN_SHORT + STG;
+  static_assert(WR * WC == NW && MT * NT * 4 <= 32, "one pending bit per accumulator element");
+  __shared__ __align__(16) float buf0[(RT + KNN_COLS) * FK], buf1[(RT + KNN_COLS) * FK];
+  __shared__ uint64_t keys[RT * LK];  // per row: sorted list, then stage
+  __shared__ float bnorm[KNN_COLS], thr[RT];
+  __shared__ int cnt[RT];
+  // With 8 ranges or more, the row tiles of one range run on one XCD
+  // (workgroup b is dealt to XCD b % 8) and share its reads of B.
+  const int b = (int)blockIdx.x;
+  const int rt = splits >= 8 ? (b >> 3) % row_tiles : b % row_tiles;
+  const int split = splits >= 8 ? (b >> 3) / row_tiles * 8 + (b & 7) : b / row_tiles;
+  if (split >= splits) return;
+  const int lane = lane_id(), wave = threadIdx.x >> 6;
+  const int64_t row0 = (int64_t)rt * RT;
+  const int64_t c_begin = (int64_t)split * per_split;
+  const int64_t c_end = c_begin + per_split < cols ? c_begin + per_split : cols;
+  const int wr = wave / WC * (RT / WR), wc = wave % WC * (KNN_COLS / WC);
+  for (int e = threadIdx.x; e < RT * LK; e += 64 * NW) keys[e] = KEY_NONE;
+  for (int e = threadIdx.x; e < RT; e += 64 * NW) {
+    thr[e] = __builtin_inff();
+    cnt[e] = 0;
+  }
+  float arow[MT][4];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t row = row0 + wr + m * 16 + 4 * (lane >> 4) + i;
+      arow[m][i] = row < rows ? an[row] : 0.f;
+    }
+  // one wave sorts a row's kept and staged keys and keeps the smallest
+  auto flush_row = [&](int r) {
+    uint64_t* kr = keys + (size_t)r * LK;
+    const int n = KNN_SHORT + min(cnt[r], STG);
+    wave_sync();
+    uint64_t k = lane < n ? kr[lane] : KEY_NONE;
+    k = wave_sort64(k);
+    wave_sync();
+    if (lane < KNN_SHORT) kr[lane] = k;
+    const float t = key_ceil(lane_u64(k, KNN_SHORT - 1));
+    if (lane == 0) {
+      thr[r] = t;
+      cnt[r] = 0;
+    }
+  };
+  // the wave's rows wave, wave + NW, ... whose stage holds at least `least` keys
+  auto flush_rows = [&](int least) {
+    const int own = lane < RT / NW ? cnt[wave + lane * NW] : 0;
+    uint64_t m = __ballot(own >= least);
+    while (m) {  // wave-uniform
+      const int j = __builtin_ctzll(m);
+      m &= m - 1;
+      flush_row(wave + j * NW);
+    }
+  };
+
+  const int nk = (d + FK - 1) / FK;
+  // chunk k of the tile at col, which for k >= nk lies in the next tile (nk
+  // even: the stream of chunks goes on over the tiles; nk odd: the buffer that
+  // the next tile starts with is the one its last chunk was read from, so each
+  // tile starts anew)
+  auto fetch = [&](float* dst, int64_t col, int k) {
+    if (k >= nk) {
+      col += KNN_COLS;
+      k -= nk;
+    }
+    if (col < c_end && k < nk) {
+      fetch_chunk<RT, NW>(dst, A, rows, d, row0, k * FK);
+      fetch_chunk<KNN_COLS, NW>(dst + RT * FK, Bm, cols, d, col, k * FK);
+    }
+  };
+  const int br = threadIdx.x >> 2, bq = threadIdx.x & 3;  // norms: 4 threads per row of B
+  float bsum = 0.f;
+  auto norm = [&](const float* Bs, int valid) {  // valid: depths of the chunk
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int pos = bq + 4 * h;
+      const floatx4 v = *reinterpret_cast<const floatx4*>(Bs + br * FK + pos * 4);
+      if ((pos ^ (br & 7)) * 4 < valid) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bsum = fmaf(v[e], v[e], bsum);
+      }
+    }
+  };
+  auto step = [&](floatx4(&acc)[MT][NT], const float* cur, int valid) {
+    norm(cur + RT * FK, valid);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      HalfFrag<MT, NT> f;
+      f.load(cur, cur + RT * FK, wr, wc, h);
+      if (valid < FK) f.clip(h, valid);
+      f.mma(acc);
+    }
+  };
+  auto ready = [&]() {
+    __builtin_amdgcn_s_waitcnt(0);  // this wave's requests for the chunk have landed
+    __syncthreads();                // every wave's have, and every wave is done with the chunk before
+  };
+  const bool stream = nk % 2 == 0;
+  fetch(buf0, c_begin, 0);
+  for (int64_t col0 = c_begin; col0 < c_end; col0 += KNN_COLS) {
+    floatx4 acc[MT][NT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int n = 0; n < NT; ++n) acc[m][n] = floatx4{0.f, 0.f, 0.f, 0.f};
+    bsum = 0.f;
+    for (int k = 0; k < nk; k += 2) {
+      ready();
+      if (k + 1 < nk) fetch(buf1, col0, k + 1);
+      step(acc, buf0, d - k * FK);
+      if (k + 1 >= nk) break;
+      ready();
+      if (stream || k + 2 < nk) fetch(buf0, col0, k + 2);
+      step(acc, buf1, d - (k + 1) * FK);
+    }
+    bsum += __uint_as_float(lane_xor<1>(__float_as_uint(bsum)));
+    bsum += __uint_as_float(lane_xor<2>(__float_as_uint(bsum)));
+    if (bq == 0) bnorm[br] = bsum;
+    __syncthreads();
+    if (!stream) fetch(buf0, col0, nk);
+    float bcol[NT];
+    uint32_t pend = 0;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const int cl = wc + n * 16 + (lane & 15);
+      bcol[n] = bnorm[cl];
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (col0 + cl < c_end && row0 + wr + m * 16 + 4 * (lane >> 4) + i < rows) pend |= 1u << ((m * 4 + i) * NT + n);
+    }
+    for (;;) {
+      int over = 0;
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int rl = wr + m * 16 + 4 * (lane >> 4) + i;
+          const float t = thr[rl];
+#pragma unroll
+          for (int n = 0; n < NT; ++n) {
+            const uint32_t bit = 1u << ((m * 4 + i) * NT + n);
+            const float v = fmaxf(arow[m][i] + bcol[n] - 2.f * acc[m][n][i], 0.f);
+            if ((pend & bit) && v <= t) {
+              const int at = atomicAdd(&cnt[rl], 1);
+              if (at < STG) {
+                keys[(size_t)rl * LK + KNN_SHORT + at] = make_key(v, (uint32_t)(col0 + wc + n * 16 + (lane & 15)));
+                pend &= ~bit;
+              } else {
+                over = 1;
+              }
+            } else {
+              pend &= ~bit;  // above the threshold, which only falls
+            }
+          }
+        }
+      // every round with a full stage empties it, so the pending values shrink
+      if (!__syncthreads_or(over)) break;
+      flush_rows(STG);
+      __syncthreads();
+    }
+  }
+  flush_rows(1);
+  wave_sync();
+  for (int j = 0; j < RT / NW; ++j) {
+    const int r = wave + j * NW;
+    const int64_t row = row0 + r;
+    if (row < rows && lane < KNN_SHORT) part[((size_t)row * splits + split) * KNN_SHORT + lane] = keys[(size_t)r * LK + lane];
+  }
+}
+
+// Pass 1 for rows that allow no 16-byte loads, grid (row tiles of 64, ranges).
 __global__ __launch_bounds__(256) void knn_partial_kernel(const float* __restrict__ A, const float* __restrict__ an,
                                                           int64_t rows, const float* __restrict__ Bm,
                                                           const float* __restrict__ bn, int64_t cols, int d,
-                                                          int64_t per_split, uint64_t* __restrict__ part,
-                                                          bool vec4) {
+                                                          int64_t per_split, uint64_t* __restrict__ part) {
   __shared__ float tiles[2 * TM * LDT];  // As and Bs; then the 64 x 64 distance tile
   __shared__ uint64_t stage[4][16][64];
   float(*As)[LDT] = reinterpret_cast<float(*)[LDT]>(tiles);
@@ -523,7 +891,7 @@ __global__ __launch_bounds__(256) void knn_partial_kernel(const float* __restric
   for (int r = 0; r < 16; ++r) L[r].init(stage[wave][r], KNN_SHORT);
   for (int64_t col0 = c_begin; col0 < c_end; col0 += TN) {
     floatx4 acc[2][2];
-    tile_dot(acc, As, Bs, A, rows, Bm, (int)(c_end < cols ? c_end : cols), d, row0, (int)col0, vec4);
+    tile_dot(acc, As, Bs, A, rows, Bm, (int)(c_end < cols ? c_end : cols), d, row0, (int)col0, false);
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
@@ -564,26 +932,40 @@ __global__ __launch_bounds__(256) void knn_merge_kernel(const float* __restrict_
   if (row >= rows) return;
   WaveTop64 L;
   L.init(stage[wave], KNN_SHORT);
-  for (int sp = 0; sp < splits; ++sp) {
-    const uint64_t key = lane < KNN_SHORT ? part[((size_t)row * splits + sp) * KNN_SHORT + lane] : KEY_NONE;
+  const uint64_t* src = part + (size_t)row * splits * KNN_SHORT;
+  for (int e = lane; e - lane < splits * KNN_SHORT; e += HNTL_WAVE) {  // two lists at a time
+    const uint64_t key = e < splits * KNN_SHORT ? src[e] : KEY_NONE;
     L.offer(key, key != KEY_NONE);
   }
   L.finish();
   const uint64_t mine = L.best;
   const float* a = A + row * d;
   uint64_t ex = KEY_NONE;
-  for (int j = 0; j < KNN_SHORT; ++j) {
-    const uint64_t kj = shfl_u64(mine, j);
-    if (kj == KEY_NONE) break;
-    const uint32_t c = key_id(kj);
-    const float* b = Bm + (size_t)c * d;
-    float acc = 0.f;
-    for (int t = lane; t < d; t += HNTL_WAVE) {
-      const float df = a[t] - b[t];
-      acc = fmaf(df, df, acc);
+  const int have = __popcll(__ballot(lane < KNN_SHORT && mine != KEY_NONE));
+  constexpr int RB = 8;  // shortlist entries re-scored together (their loads overlap)
+  for (int j0 = 0; j0 < have; j0 += RB) {
+    const float* bp[RB];
+    uint32_t cs[RB];
+    float acc[RB];
+#pragma unroll
+    for (int u = 0; u < RB; ++u) {
+      cs[u] = key_id(shfl_u64(mine, j0 + u < have ? j0 + u : j0));
+      bp[u] = Bm + (size_t)cs[u] * d;
+      acc[u] = 0.f;
     }
-    acc = wave_sum(acc);
-    if (lane == j) ex = make_key(acc, c);
+    for (int t = lane; t < d; t += HNTL_WAVE) {
+      const float av = a[t];
+#pragma unroll
+      for (int u = 0; u < RB; ++u) {
+        const float df = av - bp[u][t];
+        acc[u] = fmaf(df, df, acc[u]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < RB; ++u) {
+      const float tot = wave_sum(acc[u]);
+      if (lane == j0 + u && lane < have) ex = make_key(tot, cs[u]);
+    }
   }
   ex = wave_sort64(ex);
   if (lane < k) {
@@ -610,9 +992,35 @@ void launch_dist_matrix(const float* A, const float* an, int64_t rows, const flo
     return;
   }
   const bool vec4 = (d % 4) == 0 && ((uintptr_t)A % 16) == 0 && ((uintptr_t)Bm % 16) == 0;
+  // below six chunks of depth a tile is mostly prologue and stores: tile_dot's
+  // five workgroups a CU hide them better (10,000 x 1,024 x 128: 38.6 against 39.9 us)
+  if (vec4 && d >= 6 * FK) {
+    // 128 x 64 tiles once every CU gets eight of them (16,384 x 8,192 x 768:
+    // 1.77 ms against 1.89 on 64 x 64), else 64 x 64 (10,000 x 1,024 x 768: 155
+    // against 156 us; 3,001 x 1,024 x 768: 50 against 61; tile_dot: 158 and 54)
+#define HNTL_DIST(RT, CT, WR, WC)                                                                                 \
+  hipLaunchKernelGGL((dist_tile_kernel<RT, CT, WR, WC>),                                                          \
+                     dim3((unsigned)((rows + RT - 1) / RT), (unsigned)((cols + CT - 1) / CT)), dim3(64 * WR * WC), \
+                     0, s, A, an, rows, Bm, bn, cols, d, D, nlim, row_base)
+    if ((rows + 127) / 128 * ((cols + 63) / 64) >= 2048)
+      HNTL_DIST(128, 64, 4, 2);
+    else
+      HNTL_DIST(64, 64, 2, 2);
+#undef HNTL_DIST
+    HIP_TRY(hipGetLastError());
+    return;
+  }
   dim3 grid((unsigned)((rows + TM - 1) / TM), (unsigned)((cols + TN - 1) / TN));
-  hipLaunchKernelGGL(dist_matrix_kernel, grid, dim3(256), 0, s, A, an, rows, Bm, bn, cols, d, D, vec4, nlim,
-                     row_base);
+  hipLaunchKernelGGL(dist_matrix_kernel, grid, dim3(256), 0, s, A, an, rows, Bm, bn, cols, d, D, vec4, nlim, row_base);
+  HIP_TRY(hipGetLastError());
+}
+
+void launch_dist_candidates(const float* A, const float* an, int64_t rows, const float* Bm, const float* bn, int cols,
+                            int d, float* D, hipStream_t s) {
+  if (rows <= DIRECT_ROWS && d <= 16 * HNTL_WAVE) return launch_dist_matrix(A, an, rows, Bm, bn, cols, d, D, s);
+  const bool vec4 = (d % 4) == 0 && ((uintptr_t)A % 16) == 0 && ((uintptr_t)Bm % 16) == 0;
+  dim3 grid((unsigned)((rows + TM - 1) / TM), (unsigned)((cols + TN - 1) / TN));
+  hipLaunchKernelGGL(dist_matrix_kernel, grid, dim3(256), 0, s, A, an, rows, Bm, bn, cols, d, D, vec4, nullptr, 0);
   HIP_TRY(hipGetLastError());
 }
 
@@ -657,26 +1065,65 @@ void launch_knn(const float* A, int64_t rows, const float* Bm, int64_t cols, int
   if (rows <= 0) return;
   if (k < 1 || k > 16) throw ArgError{HNTL_EUNSUPPORTED, "brute-force kNN supports 1 <= k <= 16"};
   if (cols >= (1ll << 31)) throw ArgError{HNTL_EUNSUPPORTED, "brute-force kNN needs fewer than 2^31 rows"};
-  const bool vec4 = (d % 4) == 0 && ((uintptr_t)A % 16) == 0 && ((uintptr_t)Bm % 16) == 0;
-  const int64_t rt = (rows + TM - 1) / TM;
-  int64_t splits = std::max<int64_t>(1, std::min<int64_t>((cols + TN - 1) / TN, 2048 / rt));
-  int64_t per = ((cols + splits - 1) / splits + TN - 1) / TN * TN;
-  splits = (cols + per - 1) / per;
   float *an = nullptr, *bn = nullptr;
   uint64_t* part = nullptr;
+  int64_t splits, per;
   HIP_TRY(hipMallocAsync((void**)&an, sizeof(float) * rows, s));
-  HIP_TRY(hipMallocAsync((void**)&bn, sizeof(float) * cols, s));
-  HIP_TRY(hipMallocAsync((void**)&part, sizeof(uint64_t) * rows * splits * KNN_SHORT, s));
   launch_row_norms(A, rows, d, an, s);
-  launch_row_norms(Bm, cols, d, bn, s);
-  hipLaunchKernelGGL(knn_partial_kernel, dim3((unsigned)rt, (unsigned)splits), dim3(256), 0, s, A, an, rows, Bm, bn,
-                     cols, d, per, part, vec4);
+  if ((d % 4) == 0 && ((uintptr_t)A % 16) == 0 && ((uintptr_t)Bm % 16) == 0) {
+    // rows per tile: the work is that of the rows padded to the tile, and 128
+    // rows run 4% faster than twice 64 (1,000,000 x 768: 1,024 queries 13.9
+    // against 14.5 ms, 300 queries 5.9 against 5.2)
+    auto padded = [&](int64_t t) { return (rows + t - 1) / t * t; };
+    const int RT = rows <= 16 ? 16 : 100 * padded(128) <= 103 * padded(64) ? 128 : 64;
+    const int64_t rt = (rows + RT - 1) / RT;
+    // column ranges: the fewest (each adds a list per row to merge) that leave
+    // the last round of workgroups at least 95% full, at least 8 tiles a range
+    const int64_t slots = 256 * (RT == 128 ? 1 : 2);
+    const int64_t most = std::max<int64_t>(1, std::min<int64_t>(cols / (8 * KNN_COLS), 4 * slots));
+    double best = 0.0;
+    splits = 1;
+    for (int64_t sp = 1; sp <= most && best < 0.95; ++sp) {
+      if (sp > 8 && sp % 8) continue;  // whole rounds over the XCDs
+      const int64_t wg = rt * sp;
+      const double full = (double)wg / (double)((wg + slots - 1) / slots * slots);
+      if (full > best) {
+        best = full;
+        splits = sp;
+      }
+      if (wg > 8 * slots) break;
+    }
+    per = ((cols + splits - 1) / splits + KNN_COLS - 1) / KNN_COLS * KNN_COLS;
+    splits = (cols + per - 1) / per;
+    HIP_TRY(hipMallocAsync((void**)&part, sizeof(uint64_t) * rows * splits * KNN_SHORT, s));
+    const int64_t grid = rt * (splits >= 8 ? (splits + 7) / 8 * 8 : splits);
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * KNN_WAVES), 0, s, A, an, rows, Bm, cols, d, per,
+                         (int)splits, (int)rt, part);
+    };
+    if (RT == 16)
+      launch(knn_tile_kernel<16, 1, 8>);
+    else if (RT == 64)
+      launch(knn_tile_kernel<64, 2, 4>);
+    else
+      launch(knn_tile_kernel<128, 4, 2>);
+  } else {
+    const int64_t rt = (rows + TM - 1) / TM;
+    splits = std::max<int64_t>(1, std::min<int64_t>((cols + TN - 1) / TN, 2048 / rt));
+    per = ((cols + splits - 1) / splits + TN - 1) / TN * TN;
+    splits = (cols + per - 1) / per;
+    HIP_TRY(hipMallocAsync((void**)&bn, sizeof(float) * cols, s));
+    HIP_TRY(hipMallocAsync((void**)&part, sizeof(uint64_t) * rows * splits * KNN_SHORT, s));
+    launch_row_norms(Bm, cols, d, bn, s);
+    hipLaunchKernelGGL(knn_partial_kernel, dim3((unsigned)rt, (unsigned)splits), dim3(256), 0, s, A, an, rows, Bm, bn,
+                       cols, d, per, part);
+  }
   HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(knn_merge_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, A, rows, Bm, d,
                      (int)splits, part, k, ids, dist);
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipFreeAsync(an, s));
-  HIP_TRY(hipFreeAsync(bn, s));
+  if (bn) HIP_TRY(hipFreeAsync(bn, s));
   HIP_TRY(hipFreeAsync(part, s));
 }
 

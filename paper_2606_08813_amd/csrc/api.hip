@@ -22,7 +22,7 @@ hntl_status fail(hntl_status s, const std::string& msg) {
 Index::~Index() {
   void* ptrs[] = {centroids, cnorm,    basis,   goff,      boff,     perm,       codes,  eps,
                   codes_bf16, codes_fp8, scales, basis_bf16, codes_i16, i16_steps, eps_i16, X,
-                  blo,       bhi,       emin,   gorder,     cent_split, eps_id};
+                  blo,       bhi,       emin,   gorder, grank, cent_split, eps_id};
   int prev = 0;
   (void)hipGetDevice(&prev);
   (void)hipSetDevice(device);
@@ -262,11 +262,8 @@ struct StagedScratch {
       }
     }
     b.G = (int)ix.G;
-    b.gcount = (int32_t*)take(4 * (size_t)ix.G);
-    b.gcount0 = (int32_t*)take(4 * (size_t)ix.G);
+    b.cnt = (int32_t*)take(8 * (size_t)ix.G);
     b.gstart = (int32_t*)take(4 * (size_t)ix.G);
-    b.cur0 = (int32_t*)take(4 * (size_t)ix.G);
-    b.cur1 = (int32_t*)take(4 * (size_t)ix.G);
     b.order = (int32_t*)take(4 * (size_t)npairs);
     // the projection item size depends only on d, the code form and Q's alignment
     const int tiles[3] = {16, 16, project_tile(ix, Q, (sp.flags & HNTL_FLAG_PROJECT_BF16) != 0)};
@@ -274,8 +271,6 @@ struct StagedScratch {
     for (int L = 0; L < 3; ++L) {
       b.lists.tile[L] = tiles[L];
       b.lists.ioff[L] = (int32_t*)take(4 * ((size_t)ix.G + 1));
-      b.lists.lstart[L] = (int32_t*)take(4 * (size_t)ix.G);
-      b.lists.lcount[L] = (int32_t*)take(4 * (size_t)ix.G);
       b.max_items[L] = (int)(np[L] / tiles[L] + std::min<int64_t>(ix.G, np[L]) + 1);
     }
     if (!io.tangent_in) {
@@ -283,6 +278,7 @@ struct StagedScratch {
       if (!io.epsq_out) eq = (float*)take(4 * (size_t)npairs);
     }
     part = (uint64_t*)take(8 * (size_t)npairs * sp.C);
+    b.slot = (int32_t*)part;  // read before the first list is written
     return off;
   }
 };
@@ -319,7 +315,7 @@ void run_staged(const Index& ix, const float* Q, uint32_t nq, const hntl_search_
     // 2. bucketing by grain (each grain's probe-slot-0 pairs first, so that
     //    slot 0 is scanned first and its C-th key bounds the other slots)
     clk.at(HNTL_STAGE_BUCKET);
-    launch_bucket(probes, nq, (int)P, (int)ix.G, w.b, s);
+    launch_bucket(probes, nq, (int)P, w.b, s);
     // 3. projection
     const float* T = io.tangent_in;
     const float* eq = io.epsq_in;
@@ -327,7 +323,7 @@ void run_staged(const Index& ix, const float* Q, uint32_t nq, const hntl_search_
       clk.at(HNTL_STAGE_PROJECT);
       float* To = io.tangent_out ? io.tangent_out : w.T;
       float* eo = io.epsq_out ? io.epsq_out : w.eq;
-      launch_project(ix, Q, (int)P, w.b, To, eo, (sp.flags & HNTL_FLAG_PROJECT_BF16) != 0, nullptr, s);
+      launch_project(ix, Q, (int)P, w.b, To, eo, (sp.flags & HNTL_FLAG_PROJECT_BF16) != 0, s);
       T = To;
       eq = eo;
     }
@@ -348,7 +344,7 @@ void run_staged(const Index& ix, const float* Q, uint32_t nq, const hntl_search_
   // 5. pool merge + exact rerank
   clk.at(HNTL_STAGE_RERANK);
   launch_merge_rerank(ix, Q, nq, (int)P, (int)C, (int)k, probes, part, io.pool_in, io.pool_out, io.pool_D_out, io.ids,
-                      io.dist, s, nullptr, mode_a ? ix.eps_id : nullptr);
+                      io.dist, s, nullptr, nullptr, mode_a ? ix.eps_id : nullptr);
   clk.done();
   if (sp.flags & HNTL_FLAG_SYNC) {
     HIP_TRY(hipStreamSynchronize(s));

@@ -2,16 +2,25 @@
 // projection and scan run grain-major so that a grain's basis and Block-SoA
 // codes are read once per tile of queries instead of once per query.
 //
-// A counting sort groups the pair ids q * P + slot by grain.  Inside a grain's
-// range the pairs of probe slot 0 (each query's nearest grain) come first, so
-// the scan can take slot 0 in a pass of its own whose results bound the other
-// slots.  Three work-item lists are cut from the ranges without materialising
-// them: per list L and grain g, lstart[L][g] / lcount[L][g] give the pairs, and
-// the exclusive prefix ioff[L][g] of ceil(lcount / tile_L) numbers its items;
-// a kernel finds the grain of item i by binary search in ioff.
+// A counting sort groups the pair ids q * P + slot by grain, grains in the
+// order of their rank (Buckets::grank; the grain number where none is given).
+// Inside a grain's range the pairs of probe slot 0 (each query's nearest
+// grain) come first, so the scan can take slot 0 in a pass of its own whose
+// results bound the other slots.  Three work-item lists are cut from the ranges
+// without materialising them: the exclusive prefix ioff[L][rank] of
+// ceil(pairs / tile_L) numbers list L's items, and a kernel finds the grain of
+// item i by binary search in ioff (or from the decoded item table).
+//
+// Three kernels: bucket_count_kernel takes every pair's place among its
+// grain's pairs of the same kind from the counter itself (a returning atomic),
+// bucket_scan_kernel turns the counts into offsets, bucket_place_kernel writes
+// the pair ids, the pairs' candidate-list slots and the item table.  Batches
+// of up to SMALL_PAIRS pairs do all of it in one workgroup.  Bound by launches
+// and by dependent round trips, not by bytes (262,144 pairs: 3 MB).  On
+// 16,384 x 16 pairs over 8,192 grains the bucketing stage takes 33 us
+// (eight kernels with a histogram, a scatter and lists numbered query by query:
+// 135 us), on 256 x 16 pairs 24 us (117 us).
 #include <algorithm>
-
-#include <atomic>
 
 #include "hntl_device.h"
 #include "hntl_internal.h"
@@ -20,338 +29,297 @@ namespace hntl {
 
 namespace {
 
-constexpr int CHUNK = 4096;      // pairs per workgroup
-constexpr int LDS_MAX_G = 8192;  // grain counters kept in LDS up to this G (scatter: 4 G ints = 128 KiB)
+constexpr int SMALL_PAIRS = 4096;   // pairs and grains of the one-workgroup form: four pairs a
+constexpr int SMALL_GRAINS = 8192;  // thread in registers, four counters a grain in the LDS (128 KiB)
+constexpr int64_t ITEM_WGS = 1024;   // workgroups that write an item table (each thread strides over it)
 
 __device__ __forceinline__ int probe_of(const int32_t* __restrict__ probes, int64_t p, int G) {
   const int g = probes[p];
   return (g >= 0 && g < G) ? g : -1;
 }
 
-// Per-grain pair counts, all slots and slot 0; counters live in LDS per
-// workgroup and are added to the global ones once per (workgroup, grain).
-__global__ __launch_bounds__(256) void bucket_hist_kernel(const int32_t* __restrict__ probes, int64_t npairs, int P,
-                                                          int G, int32_t* __restrict__ gcount,
-                                                          int32_t* __restrict__ gcount0) {
-  extern __shared__ int lds_mem[];
-  int* lc = lds_mem;
-  int* lc0 = lds_mem + G;
-  const bool lds = G <= LDS_MAX_G;
-  if (lds) {
-    for (int g = threadIdx.x; g < G; g += 256) {
-      lc[g] = 0;
-      lc0[g] = 0;
-    }
-    __syncthreads();
-  }
-  const int64_t p0 = (int64_t)blockIdx.x * CHUNK;
-  for (int u = threadIdx.x; u < CHUNK; u += 256) {
-    const int64_t p = p0 + u;
-    if (p >= npairs) break;
-    const int g = probe_of(probes, p, G);
-    if (g < 0) continue;
-    const bool s0 = (p % P) == 0;
-    if (lds) {
-      atomicAdd(&lc[g], 1);
-      if (s0) atomicAdd(&lc0[g], 1);
-    } else {
-      atomicAdd(&gcount[g], 1);
-      if (s0) atomicAdd(&gcount0[g], 1);
-    }
-  }
-  if (!lds) return;
-  __syncthreads();
-  for (int g = threadIdx.x; g < G; g += 256) {
-    if (lc[g]) atomicAdd(&gcount[g], lc[g]);
-    if (lc0[g]) atomicAdd(&gcount0[g], lc0[g]);
-  }
+// Inclusive scan over the lanes of a wave, DPP moves only.
+__device__ __forceinline__ int wave_inclusive_scan(int x) {
+#define HNTL_SCAN_STEP(CTRL, ROWS) x += __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, false)
+  HNTL_SCAN_STEP(0x111, 0xF);  // row_shr:1, 2, 4, 8: prefixes inside each row of 16 lanes
+  HNTL_SCAN_STEP(0x112, 0xF);
+  HNTL_SCAN_STEP(0x114, 0xF);
+  HNTL_SCAN_STEP(0x118, 0xF);
+  HNTL_SCAN_STEP(0x142, 0xA);  // row_bcast:15 into rows 1 and 3
+  HNTL_SCAN_STEP(0x143, 0xC);  // row_bcast:31 into rows 2 and 3
+#undef HNTL_SCAN_STEP
+  return x;
 }
 
-// Exclusive scan of one value per thread of a 1024-thread workgroup.
-__device__ int block_exclusive_scan(int v, int* tmp /* >= 16 ints */, int& total) {
+// Exclusive scan of N values per thread of a 1024-thread workgroup.
+template <int N>
+__device__ void block_exclusive_scan(const int (&v)[N], int (&ex)[N], int (&total)[N], int (*tmp)[16] /* N */) {
   const int lane = lane_id(), wave = threadIdx.x >> 6;
-  int x = v;
+  int x[N];
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
-  if (lane == 63) tmp[wave] = x;
-  __syncthreads();
-  int wsum = 0, all = 0;
-  const int nw = blockDim.x >> 6;
-  for (int w = 0; w < nw; ++w) {
-    const int t = tmp[w];
-    if (w < wave) wsum += t;
-    all += t;
-  }
-  __syncthreads();
-  total = all;
-  return wsum + x - v;
-}
-
-// Exclusive scan of four values per thread of a 1024-thread workgroup.
-__device__ void block_exclusive_scan4(const int (&v)[4], int (&ex)[4], int (&total)[4], int (*tmp)[4]) {
-  const int lane = lane_id(), wave = threadIdx.x >> 6;
-  int x[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    x[c] = v[c];
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(x[c], o, 64);
-      if (lane >= o) x[c] += y;
-    }
-  }
+  for (int c = 0; c < N; ++c) x[c] = wave_inclusive_scan(v[c]);
   if (lane == 63)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) tmp[wave][c] = x[c];
+    for (int c = 0; c < N; ++c) tmp[c][wave] = x[c];
   __syncthreads();
-  const int nw = blockDim.x >> 6;
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    int wsum = 0, all = 0;
-    for (int w = 0; w < nw; ++w) {
-      const int t = tmp[w][c];
-      if (w < wave) wsum += t;
-      all += t;
-    }
-    ex[c] = wsum + x[c] - v[c];
-    total[c] = all;
+  for (int c = 0; c < N; ++c) {
+    const int t = lane < 16 ? tmp[c][lane] : 0;
+    const int y = wave_inclusive_scan(t);  // lane w < 16: the waves up to w
+    total[c] = __builtin_amdgcn_readlane(y, 15);
+    const int before = __builtin_amdgcn_readlane(y, wave == 0 ? 0 : wave - 1);
+    ex[c] = (wave == 0 ? 0 : before) + x[c] - v[c];
   }
   __syncthreads();
 }
 
-// Single workgroup: grain starts (gstart) and the three lists' item offsets.
-// Grains are visited in the order `gorder` (rank -> grain; identity if null)
-// and ioff is indexed by that rank, so items come out in that order; the
-// per-grain list ranges (lstart, lcount, indexed by grain) follow from gstart
-// in bucket_lists_kernel.  With `nsplit`, a grain's slot-0 and rest
-// tiles each become nsplit[g] items (one per block range of the grain).
-// Thread t owns the consecutive ranks t * per .. t * per + per - 1: a local
-// pass sums its pairs and items, one workgroup scan turns the sums into
-// offsets, a second local pass writes them.
-__global__ __launch_bounds__(1024) void bucket_scan_kernel(const int32_t* __restrict__ gcount,
-                                                           const int32_t* __restrict__ gcount0, int G,
-                                                           const int32_t* __restrict__ gorder,
-                                                           const int32_t* __restrict__ nsplit,
-                                                           int32_t* __restrict__ gstart, ItemLists lists) {
-  __shared__ int tmp[16][4];
-  const int per = (G + (int)blockDim.x - 1) / (int)blockDim.x;
-  const int r0 = (int)threadIdx.x * per;
-  const int t0 = lists.tile[LIST_SLOT0], t1 = lists.tile[LIST_REST], t2 = lists.tile[LIST_ALL];
-  // up to SCAN_REG ranks per thread (G <= 8,192): every load of a thread's ranks
-  // is issued before any is used, and the values stay in registers for the
-  // second pass (no chains of dependent loads)
-  constexpr int SCAN_REG = 8;
-  const bool reg = per <= SCAN_REG;
-  int gg[SCAN_REG], cc[SCAN_REG], c0s[SCAN_REG], sp[SCAN_REG];
-  if (reg) {
+// Eight consecutive values of a 16-byte aligned array (zeros from n on).
+__device__ __forceinline__ void load8(int (&v)[8], const int* a, int i, int n) {
+  if (i + 8 <= n) {
+    const int4 x = *reinterpret_cast<const int4*>(a + i), y = *reinterpret_cast<const int4*>(a + i + 4);
+    v[0] = x.x, v[1] = x.y, v[2] = x.z, v[3] = x.w;
+    v[4] = y.x, v[5] = y.y, v[6] = y.z, v[7] = y.w;
+  } else {
 #pragma unroll
-    for (int i = 0; i < SCAN_REG; ++i) {
-      const int rank = r0 + i;
-      gg[i] = (i < per && rank < G) ? (gorder ? gorder[rank] : rank) : -1;
-    }
+    for (int u = 0; u < 8; ++u) v[u] = i + u < n ? a[i + u] : 0;
+  }
+}
+__device__ __forceinline__ void store8(int* a, int i, int n, const int (&v)[8]) {
+  if (i + 8 <= n) {
+    *reinterpret_cast<int4*>(a + i) = make_int4(v[0], v[1], v[2], v[3]);
+    *reinterpret_cast<int4*>(a + i + 4) = make_int4(v[4], v[5], v[6], v[7]);
+  } else {
 #pragma unroll
-    for (int i = 0; i < SCAN_REG; ++i) {
-      const int g = gg[i];
-      cc[i] = g >= 0 ? gcount[g] : 0;
-      c0s[i] = g >= 0 ? gcount0[g] : 0;
-      sp[i] = g >= 0 ? (nsplit ? nsplit[g] : 1) : 0;
-    }
+    for (int u = 0; u < 8; ++u)
+      if (i + u < n) a[i + u] = v[u];
   }
-  auto fetch = [&](int i, int& g, int& c, int& c0, int& split) -> bool {
-    const int rank = r0 + i;
-    if (i >= per || rank >= G) return false;
-    if (reg && i < SCAN_REG) {
-      g = gg[i];
-      c = cc[i];
-      c0 = c0s[i];
-      split = sp[i];
-    } else {
-      g = gorder ? gorder[rank] : rank;
-      c = gcount[g];
-      c0 = gcount0[g];
-      split = nsplit ? nsplit[g] : 1;
+}
+
+// Offsets of every rank from the counts (one workgroup of 1,024 threads), 8,192
+// ranks at a time: thread t owns ranks 8 t .. 8 t + 7 of them (16-byte accesses;
+// single ones in that order touch every cache line eight times: 33 us at 8,192
+// grains, this takes 9), sums its pairs, items and lists, one workgroup
+// scan turns the sums into offsets, and it writes its own.  Counts come from c0 and
+// c1 and start offsets go to first and lists (LDS or global); item offsets go
+// to b.  With b.nsplit_rank, a grain's slot-0 and rest tiles each become nsplit
+// items (one per block range of the grain) and each of its pairs owns nsplit
+// candidate lists.
+__device__ __forceinline__ void scan_ranks(const Buckets& b, const int* c0a, const int* c1a, bool c1_aligned,
+                                           int* first, int* lists) {
+  __shared__ int tmp[5][16];
+  const int G = b.G;
+  const int t0 = b.lists.tile[LIST_SLOT0], t1 = b.lists.tile[LIST_REST], t2 = b.lists.tile[LIST_ALL];
+  int carry[5] = {0, 0, 0, 0, 0};
+  for (int base = 0; base < G; base += 8192) {
+    const int r0 = base + 8 * (int)threadIdx.x;
+    int c0[8], c1[8], sp[8];
+    load8(c0, c0a, r0, G);
+    if (c1_aligned)
+      load8(c1, c1a, r0, G);
+    else
+#pragma unroll
+      for (int u = 0; u < 8; ++u) c1[u] = r0 + u < G ? c1a[r0 + u] : 0;
+    if (b.nsplit_rank)
+      load8(sp, b.nsplit_rank, r0, G);
+    else
+#pragma unroll
+      for (int u = 0; u < 8; ++u) sp[u] = 1;
+    int add[5][8];
+    int sum[5] = {0, 0, 0, 0, 0};
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      add[0][u] = c0[u] + c1[u];
+      add[1][u] = (c0[u] + t0 - 1) / t0 * sp[u];
+      add[2][u] = (c1[u] + t1 - 1) / t1 * sp[u];
+      add[3][u] = (c0[u] + c1[u] + t2 - 1) / t2;
+      add[4][u] = (c0[u] + c1[u]) * sp[u];
+#pragma unroll
+      for (int c = 0; c < 5; ++c) sum[c] += add[c][u];
     }
-    return true;
-  };
-  int loc[4] = {0, 0, 0, 0};  // pairs, items of slot 0, of the rest, of all
-  for (int i = 0; i < per; ++i) {
-    int g, c, c0, split;
-    if (!fetch(i, g, c, c0, split)) break;
-    loc[0] += c;
-    loc[1] += (c0 + t0 - 1) / t0 * split;
-    loc[2] += (c - c0 + t1 - 1) / t1 * split;
-    loc[3] += (c + t2 - 1) / t2;
-  }
-  int run[4], tot[4];
-  block_exclusive_scan4(loc, run, tot, tmp);
-  for (int i = 0; i < per; ++i) {
-    int g, c, c0, split;
-    if (!fetch(i, g, c, c0, split)) break;
-    const int rank = r0 + i;
-    gstart[g] = run[0];  // the other per-grain fields: bucket_lists_kernel, many workgroups
-    lists.ioff[LIST_SLOT0][rank] = run[1];
-    lists.ioff[LIST_REST][rank] = run[2];
-    lists.ioff[LIST_ALL][rank] = run[3];
-    run[0] += c;
-    run[1] += (c0 + t0 - 1) / t0 * split;
-    run[2] += (c - c0 + t1 - 1) / t1 * split;
-    run[3] += (c + t2 - 1) / t2;
+    int run[5], tot[5];
+    block_exclusive_scan<5>(sum, run, tot, tmp);
+#pragma unroll
+    for (int c = 0; c < 5; ++c) {
+      run[c] += carry[c];
+      carry[c] += tot[c];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int v = add[c][u];
+        add[c][u] = run[c];
+        run[c] += v;
+      }
+    }
+    store8(first, r0, G, add[0]);
+    store8(b.lists.ioff[LIST_SLOT0], r0, G, add[1]);
+    store8(b.lists.ioff[LIST_REST], r0, G, add[2]);
+    store8(b.lists.ioff[LIST_ALL], r0, G, add[3]);
+    if (lists) store8(lists, r0, G, add[4]);
   }
   if (threadIdx.x == 0) {
-    lists.ioff[LIST_SLOT0][G] = tot[1];
-    lists.ioff[LIST_REST][G] = tot[2];
-    lists.ioff[LIST_ALL][G] = tot[3];
+    b.lists.ioff[LIST_SLOT0][G] = carry[1];
+    b.lists.ioff[LIST_REST][G] = carry[2];
+    b.lists.ioff[LIST_ALL][G] = carry[3];
   }
 }
 
-// Per-grain list ranges from the grain starts (one thread per grain): these
-// scattered writes are spread over many workgroups instead of the scan's one.
-__global__ __launch_bounds__(256) void bucket_lists_kernel(const int32_t* __restrict__ gcount,
-                                                           const int32_t* __restrict__ gcount0, int G,
-                                                           const int32_t* __restrict__ gstart,
-                                                           int32_t* __restrict__ cur0, int32_t* __restrict__ cur1,
-                                                           ItemLists lists) {
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= G) return;
-  const int c = gcount[g], c0 = gcount0[g], st = gstart[g];
-  cur0[g] = 0;
-  cur1[g] = 0;
-  lists.lstart[LIST_SLOT0][g] = st;
-  lists.lcount[LIST_SLOT0][g] = c0;
-  lists.lstart[LIST_REST][g] = st + c0;
-  lists.lcount[LIST_REST][g] = c - c0;
-  lists.lstart[LIST_ALL][g] = st;
-  lists.lcount[LIST_ALL][g] = c;
+// Pair p of rank r: its place in the order and its first candidate list.  start
+// is the rank's first place, lists its first list, at the pair's number among
+// the rank's pairs (slot 0 first).
+__device__ __forceinline__ void place_pair(const Buckets& b, int p, int r, int start, int lists, int at) {
+  b.order[start + at] = p;
+  if (b.lbase) b.lbase[p] = lists + at * b.nsplit_rank[r];
 }
 
-// Scatter pair ids into their grain's range (slot 0 first): each workgroup
-// reserves one run per grain and kind with a single global atomic, then ranks
-// its pairs with LDS atomics.  The order inside a grain's run is not fixed;
-// every consumer writes its results by pair id, so outputs do not depend on it.
-__global__ __launch_bounds__(256) void bucket_scatter_kernel(const int32_t* __restrict__ probes, int64_t npairs,
-                                                             int P, int G, const int32_t* __restrict__ gstart,
-                                                             const int32_t* __restrict__ gcount0,
-                                                             int32_t* __restrict__ cur0, int32_t* __restrict__ cur1,
-                                                             int32_t* __restrict__ order) {
-  extern __shared__ int lds_mem[];
-  const bool lds = G <= LDS_MAX_G;
-  const int64_t p0 = (int64_t)blockIdx.x * CHUNK;
-  if (!lds) {
-    for (int u = threadIdx.x; u < CHUNK; u += 256) {
-      const int64_t p = p0 + u;
-      if (p >= npairs) break;
-      const int g = probe_of(probes, p, G);
-      if (g < 0) continue;
-      const int pos = (p % P) == 0 ? gstart[g] + atomicAdd(&cur0[g], 1)
-                                   : gstart[g] + gcount0[g] + atomicAdd(&cur1[g], 1);
-      order[pos] = (int32_t)p;
+// One decoded work item (see ItemDesc).
+__device__ __forceinline__ void write_item(const Buckets& b, int it, int nP, int n0) {
+  ItemDesc d{};
+  const int G = b.G;
+  // largest rank with ioff[rank] <= item
+  auto rank_of = [&](const int32_t* ioff, int item) {
+    int lo = 0, hi = G;
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (ioff[mid] <= item)
+        lo = mid;
+      else
+        hi = mid;
     }
+    return lo;
+  };
+  if (it < nP) {
+    const int r = rank_of(b.lists.ioff[LIST_ALL], it);
+    const int tp = b.lists.tile[LIST_ALL];
+    const int first = (it - b.lists.ioff[LIST_ALL][r]) * tp;
+    d.g = b.gorder ? b.gorder[r] : r;
+    d.off = b.gstart[r] + first;
+    d.cnt = min(tp, b.cnt[r] + b.cnt[G + r] - first);
+    d.c0 = d.c1 = it;
+  } else {
+    const bool s0 = it < nP + n0;
+    const int L = s0 ? LIST_SLOT0 : LIST_REST;
+    const int li = it - (s0 ? nP : nP + n0);
+    const int r = rank_of(b.lists.ioff[L], li);
+    const int c0 = b.cnt[r], lc = s0 ? c0 : b.cnt[G + r];
+    const int qt = b.lists.tile[L];
+    const int ntiles = (lc + qt - 1) / qt;
+    const int k = li - b.lists.ioff[L][r];
+    const int first = k % ntiles * qt;  // range-major: a range's tiles run together
+    const int base = (s0 ? 0 : c0) + first;
+    d.g = b.gorder ? b.gorder[r] : r;
+    d.range = k / ntiles;
+    d.off = b.gstart[r] + base;
+    d.cnt = min(qt, lc - first);
+    // a grain's projection list is its slot-0 pairs followed by the others, in
+    // 16-pair items when the fused kernel projects (the only reader of c0 / c1):
+    // this tile's pairs lie in items c0 .. c1 (at most two)
+    const int pi0 = b.lists.ioff[LIST_ALL][r];
+    d.c0 = pi0 + base / 16;
+    d.c1 = pi0 + (base + d.cnt - 1) / 16;
+  }
+  b.items[it] = d;
+}
+
+// Every item of the table, dealt out to `stride` threads from `first` on.
+__device__ __forceinline__ void write_items(const Buckets& b, int64_t first, int64_t stride) {
+  const int G = b.G;
+  const int nP = b.lists.ioff[LIST_ALL][G], n0 = b.lists.ioff[LIST_SLOT0][G], n1 = b.lists.ioff[LIST_REST][G];
+  for (int64_t it = first; it < (int64_t)nP + n0 + n1; it += stride) write_item(b, (int)it, nP, n0);
+}
+
+// The pairs' numbers and the counts.  Up to SMALL_GRAINS grains a workgroup
+// numbers its 4,096 pairs in the LDS and reserves one run per grain and kind
+// with a single global atomic: 13 us for 262,144 pairs over 8,192 grains, where
+// a global atomic per pair takes 31 us, and longer yet over fewer grains.
+template <bool LDS>
+__global__ __launch_bounds__(1024) void bucket_count_kernel(Buckets b, const int32_t* __restrict__ probes,
+                                                            int64_t npairs, int P) {
+  __shared__ int cnt[LDS ? 2 * SMALL_GRAINS : 1];
+  constexpr int U = 4;
+  const int G = b.G;
+  const int64_t p0 = (int64_t)blockIdx.x * (U * 1024) + threadIdx.x;
+  int at[U], key[U];  // key: the pair's counter
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int64_t p = p0 + u * 1024;
+    const int g = p < npairs ? probe_of(probes, p, G) : -1;
+    key[u] = g < 0 ? -1 : (b.grank ? b.grank[g] : g) + (p % P == 0 ? 0 : G);
+  }
+  if constexpr (LDS) {
+    for (int r = threadIdx.x; r < 2 * G; r += 1024) cnt[r] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (key[u] >= 0) at[u] = atomicAdd(&cnt[key[u]], 1);
+    __syncthreads();
+    for (int r = threadIdx.x; r < 2 * G; r += 1024) {
+      const int n = cnt[r];
+      if (n) cnt[r] = atomicAdd(&b.cnt[r], n);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (key[u] >= 0) b.slot[p0 + u * 1024] = cnt[key[u]] + at[u];
+  } else {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (key[u] >= 0) b.slot[p0 + u * 1024] = atomicAdd(&b.cnt[key[u]], 1);
+  }
+}
+
+__global__ __launch_bounds__(1024) void bucket_scan_kernel(Buckets b) {
+  scan_ranks(b, b.cnt, b.cnt + b.G, b.G % 4 == 0, b.gstart, b.glist);
+}
+
+// Workgroups below pair_wgs place pairs, the others write the item table.
+__global__ __launch_bounds__(256) void bucket_place_kernel(Buckets b, const int32_t* __restrict__ probes,
+                                                           int64_t npairs, int P, int pair_wgs) {
+  if ((int)blockIdx.x >= pair_wgs) {
+    write_items(b, (int64_t)((int)blockIdx.x - pair_wgs) * 256 + threadIdx.x,
+                (int64_t)((int)gridDim.x - pair_wgs) * 256);
     return;
   }
-  int* n0 = lds_mem;
-  int* n1 = lds_mem + G;
-  int* b0 = lds_mem + 2 * G;
-  int* b1 = lds_mem + 3 * G;
-  for (int g = threadIdx.x; g < G; g += 256) {
-    n0[g] = 0;
-    n1[g] = 0;
-  }
-  __syncthreads();
-  for (int u = threadIdx.x; u < CHUNK; u += 256) {
-    const int64_t p = p0 + u;
-    if (p >= npairs) break;
-    const int g = probe_of(probes, p, G);
-    if (g >= 0) atomicAdd((p % P) == 0 ? &n0[g] : &n1[g], 1);
-  }
-  __syncthreads();
-  for (int g = threadIdx.x; g < G; g += 256) {
-    b0[g] = n0[g] ? gstart[g] + atomicAdd(&cur0[g], n0[g]) : 0;
-    b1[g] = n1[g] ? gstart[g] + gcount0[g] + atomicAdd(&cur1[g], n1[g]) : 0;
-    n0[g] = 0;
-    n1[g] = 0;
-  }
-  __syncthreads();
-  for (int u = threadIdx.x; u < CHUNK; u += 256) {
-    const int64_t p = p0 + u;
-    if (p >= npairs) break;
-    const int g = probe_of(probes, p, G);
-    if (g < 0) continue;
-    const int pos = (p % P) == 0 ? b0[g] + atomicAdd(&n0[g], 1) : b1[g] + atomicAdd(&n1[g], 1);
-    order[pos] = (int32_t)p;
-  }
+  const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (p >= npairs) return;
+  const int g = probe_of(probes, p, b.G);
+  if (g < 0) return;
+  const int r = b.grank ? b.grank[g] : g;
+  const int at = b.slot[p] + ((p % P) == 0 ? 0 : b.cnt[r]);
+  place_pair(b, (int)p, r, b.gstart[r], b.lbase ? b.glist[r] : 0, at);
 }
 
-// Per-pair list slots when grains are split into block ranges: pair
-// (q, slot) of grain g owns the nsplit[g] consecutive lists from lbase[pair];
-// a query's lists are contiguous, qoff[q] .. qoff[q + 1].  Three passes: the
-// lists of each query (one thread per query), an exclusive scan over the
-// queries (one workgroup, each thread a contiguous run), the per-slot bases
-// (one thread per query).
-__global__ __launch_bounds__(256) void query_lists_kernel(const int32_t* __restrict__ probes, int64_t nq, int P,
-                                                          int G, const int32_t* __restrict__ nsplit,
-                                                          int32_t* __restrict__ qoff) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= nq) return;
-  int tot = 0;
-  for (int sl = 0; sl < P; ++sl) {
-    const int g = probes[q * P + sl];
-    tot += (g >= 0 && g < G) ? nsplit[g] : 0;
-  }
-  qoff[q] = tot;
-}
-
-__global__ __launch_bounds__(1024) void query_scan_kernel(int64_t nq, int32_t* __restrict__ qoff) {
-  __shared__ int tmp[32];
-  const int64_t per = (nq + (int64_t)blockDim.x - 1) / (int64_t)blockDim.x;
-  const int64_t q0 = (int64_t)threadIdx.x * per;
-  const int64_t q1 = q0 + per < nq ? q0 + per : nq;
-  // up to QREG queries per thread (nq <= 16,384): all loads issued at once and
-  // kept in registers for the second pass
-  constexpr int QREG = 16;
-  int sum = 0;
-  if (per <= QREG) {
-    int v[QREG];
+__global__ __launch_bounds__(1024) void bucket_small_kernel(Buckets b, const int32_t* __restrict__ probes, int npairs,
+                                                            int P) {
+  __shared__ __align__(16) int cnt[2][SMALL_GRAINS], first[SMALL_GRAINS], lists[SMALL_GRAINS];
+  constexpr int U = SMALL_PAIRS / 1024;
+  const int G = b.G;
+  int rank[U], at[U];
 #pragma unroll
-    for (int i = 0; i < QREG; ++i) v[i] = q0 + i < q1 ? qoff[q0 + i] : 0;
+  for (int u = 0; u < U; ++u) {
+    const int p = (int)threadIdx.x + u * 1024;
+    const int g = p < npairs ? probe_of(probes, p, G) : -1;
+    rank[u] = g < 0 ? -1 : b.grank ? b.grank[g] : g;
+  }
+  for (int r = threadIdx.x; r < G; r += 1024) cnt[0][r] = cnt[1][r] = 0;
+  __syncthreads();
 #pragma unroll
-    for (int i = 0; i < QREG; ++i) sum += v[i];
-    int all;
-    int run = block_exclusive_scan(sum, tmp, all);
+  for (int u = 0; u < U; ++u)
+    if (rank[u] >= 0) at[u] = atomicAdd(&cnt[((int)threadIdx.x + u * 1024) % P == 0 ? 0 : 1][rank[u]], 1);
+  __syncthreads();
+  scan_ranks(b, cnt[0], cnt[1], true, first, lists);
+  __syncthreads();
+  for (int r = threadIdx.x; r < G; r += 1024) {
+    b.gstart[r] = first[r];
+    b.cnt[r] = cnt[0][r];
+    b.cnt[G + r] = cnt[1][r];
+  }
 #pragma unroll
-    for (int i = 0; i < QREG; ++i)
-      if (q0 + i < q1) {
-        qoff[q0 + i] = run;
-        run += v[i];
-      }
-    if (threadIdx.x == 0) qoff[nq] = all;
-    return;
-  }
-  for (int64_t q = q0; q < q1; ++q) sum += qoff[q];
-  int all;
-  int run = block_exclusive_scan(sum, tmp, all);
-  for (int64_t q = q0; q < q1; ++q) {
-    const int v = qoff[q];
-    qoff[q] = run;
-    run += v;
-  }
-  if (threadIdx.x == 0) qoff[nq] = all;
-}
-
-__global__ __launch_bounds__(256) void pair_lists_kernel(const int32_t* __restrict__ probes, int64_t nq, int P,
-                                                         int G, const int32_t* __restrict__ nsplit,
-                                                         const int32_t* __restrict__ qoff,
-                                                         int32_t* __restrict__ lbase) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= nq) return;
-  int run = qoff[q];
-  for (int sl = 0; sl < P; ++sl) {
-    const int g = probes[q * P + sl];
-    lbase[q * P + sl] = run;
-    run += (g >= 0 && g < G) ? nsplit[g] : 0;
-  }
+  for (int u = 0; u < U; ++u)
+    if (rank[u] >= 0) {
+      const int p = (int)threadIdx.x + u * 1024, r = rank[u];
+      place_pair(b, p, r, first[r], lists[r], at[u] + (p % P == 0 ? 0 : cnt[0][r]));
+    }
+  __syncthreads();  // the arrays written above are read back by other threads of this workgroup
+  if (b.items) write_items(b, threadIdx.x, 1024);
 }
 
 __global__ void fill_i32_kernel(int32_t* __restrict__ p, int64_t n, int32_t v) {
@@ -383,117 +351,33 @@ void launch_fill_multi(const FillList& L, hipStream_t s) {
   HIP_TRY(hipGetLastError());
 }
 
-namespace {
-// Largest rank with ioff[rank] <= item (ioff[G] > item).
-__device__ __forceinline__ int item_rank(const int32_t* __restrict__ ioff, int G, int item) {
-  int lo = 0, hi = G;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (ioff[mid] <= item)
-      lo = mid;
-    else
-      hi = mid;
-  }
-  return lo;
-}
-
-__global__ __launch_bounds__(256) void item_table_kernel(ItemLists lists, const int32_t* __restrict__ gorder, int G,
-                                                         int qt, int64_t max_items, ItemDesc* __restrict__ out) {
-  const int64_t it64 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (it64 >= max_items) return;
-  const int it = (int)it64;
-  const int nP = lists.ioff[LIST_ALL][G], n0 = lists.ioff[LIST_SLOT0][G], n1 = lists.ioff[LIST_REST][G];
-  if (it >= nP + n0 + n1) return;
-  ItemDesc d{};
-  if (it < nP) {
-    const int rank = item_rank(lists.ioff[LIST_ALL], G, it);
-    const int g = gorder ? gorder[rank] : rank;
-    const int tp = lists.tile[LIST_ALL];
-    const int first = (it - lists.ioff[LIST_ALL][rank]) * tp;
-    d.g = g;
-    d.off = lists.lstart[LIST_ALL][g] + first;
-    d.cnt = min(tp, lists.lcount[LIST_ALL][g] - first);
-    d.c0 = d.c1 = it;
-  } else {
-    const int L = it < nP + n0 ? LIST_SLOT0 : LIST_REST;
-    const int li = it - (L == LIST_SLOT0 ? nP : nP + n0);
-    const int rank = item_rank(lists.ioff[L], G, li);
-    const int g = gorder ? gorder[rank] : rank;
-    const int lc = lists.lcount[L][g];
-    const int ntiles = (lc + qt - 1) / qt;
-    const int k = li - lists.ioff[L][rank];
-    const int tile = k % ntiles;  // range-major: a range's tiles run together
-    const int first = tile * qt;
-    d.g = g;
-    d.range = k / ntiles;
-    d.off = lists.lstart[L][g] + first;
-    d.cnt = min(qt, lc - first);
-    // a grain's projection list is its slot-0 pairs followed by the others, in
-    // 16-pair items when the fused kernel projects (the only reader of c0 / c1):
-    // this tile's pairs lie in items c0 .. c1 (at most two)
-    const int base = (L == LIST_SLOT0 ? 0 : lists.lcount[LIST_SLOT0][g]) + first;
-    const int pi0 = lists.ioff[LIST_ALL][rank];
-    d.c0 = pi0 + base / 16;
-    d.c1 = pi0 + (base + d.cnt - 1) / 16;
-  }
-  out[it] = d;
-}
-}  // namespace
-
-void launch_item_table(const ItemLists& lists, const int32_t* gorder, int G, int qt, int64_t max_items,
-                       ItemDesc* out, hipStream_t s) {
-  if (max_items <= 0) return;
-  hipLaunchKernelGGL(item_table_kernel, dim3((unsigned)((max_items + 255) / 256)), dim3(256), 0, s, lists, gorder, G,
-                     qt, max_items, out);
-  HIP_TRY(hipGetLastError());
-}
-
-void launch_pair_lists(const int32_t* probes, int64_t nq, int P, int G, const int32_t* nsplit, int32_t* lbase,
-                       int32_t* qoff, hipStream_t s) {
-  if (nq <= 0) return;
-  const dim3 grid((unsigned)((nq + 255) / 256));
-  hipLaunchKernelGGL(query_lists_kernel, grid, dim3(256), 0, s, probes, nq, P, G, nsplit, qoff);
-  hipLaunchKernelGGL(query_scan_kernel, dim3(1), dim3(1024), 0, s, nq, qoff);
-  hipLaunchKernelGGL(pair_lists_kernel, grid, dim3(256), 0, s, probes, nq, P, G, nsplit, qoff, lbase);
-  HIP_TRY(hipGetLastError());
-}
-
-void launch_bucket(const int32_t* probes, int64_t nq, int P, int G, Buckets& b, hipStream_t s,
-                   const int32_t* gorder, const int32_t* nsplit, bool counts_zeroed) {
+void launch_bucket(const int32_t* probes, int64_t nq, int P, const Buckets& b, hipStream_t s, bool counts_zeroed) {
   const int64_t npairs = nq * P;
-  if (!counts_zeroed) {
-    FillList f{};
-    f.seg[0] = FillSeg{b.gcount, G, 0};
-    f.seg[1] = FillSeg{b.gcount0, G, 0};
-    f.n = 2;
-    launch_fill_multi(f, s);
-  }
-  const unsigned nb = (unsigned)((npairs + CHUNK - 1) / CHUNK);
-  if (npairs > 0) {
-    hipLaunchKernelGGL(bucket_hist_kernel, dim3(nb), dim3(256), G <= LDS_MAX_G ? 2 * G * sizeof(int) : 0, s,
-                       probes, npairs, P, G, b.gcount, b.gcount0);
+  if (npairs <= 0) return;
+  if (npairs <= SMALL_PAIRS && b.G <= SMALL_GRAINS) {
+    Buckets one = b;
+    // a long item table is written by many workgroups
+    const bool inside = b.items && b.items_cap <= SMALL_PAIRS;
+    if (!inside) one.items = nullptr;
+    hipLaunchKernelGGL(bucket_small_kernel, dim3(1), dim3(1024), 0, s, one, probes, (int)npairs, P);
     HIP_TRY(hipGetLastError());
+    if (!b.items || inside) return;
+    const unsigned iwgs = (unsigned)std::min<int64_t>((b.items_cap + 255) / 256, ITEM_WGS);
+    hipLaunchKernelGGL(bucket_place_kernel, dim3(iwgs), dim3(256), 0, s, b, probes, npairs, P, 0);
+    HIP_TRY(hipGetLastError());
+    return;
   }
-  hipLaunchKernelGGL(bucket_scan_kernel, dim3(1), dim3(1024), 0, s, b.gcount, b.gcount0, G, gorder, nsplit, b.gstart,
-                     b.lists);
-  hipLaunchKernelGGL(bucket_lists_kernel, dim3((unsigned)((G + 255) / 256)), dim3(256), 0, s, b.gcount, b.gcount0, G,
-                     b.gstart, b.cur0, b.cur1, b.lists);
+  if (!counts_zeroed) launch_fill_i32(b.cnt, 2 * (int64_t)b.G, 0, s);
+  const unsigned pwgs = (unsigned)((npairs + 255) / 256);
+  const dim3 cgrid((unsigned)((npairs + 4095) / 4096));
+  if (b.G <= SMALL_GRAINS)
+    hipLaunchKernelGGL(bucket_count_kernel<true>, cgrid, dim3(1024), 0, s, b, probes, npairs, P);
+  else
+    hipLaunchKernelGGL(bucket_count_kernel<false>, cgrid, dim3(1024), 0, s, b, probes, npairs, P);
+  hipLaunchKernelGGL(bucket_scan_kernel, dim3(1), dim3(1024), 0, s, b);
+  const unsigned iwgs = b.items ? (unsigned)std::min<int64_t>((b.items_cap + 255) / 256, ITEM_WGS) : 0;
+  hipLaunchKernelGGL(bucket_place_kernel, dim3(pwgs + iwgs), dim3(256), 0, s, b, probes, npairs, P, (int)pwgs);
   HIP_TRY(hipGetLastError());
-  if (npairs > 0) {
-    const size_t lds = G <= LDS_MAX_G ? 4 * (size_t)G * sizeof(int) : 0;
-    // up to 128 KiB of dynamic LDS (gfx950 has 160 KiB per CU), allowed once per device
-    static std::atomic<bool> lds_set[64];
-    int dev = 0;
-    HIP_TRY(hipGetDevice(&dev));
-    if (dev < 0 || dev >= 64 || !lds_set[dev].load()) {
-      HIP_TRY(hipFuncSetAttribute((const void*)bucket_scatter_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)(4 * LDS_MAX_G * sizeof(int))));
-      if (dev >= 0 && dev < 64) lds_set[dev].store(true);
-    }
-    hipLaunchKernelGGL(bucket_scatter_kernel, dim3(nb), dim3(256), lds, s, probes, npairs, P, G, b.gstart, b.gcount0,
-                       b.cur0, b.cur1, b.order);
-    HIP_TRY(hipGetLastError());
-  }
 }
 
 }  // namespace hntl

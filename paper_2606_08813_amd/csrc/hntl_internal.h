@@ -81,6 +81,7 @@ struct Index {
   float* bhi = nullptr;        // G x rp: per-grain maximum
   float* emin = nullptr;       // G: per-grain minimum eps_i
   int32_t* gorder = nullptr;   // G: grains by size, largest first (made by the first search plan)
+  int32_t* grank = nullptr;    // G: a grain's place in gorder
   uint16_t* cent_split = nullptr;  // G x 3d bf16: [hi | lo | hi] of the centroids (split-BF16 routing, on first use)
   float* eps_id = nullptr;         // N: eps_i by original row id (Mode A answers, on first use)
   std::unique_ptr<Router> router;  // learned router (trained or imported), else null
@@ -201,27 +202,55 @@ void launch_route_centroid(const Index& ix, const float* Q, int64_t nq, int P, c
 void launch_knn(const float* A, int64_t rows, const float* Bm, int64_t cols, int d, int k, int32_t* ids, float* dist,
                 hipStream_t s);
 
-// grain bucketing of (query, probe) pairs; work-item lists cut from it
+// One work item of the fused kernel, decoded once per run: a projection item
+// (16 pairs of grain g from order[off]) or a scan item (cnt pairs of grain g
+// from order[off] against block range `range`; its pairs' tangents come from
+// projection items c0 .. c1).
+struct ItemDesc {
+  int32_t g, range, off, cnt, c0, c1, pad0, pad1;
+};
+
+// grain bucketing of (query, probe) pairs; work-item lists cut from it.  All
+// per-grain arrays are indexed by rank (grank[g]; the grain number without).
 enum { LIST_SLOT0 = 0, LIST_REST = 1, LIST_ALL = 2 };
 struct ItemLists {
-  int32_t* ioff[3];    // G + 1 each: exclusive prefix of items per grain
-  int32_t* lstart[3];  // G each: first position of the list's pairs of grain g in `order`
-  int32_t* lcount[3];  // G each: number of the list's pairs of grain g
-  int tile[3];         // pairs per work item
+  int32_t* ioff[3];  // G + 1 each: exclusive prefix of items per rank
+  int tile[3];       // pairs per work item
 };
 struct Buckets {
-  int32_t* gcount;   // G: pairs per grain
-  int32_t* gcount0;  // G: probe-slot-0 pairs per grain
-  int32_t* gstart;   // G
-  int32_t* cur0;     // G
-  int32_t* cur1;     // G
-  int32_t* order;    // npairs: pair ids grouped by grain, slot-0 pairs first
+  int G;
+  const int32_t* gorder;       // rank -> grain (null: the same)
+  const int32_t* grank;        // grain -> rank
+  const int32_t* nsplit_rank;  // block ranges per grain (null: 1)
+  int32_t* cnt;                // 2 G: pairs of probe slot 0, then of the other slots
+  int32_t* gstart;             // G: first place of the rank's pairs in `order`
+  int32_t* glist;              // G: first candidate list of the rank's pairs (with lbase)
+  int32_t* slot;               // npairs: a pair's number among its grain's pairs of its kind
+  int32_t* order;              // npairs: pair ids grouped by grain, slot-0 pairs first
+  int32_t* lbase;              // npairs: a pair's first candidate list (null: lists are numbered by pair id)
   ItemLists lists;
   int max_items[3];  // upper bounds of the item counts (grid sizes)
-  int G;
+  // Decoded items (null: none), items_cap the table's size: 0 .. nP-1 are the
+  // projection items (LIST_ALL), then the scan items of LIST_SLOT0 and
+  // LIST_REST (tile x block range), in the lists' item order.
+  ItemDesc* items;
+  int64_t items_cap;
 };
-void launch_bucket(const int32_t* probes, int64_t nq, int P, int G, Buckets& b, hipStream_t s,
-                   const int32_t* gorder = nullptr, const int32_t* nsplit = nullptr, bool counts_zeroed = false);
+// The pairs of list L of one rank: where they start in `order`, and how many.
+struct ListRef {
+  const int32_t *ioff, *gstart, *cnt0, *cnt1;
+  int L;
+  __host__ __device__ int start(int r) const { return gstart[r] + (L == LIST_REST ? cnt0[r] : 0); }
+  __host__ __device__ int count(int r) const {
+    return L == LIST_SLOT0 ? cnt0[r] : L == LIST_REST ? cnt1[r] : cnt0[r] + cnt1[r];
+  }
+};
+inline ListRef list_ref(const Buckets& b, int L) {
+  return ListRef{b.lists.ioff[L], b.gstart, b.cnt, b.cnt + b.G, L};
+}
+// counts_zeroed: b.cnt holds zeros (larger batches fill it first otherwise).
+void launch_bucket(const int32_t* probes, int64_t nq, int P, const Buckets& b, hipStream_t s,
+                   bool counts_zeroed = false);
 // up to 8 fills in one launch (graph-friendly resets)
 struct FillSeg {
   int32_t* p;
@@ -233,20 +262,6 @@ struct FillList {
   int n;
 };
 void launch_fill_multi(const FillList& L, hipStream_t s);
-// One work item of the fused kernel, decoded once per run: a projection item
-// (16 pairs of grain g from order[off]) or a scan item (cnt pairs of grain g
-// from order[off] against block range `range`; its pairs' tangents come from
-// projection items c0 .. c1).
-struct ItemDesc {
-  int32_t g, range, off, cnt, c0, c1, pad0, pad1;
-};
-// Items 0 .. nP-1 are the projection items (LIST_ALL, 16 pairs), then the
-// scan items of LIST_SLOT0 and LIST_REST (qt pairs x block ranges), in the
-// lists' item order; threads past the device item count write nothing.
-void launch_item_table(const ItemLists& lists, const int32_t* gorder, int G, int qt, int64_t max_items,
-                       ItemDesc* out, hipStream_t s);
-void launch_pair_lists(const int32_t* probes, int64_t nq, int P, int G, const int32_t* nsplit, int32_t* lbase,
-                       int32_t* qoff, hipStream_t s);
 void launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
 
 constexpr int PROJECT_TILE = 64;  // pairs per workgroup of the shared-basis projection kernel
@@ -254,9 +269,8 @@ constexpr int PROJECT_TILE = 64;  // pairs per workgroup of the shared-basis pro
 // shared-basis kernel applies (vector loads: d % 4 == 0 FP32, d % 8 == 0 BF16,
 // 16-byte aligned Q), else 16.
 int project_tile(const Index& ix, const float* Q, bool bf16);
-// gorder: the rank -> grain map when the buckets were built in that order (ioff by rank), else null
 void launch_project(const Index& ix, const float* Q, int P, const Buckets& b, float* T, float* epsq, bool bf16,
-                    const int32_t* gorder, hipStream_t s);  // over LIST_ALL
+                    hipStream_t s);  // over LIST_ALL
 // Scan of the bucketed pairs.  With `bound_lists` (the lists of probe slot 0,
 // already written into part), each pair starts from its query's C-th key of
 // slot 0 as threshold and, when `prune`, is skipped outright if an exact
@@ -277,11 +291,13 @@ void launch_segmented_mean(const float* X, int d, const int32_t* order, const in
                            float* cent, hipStream_t s);
 // eps_i by original id, made once (Mode A).
 void ensure_eps_by_id(Index& ix, hipStream_t s);
-// eps_id != null: Mode A (reconstruction distances of the pool, no raw vectors).
+// lbase, nsplit: pair p of grain g owns the nsplit[g] lists from lbase[p] (null:
+// the list of its number).  eps_id != null: Mode A (reconstruction distances of the pool, no raw vectors).
 void launch_merge_rerank(const Index& ix, const float* Q, int64_t nq, int P, int C, int k,
                          const int32_t* probes, const uint64_t* part, const int32_t* pool_in, int32_t* pool_out,
                          float* pool_D_out, int32_t* ids, float* dist, hipStream_t s,
-                         const int32_t* qoff = nullptr, const float* eps_id = nullptr,
+                         const int32_t* lbase = nullptr, const int32_t* nsplit = nullptr,
+                         const float* eps_id = nullptr,
                          const int32_t* nlim = nullptr);  // rows from *nlim on: -1 / +inf only
 
 // Persistent fused project-scan-select kernel (the batching form).  Its
@@ -309,9 +325,6 @@ struct FusedArgs {
   const float* Q;
   // work items
   const int32_t* ioff[3];  // indexed by grain rank
-  const int32_t* lstart[3];
-  const int32_t* lcount[3];
-  const int32_t* gorder;
   const int32_t* order;
   const int32_t* lbase;  // per pair: first list slot (null: the pair id)
   int R;

@@ -9,8 +9,8 @@
 //          bounds; graphs hold kernel nodes only)
 //   routing          row norms, centroid distances (own MFMA GEMMs with a
 //                    distance epilogue), top-P + exact re-score
-//   bucketing        pairs grouped by grain, items numbered largest grain first
-//   pair lists       per-pair list slots when grains are split into ranges
+//   bucketing        pairs grouped by grain, items numbered largest grain first,
+//                    per-pair list slots when grains are split into ranges
 //   fused kernel     projection + scan + per-list top-C (persistent)
 //   merge + rerank   pool = exact top C over the query's lists, FP32 rerank
 //
@@ -106,7 +106,11 @@ void ensure_grain_order(Index& ix) {
   std::stable_sort(o.begin(), o.end(), [&](int32_t a, int32_t b) {
     return ix.offsets_h[a + 1] - ix.offsets_h[a] > ix.offsets_h[b + 1] - ix.offsets_h[b];
   });
+  std::vector<int32_t> rank(ix.G);
+  for (uint32_t i = 0; i < ix.G; ++i) rank[o[i]] = (int32_t)i;
   int32_t* d = dev_alloc<int32_t>(&ix, ix.G);
+  if (!ix.grank) ix.grank = dev_alloc<int32_t>(&ix, ix.G);
+  HIP_TRY(hipMemcpy(ix.grank, rank.data(), sizeof(int32_t) * ix.G, hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(d, o.data(), sizeof(int32_t) * ix.G, hipMemcpyHostToDevice));
   ix.gorder = d;
 }
@@ -151,16 +155,13 @@ struct Plan {
   RouteScratch route;
   // bucketing
   Buckets b{};
-  int32_t* nsplit = nullptr;
-  int32_t* lbase = nullptr;
-  int32_t* qoff = nullptr;
+  int32_t* nsplit = nullptr;       // block ranges per grain
+  int32_t* nsplit_rank = nullptr;  // the same by rank
   // fused kernel state
   FusedArgs* args_dev = nullptr;
   int32_t* ticket = nullptr;
   int32_t* proj_done = nullptr;  // one flag per projection item
   int64_t proj_items = 0;
-  ItemDesc* items = nullptr;  // decoded work items of the fused kernel
-  int64_t max_items = 0;
   uint32_t* qbound = nullptr;
   int32_t* err = nullptr;
   float* T = nullptr;
@@ -206,31 +207,30 @@ struct Plan {
       route.layout(rb, x, max_nq, form);
     }
     b.G = (int)x.G;
-    b.gcount = L.take<int32_t>(x.G);
-    b.gcount0 = L.take<int32_t>(x.G);
+    b.gorder = x.gorder;
+    b.grank = x.grank;
+    b.cnt = L.take<int32_t>(2 * (size_t)x.G);
     b.gstart = L.take<int32_t>(x.G);
-    b.cur0 = L.take<int32_t>(x.G);
-    b.cur1 = L.take<int32_t>(x.G);
+    b.glist = L.take<int32_t>(x.G);
+    b.slot = L.take<int32_t>(np);
     b.order = L.take<int32_t>(np);
-    for (int l = 0; l < 3; ++l) {
-      b.lists.ioff[l] = L.take<int32_t>(x.G + 1);
-      b.lists.lstart[l] = L.take<int32_t>(x.G);
-      b.lists.lcount[l] = L.take<int32_t>(x.G);
-    }
+    for (int l = 0; l < 3; ++l) b.lists.ioff[l] = L.take<int32_t>(x.G + 1);
     b.lists.tile[LIST_SLOT0] = b.lists.tile[LIST_REST] = (int)sch.qt;  // scan item: qt pairs (one wave)
     // projection item: 16 pairs, one wave, inside the fused kernel; with a
     // separate projection launch, the shared-basis kernel's item where it applies
     b.lists.tile[LIST_ALL] = sch.proj ? project_tile(x, Q, (sp.flags & HNTL_FLAG_PROJECT_BF16) != 0) : 16;
     b.max_items[LIST_ALL] = (int)(np / b.lists.tile[LIST_ALL] + std::min<int64_t>(x.G, np) + 1);
     nsplit = L.take<int32_t>(x.G);
-    lbase = L.take<int32_t>(np);
-    qoff = L.take<int32_t>((size_t)max_nq + 1);
+    nsplit_rank = L.take<int32_t>(x.G);
+    b.nsplit_rank = sch.range ? nsplit_rank : nullptr;
+    int32_t* lb = L.take<int32_t>(np);
+    b.lbase = sch.range ? lb : nullptr;
     args_dev = L.take<FusedArgs>(3);  // phases 0, 1, 2
     ticket = L.take<int32_t>(2 * TICKET_INTS);  // counters of each launch (phases 0/1 and 2)
     proj_items = (int64_t)((np + 15) / 16) + x.G;  // at most sum over grains of ceil(pairs / 16)
     proj_done = L.take<int32_t>(proj_items);
-    max_items = proj_items + (int64_t)list_slots;  // projection items + at most one scan item per list
-    items = L.take<ItemDesc>((size_t)max_items);
+    b.items_cap = proj_items + (int64_t)list_slots;  // projection items + at most one scan item per list
+    b.items = L.take<ItemDesc>((size_t)b.items_cap);
     qbound = L.take<uint32_t>(max_nq);
     err = L.take<int32_t>(1);
     T = L.take<float>((size_t)np * x.r);
@@ -277,14 +277,9 @@ struct Plan {
     a.P = (int)sp.P;
     a.C = (int)sp.C;
     a.Q = Q;
-    for (int l = 0; l < 3; ++l) {
-      a.ioff[l] = b.lists.ioff[l];
-      a.lstart[l] = b.lists.lstart[l];
-      a.lcount[l] = b.lists.lcount[l];
-    }
-    a.gorder = x.gorder;
+    for (int l = 0; l < 3; ++l) a.ioff[l] = b.lists.ioff[l];
     a.order = b.order;
-    a.lbase = sch.range ? lbase : nullptr;
+    a.lbase = b.lbase;
     a.R = (int)sch.range;
     a.ticket = ticket;
     a.proj_done = proj_done;
@@ -296,7 +291,7 @@ struct Plan {
     a.scored = scored;
     a.proj_bf16 = (sp.flags & HNTL_FLAG_PROJECT_BF16) ? 1 : 0;
     a.proj_ext = sch.proj ? 1 : 0;
-    a.items = items;
+    a.items = b.items;
     a.prune = (sp.flags & HNTL_FLAG_NO_PRUNE) ? 0 : 1;
     return a;
   }
@@ -307,16 +302,15 @@ struct Plan {
   // rerank.
   void enqueue(hipStream_t s, hipEvent_t* ev = nullptr) {
     const Index& x = *ix;
-    const int P = (int)sp.P, G = (int)x.G;
+    const int P = (int)sp.P;
     if (ev) HIP_TRY(hipEventRecord(ev[0], s));
     FillList f{};
     f.seg[0] = FillSeg{ticket, 2 * TICKET_INTS, 0};
     f.seg[1] = FillSeg{reinterpret_cast<int32_t*>(scored), 2, 0};
     f.seg[2] = FillSeg{proj_done, proj_items, 0};
     f.seg[3] = FillSeg{reinterpret_cast<int32_t*>(qbound), (int64_t)max_nq, -1};
-    f.seg[4] = FillSeg{b.gcount, G, 0};
-    f.seg[5] = FillSeg{b.gcount0, G, 0};
-    f.n = 6;
+    f.seg[4] = FillSeg{b.cnt, 2 * (int64_t)x.G, 0};
+    f.n = 5;
     launch_fill_multi(f, s);
     // routing reads the batch size from nq_dev: rows past it get probes -1
     if (sp.route == HNTL_ROUTE_LEARNED)
@@ -324,11 +318,9 @@ struct Plan {
     else
       launch_route_centroid(x, Q, max_nq, P, route, probes, nullptr, s, nq_dev);
     if (ev) HIP_TRY(hipEventRecord(ev[1], s));
-    launch_bucket(probes, max_nq, P, G, b, s, x.gorder, nsplit, true);
-    if (sch.range) launch_pair_lists(probes, max_nq, P, G, nsplit, lbase, qoff, s);
-    launch_item_table(b.lists, x.gorder, G, (int)sch.qt, max_items, items, s);
+    launch_bucket(probes, max_nq, P, b, s, true);
     if (ev) HIP_TRY(hipEventRecord(ev[2], s));
-    if (sch.proj) launch_project(x, Q, P, b, T, epsq, (sp.flags & HNTL_FLAG_PROJECT_BF16) != 0, x.gorder, s);
+    if (sch.proj) launch_project(x, Q, P, b, T, epsq, (sp.flags & HNTL_FLAG_PROJECT_BF16) != 0, s);
     if (ev) HIP_TRY(hipEventRecord(ev[3], s));
     for (int ph = sch.passes == 2 ? 1 : 0; ph <= (sch.passes == 2 ? 2 : 0); ++ph) {
       if (!fused_launch((int)sp.codes, args_dev + ph, (int)x.rp, (int)sp.C, (int)sch.qt, (int)sch.nw, (int)sch.grid,
@@ -338,7 +330,7 @@ struct Plan {
     }
     if (ev) HIP_TRY(hipEventRecord(ev[4], s));
     launch_merge_rerank(x, Q, max_nq, P, (int)sp.C, (int)sp.k, probes, part, nullptr, nullptr, nullptr, ids, dist, s,
-                        sch.range ? qoff : nullptr, (sp.flags & HNTL_FLAG_MODE_A) ? x.eps_id : nullptr, nq_dev);
+                        b.lbase, nsplit, (sp.flags & HNTL_FLAG_MODE_A) ? x.eps_id : nullptr, nq_dev);
     if (ev) HIP_TRY(hipEventRecord(ev[5], s));
   }
 
@@ -453,6 +445,10 @@ Plan* make_plan(Index& ix, const hntl_search_params& sp, uint32_t max_nq, const 
   HIP_TRY(hipMemsetAsync(pl->Q, 0, sizeof(float) * (size_t)max_nq * ix.d, s));
   HIP_TRY(hipMemsetAsync(pl->err, 0, sizeof(int32_t), s));
   HIP_TRY(hipMemcpyAsync(pl->nsplit, ns.data(), sizeof(int32_t) * ix.G, hipMemcpyHostToDevice, s));
+  std::vector<int32_t> order(ix.G), nsr(ix.G);
+  HIP_TRY(hipMemcpy(order.data(), ix.gorder, sizeof(int32_t) * ix.G, hipMemcpyDeviceToHost));
+  for (uint32_t i = 0; i < ix.G; ++i) nsr[i] = ns[order[i]];
+  HIP_TRY(hipMemcpyAsync(pl->nsplit_rank, nsr.data(), sizeof(int32_t) * ix.G, hipMemcpyHostToDevice, s));
   FusedArgs a[3];
   for (int ph = 0; ph < 3; ++ph) {
     a[ph] = pl->make_args();

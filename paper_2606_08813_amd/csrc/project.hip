@@ -20,31 +20,30 @@ using namespace proj_detail;
 template <bool VEC, int NCT>
 __global__ __launch_bounds__(64) void project_kernel(
     const float* __restrict__ Q, int d, int P, const float* __restrict__ centroids, const float* __restrict__ basis,
-    int r, const int32_t* __restrict__ ioff, const int32_t* __restrict__ lstart, const int32_t* __restrict__ lcount,
-    int G, const int32_t* __restrict__ gorder, const int32_t* __restrict__ order, float* __restrict__ T,
+    int r, ListRef list, int G, const int32_t* __restrict__ gorder, const int32_t* __restrict__ order,
+    float* __restrict__ T,
     float* __restrict__ epsq) {
   int rank;
-  if (!item_grain(ioff, G, blockIdx.x, rank)) return;
+  if (!item_grain(list.ioff, G, blockIdx.x, rank)) return;
   const int g = gorder ? gorder[rank] : rank;
-  const int first = (blockIdx.x - ioff[rank]) * PT;  // within the grain's pairs
-  const int cnt = min(PT, lcount[g] - first);
+  const int first = (blockIdx.x - list.ioff[rank]) * PT;  // within the grain's pairs
+  const int cnt = min(PT, list.count(rank) - first);
   if (cnt <= 0) return;
-  project_wave<VEC, NCT>(Q, d, P, centroids, basis, r, g, order + lstart[g] + first, cnt, T, epsq);
+  project_wave<VEC, NCT>(Q, d, P, centroids, basis, r, g, order + list.start(rank) + first, cnt, T, epsq);
 }
 
 template <int NCT>
 __global__ __launch_bounds__(64) void project_bf16_kernel(
     const float* __restrict__ Q, int d, int P, const float* __restrict__ centroids,
-    const uint16_t* __restrict__ basis16, int r, const int32_t* __restrict__ ioff, const int32_t* __restrict__ lstart,
-    const int32_t* __restrict__ lcount, int G, const int32_t* __restrict__ gorder, const int32_t* __restrict__ order,
-    float* __restrict__ T, float* __restrict__ epsq) {
+    const uint16_t* __restrict__ basis16, int r, ListRef list, int G, const int32_t* __restrict__ gorder,
+    const int32_t* __restrict__ order, float* __restrict__ T, float* __restrict__ epsq) {
   int rank;
-  if (!item_grain(ioff, G, blockIdx.x, rank)) return;
+  if (!item_grain(list.ioff, G, blockIdx.x, rank)) return;
   const int g = gorder ? gorder[rank] : rank;
-  const int first = (blockIdx.x - ioff[rank]) * PT;
-  const int cnt = min(PT, lcount[g] - first);
+  const int first = (blockIdx.x - list.ioff[rank]) * PT;
+  const int cnt = min(PT, list.count(rank) - first);
   if (cnt <= 0) return;
-  project_wave_bf16<NCT>(Q, d, P, centroids, basis16, r, g, order + lstart[g] + first, cnt, T, epsq);
+  project_wave_bf16<NCT>(Q, d, P, centroids, basis16, r, g, order + list.start(rank) + first, cnt, T, epsq);
 }
 
 // ---- shared-basis form
@@ -75,9 +74,8 @@ __device__ __forceinline__ int xcd_item(int b) {
 template <bool BF16, int NCT, int NW>
 __global__ __launch_bounds__(64 * NW) void project_lds_kernel(
     const float* __restrict__ Q, int d, int P, const float* __restrict__ centroids, const float* __restrict__ basis,
-    const uint16_t* __restrict__ basis16, int r, const int32_t* __restrict__ ioff, const int32_t* __restrict__ lstart,
-    const int32_t* __restrict__ lcount, int G, const int32_t* __restrict__ gorder, const int32_t* __restrict__ order,
-    float* __restrict__ T, float* __restrict__ epsq) {
+    const uint16_t* __restrict__ basis16, int r, ListRef list, int G, const int32_t* __restrict__ gorder,
+    const int32_t* __restrict__ order, float* __restrict__ T, float* __restrict__ epsq) {
   using E = std::conditional_t<BF16, uint16_t, float>;
   constexpr int ROWS = 16 * NCT;
   constexpr int EPV = 16 / (int)sizeof(E);    // elements per 16-byte vector
@@ -92,13 +90,13 @@ __global__ __launch_bounds__(64 * NW) void project_lds_kernel(
 
   const int item = xcd_item((int)blockIdx.x);
   int rank;
-  if (!item_grain(ioff, G, item, rank)) return;  // uniform over the workgroup
+  if (!item_grain(list.ioff, G, item, rank)) return;  // uniform over the workgroup
   const int wave = (int)threadIdx.x >> 6, lane = lane_id();
   const int i = lane & 15, kq = lane >> 4;
   const int g = gorder ? gorder[rank] : rank;
-  const int first = (item - ioff[rank]) * (16 * NW) + 16 * wave;  // within the grain's pairs
-  const int cnt = __builtin_amdgcn_readfirstlane(min(16, lcount[g] - first));  // <= 0: this wave only stages
-  const int32_t* pairs = order + lstart[g] + (first < 0 ? 0 : first);
+  const int first = (item - list.ioff[rank]) * (16 * NW) + 16 * wave;  // within the grain's pairs
+  const int cnt = __builtin_amdgcn_readfirstlane(min(16, list.count(rank) - first));  // <= 0: this wave only stages
+  const int32_t* pairs = order + list.start(rank) + (first < 0 ? 0 : first);
   const int qrow = i < cnt ? ldg(pairs + i) / P : -1;
   const float* qp = Q + (size_t)(qrow < 0 ? 0 : qrow) * d;
   const float* mu = centroids + (size_t)g * d;
@@ -218,37 +216,33 @@ __global__ __launch_bounds__(64 * NW) void project_lds_kernel(
 
 template <bool BF16, bool VEC, int NCT>
 void launch_project_k(const Index& ix, const float* Q, int P, const Buckets& b, float* T, float* epsq,
-                      const int32_t* gorder, hipStream_t s) {
-  const ItemLists& L = b.lists;
-  const int tile = L.tile[LIST_ALL];
+                      hipStream_t s) {
+  const ListRef list = list_ref(b, LIST_ALL);
+  const int tile = b.lists.tile[LIST_ALL];
   if (tile == PROJECT_TILE && VEC) {
     constexpr int NW = PROJECT_TILE / PT, M = 8 * XRUN;
     const dim3 grid((unsigned)((b.max_items[LIST_ALL] + M - 1) / M * M)), block(64 * NW);
     hipLaunchKernelGGL((project_lds_kernel<BF16, NCT, NW>), grid, block, 0, s, Q, (int)ix.d, P, ix.centroids,
-                       ix.basis, ix.basis_bf16, (int)ix.r, L.ioff[LIST_ALL], L.lstart[LIST_ALL], L.lcount[LIST_ALL],
-                       (int)ix.G, gorder, b.order, T, epsq);
+                       ix.basis, ix.basis_bf16, (int)ix.r, list, (int)ix.G, b.gorder, b.order, T, epsq);
     return;
   }
   if (tile != PT) throw ArgError{HNTL_EDEVICE, "projection item size must be 16 pairs (or PROJECT_TILE, vector form)"};
   const dim3 grid((unsigned)b.max_items[LIST_ALL]), block(64);
   if constexpr (BF16)
     hipLaunchKernelGGL((project_bf16_kernel<NCT>), grid, block, 0, s, Q, (int)ix.d, P, ix.centroids, ix.basis_bf16,
-                       (int)ix.r, L.ioff[LIST_ALL], L.lstart[LIST_ALL], L.lcount[LIST_ALL], (int)ix.G, gorder, b.order,
-                       T, epsq);
+                       (int)ix.r, list, (int)ix.G, b.gorder, b.order, T, epsq);
   else
     hipLaunchKernelGGL((project_kernel<VEC, NCT>), grid, block, 0, s, Q, (int)ix.d, P, ix.centroids, ix.basis,
-                       (int)ix.r, L.ioff[LIST_ALL], L.lstart[LIST_ALL], L.lcount[LIST_ALL], (int)ix.G, gorder,
-                       b.order, T, epsq);
+                       (int)ix.r, list, (int)ix.G, b.gorder, b.order, T, epsq);
 }
 
 template <bool BF16, bool VEC>
-void launch_project_w(const Index& ix, const float* Q, int P, const Buckets& b, float* T, float* epsq,
-                      const int32_t* gorder, hipStream_t s) {
+void launch_project_w(const Index& ix, const float* Q, int P, const Buckets& b, float* T, float* epsq, hipStream_t s) {
   switch ((ix.r + 15) / 16) {
-    case 1: launch_project_k<BF16, VEC, 1>(ix, Q, P, b, T, epsq, gorder, s); break;
-    case 2: launch_project_k<BF16, VEC, 2>(ix, Q, P, b, T, epsq, gorder, s); break;
-    case 3: launch_project_k<BF16, VEC, 3>(ix, Q, P, b, T, epsq, gorder, s); break;
-    default: launch_project_k<BF16, VEC, 4>(ix, Q, P, b, T, epsq, gorder, s); break;
+    case 1: launch_project_k<BF16, VEC, 1>(ix, Q, P, b, T, epsq, s); break;
+    case 2: launch_project_k<BF16, VEC, 2>(ix, Q, P, b, T, epsq, s); break;
+    case 3: launch_project_k<BF16, VEC, 3>(ix, Q, P, b, T, epsq, s); break;
+    default: launch_project_k<BF16, VEC, 4>(ix, Q, P, b, T, epsq, s); break;
   }
 }
 
@@ -258,17 +252,17 @@ int project_tile(const Index& ix, const float* Q, bool bf16) {
 }
 
 void launch_project(const Index& ix, const float* Q, int P, const Buckets& b, float* T, float* epsq, bool bf16,
-                    const int32_t* gorder, hipStream_t s) {
+                    hipStream_t s) {
   if (b.max_items[LIST_ALL] <= 0) return;
   if (bf16) {
     if (!ix.basis_bf16) throw ArgError{HNTL_ESTATE, "BF16 projection needs the BF16 basis (build a reduced-precision code form)"};
     if ((ix.d % 8) != 0 || ((uintptr_t)Q % 16) != 0)
       throw ArgError{HNTL_EUNSUPPORTED, "BF16 projection needs d % 8 == 0 and 16-byte aligned queries"};
-    launch_project_w<true, true>(ix, Q, P, b, T, epsq, gorder, s);
+    launch_project_w<true, true>(ix, Q, P, b, T, epsq, s);
   } else if ((ix.d % 4) == 0 && ((uintptr_t)Q % 16) == 0) {
-    launch_project_w<false, true>(ix, Q, P, b, T, epsq, gorder, s);
+    launch_project_w<false, true>(ix, Q, P, b, T, epsq, s);
   } else {
-    launch_project_w<false, false>(ix, Q, P, b, T, epsq, gorder, s);
+    launch_project_w<false, false>(ix, Q, P, b, T, epsq, s);
   }
   HIP_TRY(hipGetLastError());
 }

@@ -26,7 +26,8 @@ __global__ __launch_bounds__(256) void merge_rerank_kernel(const float* __restri
                                                            const float* __restrict__ X, int32_t* __restrict__ pool_out,
                                                            float* __restrict__ pool_D_out, int32_t* __restrict__ ids,
                                                            float* __restrict__ dist, bool vec4,
-                                                           const int32_t* __restrict__ qoff,
+                                                           const int32_t* __restrict__ lbase,
+                                                           const int32_t* __restrict__ nsplit,
                                                            const float* __restrict__ eps_id, int64_t nrows,
                                                            const int32_t* __restrict__ nlim) {
   __shared__ uint64_t lst[2 * CAP];
@@ -46,67 +47,40 @@ __global__ __launch_bounds__(256) void merge_rerank_kernel(const float* __restri
   }
 
   if (pool_in == nullptr) {
-    if constexpr (CAP == 64) {
-      if (wave == 0) {
-        WaveTop64 L;
-        L.init(lst, C);
-        // the query's lists: one per probe, or (grains split into block
-        // ranges) the contiguous run qoff[q] .. qoff[q + 1]
-        const int64_t l0 = qoff ? qoff[q] : q * P;
-        const int nl = qoff ? qoff[q + 1] - qoff[q] : P;
-        const uint64_t* src = part + (size_t)l0 * C;
-        constexpr int U = 4;  // lists loaded together
-        for (int s0 = 0; s0 < nl; s0 += U) {
-          uint64_t key[U];
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const int s = s0 + u;
-            bool ok = s < nl;
-            if (ok && !qoff) {
-              const int g = probes[q * P + s];
-              ok = g >= 0 && g < G;  // invalid probe: its list was never written
-            }
-            key[u] = (ok && lane < C) ? src[(size_t)s * C + lane] : KEY_NONE;
-          }
-          // lists hold their keys in any order (a non-empty one with a key
-          // first); a pruned list holds one KEY_NONE and nothing else written:
-          // skip it whole
-#pragma unroll
-          for (int u = 0; u < U; ++u)
-            if (lane_u64(key[u], 0) != KEY_NONE) L.offer(key[u], key[u] != KEY_NONE);
-        }
-        L.finish();
-        if (lane < C) {
-          const int32_t id = L.best == KEY_NONE ? -1 : (int32_t)key_id(L.best);
-          pool[lane] = id;
-          // Mode A: eq. 6 minus eps_i is the reconstruction distance ||z_q - z_i||^2 + eps_q
-          if (eps_id) delta[lane] = id < 0 ? __builtin_inff() : key_dist(L.best) - eps_id[id];
-          if (pool_out) pool_out[q * C + lane] = id;
-          if (pool_D_out) pool_D_out[q * C + lane] = L.best == KEY_NONE ? __builtin_inff() : key_dist(L.best);
-        }
-      }
-    } else if (wave == 0) {
+    if (wave == 0) {
       WaveTopR<CAP / 64> L;
       L.init(lst, C);
-      const int64_t l0 = qoff ? qoff[q] : q * P;
-      const int nl = qoff ? qoff[q + 1] - qoff[q] : P;
-      const uint64_t* src = part + (size_t)l0 * C;
-      constexpr int NR = CAP / 64, U = 2;  // lists loaded together
-      for (int s0 = 0; s0 < nl; s0 += U) {
+      // lane t: probe slot t's lists, its first and their number (an invalid
+      // probe has none); the walk over them is wave-uniform
+      const int32_t g = lane < P ? probes[q * P + lane] : -1;
+      const bool ok = g >= 0 && g < G;
+      const int own = !ok ? 0 : lbase ? nsplit[g] : 1;
+      const int first = !ok ? 0 : lbase ? lbase[q * P + lane] : (int)(q * P + lane);
+      uint64_t slots = __ballot(own > 0);
+      int at = 0, left = 0;
+      auto next = [&]() {  // the next list's number, -1 past the last
+        if (left == 0) {
+          if (slots == 0) return -1;
+          const int t = __builtin_ctzll(slots);
+          slots &= slots - 1;
+          at = __builtin_amdgcn_readlane(first, t);
+          left = __builtin_amdgcn_readlane(own, t);
+        }
+        --left;
+        return at++;
+      };
+      constexpr int NR = CAP / 64, U = CAP == 64 ? 4 : 2;  // lists loaded together
+      for (int l = next(); l >= 0;) {
         uint64_t key[U][NR];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          const int s = s0 + u;
-          bool ok = s < nl;
-          if (ok && !qoff) {
-            const int g = probes[q * P + s];
-            ok = g >= 0 && g < G;  // invalid probe: its list was never written
-          }
+          const uint64_t* src = part + (size_t)(l < 0 ? 0 : l) * C;
 #pragma unroll
           for (int r = 0; r < NR; ++r) {
             const int c = r * 64 + lane;
-            key[u][r] = (ok && c < C) ? src[(size_t)s * C + c] : KEY_NONE;
+            key[u][r] = (l >= 0 && c < C) ? src[c] : KEY_NONE;
           }
+          if (l >= 0) l = next();
         }
         // lists hold their keys in any order, KEY_NONE-padded, a non-empty
         // one with a key first; a pruned list holds one KEY_NONE and nothing
@@ -125,6 +99,7 @@ __global__ __launch_bounds__(256) void merge_rerank_kernel(const float* __restri
         const uint64_t key = L.best[rr];
         const int32_t id = key == KEY_NONE ? -1 : (int32_t)key_id(key);
         pool[c] = id;
+        // Mode A: eq. 6 minus eps_i is the reconstruction distance ||z_q - z_i||^2 + eps_q
         if (eps_id) delta[c] = id < 0 ? __builtin_inff() : key_dist(key) - eps_id[id];
         if (pool_out) pool_out[q * C + c] = id;
         if (pool_D_out) pool_D_out[q * C + c] = key == KEY_NONE ? __builtin_inff() : key_dist(key);
@@ -263,7 +238,8 @@ void ensure_eps_by_id(Index& ix, hipStream_t s) {
 void launch_merge_rerank(const Index& ix, const float* Q, int64_t nq, int P, int C, int k, const int32_t* probes,
                          const uint64_t* part,
                          const int32_t* pool_in, int32_t* pool_out, float* pool_D_out, int32_t* ids, float* dist,
-                         hipStream_t s, const int32_t* qoff, const float* eps_id, const int32_t* nlim) {
+                         hipStream_t s, const int32_t* lbase, const int32_t* nsplit, const float* eps_id,
+                         const int32_t* nlim) {
   if (nq <= 0) return;
   if (eps_id && pool_in) throw ArgError{HNTL_EUNSUPPORTED, "Mode A answers need the merged pool, not an injected one"};
   if (!eps_id && !ix.X) throw ArgError{HNTL_ESTATE, "this index holds no raw vectors: only Mode A searches"};
@@ -275,7 +251,7 @@ void launch_merge_rerank(const Index& ix, const float* Q, int64_t nq, int P, int
 #define HNTL_MR(CAPV, RRV, JUV)                                                                                  \
   hipLaunchKernelGGL((merge_rerank_kernel<CAPV, RRV, JUV, true>), grid, dim3(256), 0, s, Q, (int)ix.d, P, C, k,      \
                      (int)ix.G, (int64_t)ix.N, probes, part, pool_in, ix.X, pool_out, pool_D_out, ids, dist, vec4,   \
-                     qoff, eps_id, nq, nlim)
+                     lbase, nsplit, eps_id, nq, nlim)
   const bool narrow = ix.d <= 4 * HNTL_WAVE;
   if (cap == 64) {
     if (narrow)

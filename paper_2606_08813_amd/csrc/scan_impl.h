@@ -176,9 +176,7 @@ template <int RP, int CAP, int QT, int CT>
 __global__ __launch_bounds__(64 * (ITEM / QT)) void scan_f32_kernel(
     const void* __restrict__ codes, const float* __restrict__ scales, const float* __restrict__ eps, const int32_t* __restrict__ goff,
     const int32_t* __restrict__ boff, const int32_t* __restrict__ perm, int r, const float* __restrict__ T,
-    const float* __restrict__ epsq, int P, int C, const int32_t* __restrict__ ioff,
-    const int32_t* __restrict__ lstart, const int32_t* __restrict__ lcount, int G,
-    const int32_t* __restrict__ order, uint64_t* __restrict__ part, const uint64_t* __restrict__ bound_lists,
+    const float* __restrict__ epsq, int P, int C, ListRef list, int G, const int32_t* __restrict__ order, uint64_t* __restrict__ part, const uint64_t* __restrict__ bound_lists,
     int prune, const float* __restrict__ blo, const float* __restrict__ bhi, const float* __restrict__ emin,
     unsigned long long* __restrict__ scored) {
   using List = typename ListOf<CAP>::type;
@@ -190,12 +188,12 @@ __global__ __launch_bounds__(64 * (ITEM / QT)) void scan_f32_kernel(
   float (*zq)[RP] = zq_all[wave];
   float* eq = eq_all[wave];
   int g;
-  if (!item_grain(ioff, G, blockIdx.x, g)) return;
-  const int first = (blockIdx.x - ioff[g]) * ITEM;
-  const int total = min(ITEM, lcount[g] - first);
+  if (!item_grain(list.ioff, G, blockIdx.x, g)) return;
+  const int first = (blockIdx.x - list.ioff[g]) * ITEM;
+  const int total = min(ITEM, list.count(g) - first);
   const int sub = wave * QT;
   if (sub >= total) return;  // no workgroup barrier below: idle waves may leave
-  const int32_t* pairs = order + lstart[g] + first + sub;
+  const int32_t* pairs = order + list.start(g) + first + sub;
   const int cnt = min(QT, total - sub);
   const int pos0 = goff[g];
   const int ng = goff[g + 1] - pos0;
@@ -386,16 +384,15 @@ void launch_rp_cap(const Index& ix, const float* T, const float* epsq, int P, in
                               : (const void*)ix.codes_i16;
   const float* scales = CT == 3 ? ix.i16_steps : ix.scales;
   const float* eps = CT == 3 ? ix.eps_i16 : ix.eps;
-  const ItemLists& Ls = b.lists;
+  const ListRef ref = list_ref(b, list);
   if (bound_lists == nullptr)
     hipLaunchKernelGGL((scan_f32_kernel<RP, CAP, 4, CT>), grid, dim3(64 * (ITEM / 4)), 0, s, codes, scales, eps,
                        ix.goff,
-                       ix.boff, ix.perm, (int)ix.r, T, epsq, P, C, Ls.ioff[list], Ls.lstart[list], Ls.lcount[list],
-                       (int)ix.G, b.order, part, bound_lists, prune ? 1 : 0, ix.blo, ix.bhi, ix.emin, scored);
+                       ix.boff, ix.perm, (int)ix.r, T, epsq, P, C, ref, (int)ix.G, b.order, part, bound_lists, prune ? 1 : 0, ix.blo, ix.bhi, ix.emin, scored);
   else
     hipLaunchKernelGGL((scan_f32_kernel<RP, CAP, QT_WIDE, CT>), grid, dim3(64 * (ITEM / QT_WIDE)), 0, s, codes,
-                       scales, eps, ix.goff, ix.boff, ix.perm, (int)ix.r, T, epsq, P, C, Ls.ioff[list], Ls.lstart[list],
-                       Ls.lcount[list], (int)ix.G, b.order, part, bound_lists, prune ? 1 : 0, ix.blo, ix.bhi, ix.emin, scored);
+                       scales, eps, ix.goff, ix.boff, ix.perm, (int)ix.r, T, epsq, P, C, ref,
+                       (int)ix.G, b.order, part, bound_lists, prune ? 1 : 0, ix.blo, ix.bhi, ix.emin, scored);
 }
 
 template <int RP, int CT>

@@ -22,7 +22,7 @@ hntl_status fail(hntl_status s, const std::string& msg) {
 Index::~Index() {
   void* ptrs[] = {centroids, cnorm,    basis,   goff,      boff,     perm,       codes,  eps,
                   codes_bf16, codes_fp8, scales, basis_bf16, codes_i16, i16_steps, eps_i16, X,
-                  blo,       bhi,       emin,   gorder, grank, cent_split, eps_id};
+                  blo,       bhi,       emin,   rmax,   gorder,     grank,  cent_split, eps_id};
   int prev = 0;
   (void)hipGetDevice(&prev);
   (void)hipSetDevice(device);
@@ -237,6 +237,8 @@ struct StagedScratch {
   float* T = nullptr;
   float* eq = nullptr;
   uint64_t* part = nullptr;
+  bool prune = false;         // slot 0 first, then what the pruning keeps (see run_staged)
+  int32_t* kept = nullptr;
 
   size_t layout(char* base, const Index& ix, const float* Q, uint32_t nq, const hntl_search_params& sp,
                 const StagedIO& io) {
@@ -262,7 +264,7 @@ struct StagedScratch {
       }
     }
     b.G = (int)ix.G;
-    b.cnt = (int32_t*)take(8 * (size_t)ix.G);
+    b.cnt = (int32_t*)take(8 * (size_t)bucket_counters(ix.G));  // two bucketings' counts
     b.gstart = (int32_t*)take(4 * (size_t)ix.G);
     b.order = (int32_t*)take(4 * (size_t)npairs);
     // the projection item size depends only on d, the code form and Q's alignment
@@ -278,6 +280,10 @@ struct StagedScratch {
       if (!io.epsq_out) eq = (float*)take(4 * (size_t)npairs);
     }
     part = (uint64_t*)take(8 * (size_t)npairs * sp.C);
+    // tangents that the caller observes or injects are of every pair
+    prune = !io.tangent_in && !io.tangent_out && !io.epsq_out && prune_pays(ix, sp, nq);
+    kept = prune && (io.probes_in || io.probes_out) ? (int32_t*)take(4 * (size_t)npairs)
+                                                    : probes;  // own probes are cut in place
     b.slot = (int32_t*)part;  // read before the first list is written
     return off;
   }
@@ -303,42 +309,67 @@ void run_staged(const Index& ix, const float* Q, uint32_t nq, const hntl_search_
   const int32_t* probes = io.probes_in;
   if (!io.pool_in) {
     // 1. routing
+    const float* pdist = nullptr;  // centroid distances of the pairs, for the pruning
     if (!probes) {
       clk.at(HNTL_STAGE_ROUTE);
       int32_t* pr = io.probes_out ? io.probes_out : w.probes;
-      if (sp.route == HNTL_ROUTE_LEARNED)
+      if (sp.route == HNTL_ROUTE_LEARNED) {
         launch_route_learned(ix, Q, nq, (int)P, sp.tau, pr, io.pdist_out, w.rw, s, nullptr, sp.mass);
-      else
-        launch_route_centroid(ix, Q, nq, (int)P, w.cw, pr, io.pdist_out, s);
+      } else {
+        // kept where eps_q goes: the pruning reads the other slots' distances
+        // after slot 0's eps_q is written and before theirs is
+        float* pd = io.pdist_out ? io.pdist_out : w.prune ? w.eq : nullptr;
+        launch_route_centroid(ix, Q, nq, (int)P, w.cw, pr, pd, s);
+        pdist = pd;
+      }
       probes = pr;
     }
+    const bool bf16 = (sp.flags & HNTL_FLAG_PROJECT_BF16) != 0;
+    const bool bounded = !(sp.flags & HNTL_FLAG_NO_PRUNE);
+    uint64_t* pt = w.part;
+    unsigned long long* scored = (sp.flags & HNTL_FLAG_PROFILE) ? g_prof.counter(ix.device) : nullptr;
     // 2. bucketing by grain (each grain's probe-slot-0 pairs first, so that
-    //    slot 0 is scanned first and its C-th key bounds the other slots)
+    //    slot 0 is scanned first and its C-th key bounds the other slots);
+    //    with w.prune only slot 0 is bucketed and projected here
     clk.at(HNTL_STAGE_BUCKET);
-    launch_bucket(probes, nq, (int)P, w.b, s);
+    Buckets b = w.b;
+    b.pick = w.prune ? PICK_SLOT0 : PICK_ALL;
+    if (w.prune) {
+      launch_fill_i32(b.cnt, 2 * bucket_counters(ix.G), 0, s);
+      b.max_items[LIST_ALL] = (int)(nq / b.lists.tile[LIST_ALL] + std::min<int64_t>(ix.G, nq) + 1);
+    }
+    launch_bucket(probes, nq, (int)P, b, s, w.prune);
     // 3. projection
     const float* T = io.tangent_in;
     const float* eq = io.epsq_in;
+    float* To = io.tangent_out ? io.tangent_out : w.T;
+    float* eo = io.epsq_out ? io.epsq_out : w.eq;
     if (!T) {
       clk.at(HNTL_STAGE_PROJECT);
-      float* To = io.tangent_out ? io.tangent_out : w.T;
-      float* eo = io.epsq_out ? io.epsq_out : w.eq;
-      launch_project(ix, Q, (int)P, w.b, To, eo, (sp.flags & HNTL_FLAG_PROJECT_BF16) != 0, s);
+      launch_project(ix, Q, (int)P, b, To, eo, bf16, s);
       T = To;
       eq = eo;
     }
     // 4. scan + per-pair top-C: slot 0 unbounded, then the other slots
     //    bounded by it (and pruned by the exact lower bound unless disabled)
-    uint64_t* pt = w.part;
     clk.at(HNTL_STAGE_SCAN);
-    unsigned long long* scored = (sp.flags & HNTL_FLAG_PROFILE) ? g_prof.counter(ix.device) : nullptr;
     if (P > 1) launch_reset_slot0_tail(pt, nq, (int)P, (int)C, s);
-    launch_scan(ix, (int)sp.codes, T, eq, (int)P, (int)C, w.b, LIST_SLOT0, pt, nullptr, false, scored, s);
-    if (P > 1) {
-      const bool bounded = !(sp.flags & HNTL_FLAG_NO_PRUNE);
-      launch_scan(ix, (int)sp.codes, T, eq, (int)P, (int)C, w.b, LIST_REST, pt, bounded ? pt : nullptr, bounded,
-                  scored, s);
+    launch_scan(ix, (int)sp.codes, T, eq, (int)P, (int)C, b, LIST_SLOT0, pt, nullptr, false, scored, s);
+    if (w.prune) {
+      // the other slots' pairs that slot 0's C-th key leaves: bucketed, projected
+      PruneArgs pa{probes, w.kept, nq, (int)P, (int)C, pdist, nullptr, pt, 0};
+      launch_prune_pairs(ix, (int)sp.codes, Q, pa, s);
+      probes = w.kept;
+      b = w.b;
+      b.pick = PICK_REST;
+      b.cnt = w.b.cnt + bucket_counters(ix.G);
+      b.slot = (int32_t*)w.T;  // slot 0's tangents are done with, the others' not yet written
+      launch_bucket(probes, nq, (int)P, b, s, true);
+      launch_project(ix, Q, (int)P, b, To, eo, bf16, s);
     }
+    if (P > 1)
+      launch_scan(ix, (int)sp.codes, T, eq, (int)P, (int)C, b, LIST_REST, pt, bounded ? pt : nullptr, bounded,
+                  scored, s);
     part = pt;
   }
   // 5. pool merge + exact rerank

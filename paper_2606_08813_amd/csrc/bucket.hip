@@ -33,9 +33,21 @@ constexpr int SMALL_PAIRS = 4096;   // pairs and grains of the one-workgroup for
 constexpr int SMALL_GRAINS = 8192;  // thread in registers, four counters a grain in the LDS (128 KiB)
 constexpr int64_t ITEM_WGS = 1024;   // workgroups that write an item table (each thread strides over it)
 
-__device__ __forceinline__ int probe_of(const int32_t* __restrict__ probes, int64_t p, int G) {
+// The pairs of a bucketing are numbered e = 0, 1, ...: every pair, or with
+// PICK_SLOT0 the first of every query.
+__device__ __forceinline__ int64_t pair_of(const Buckets& b, int64_t e, int P) {
+  return b.pick == PICK_SLOT0 ? e * P : e;
+}
+
+// Grain of pair p, -1 for a pair that is not taken.
+__device__ __forceinline__ int probe_of(const Buckets& b, const int32_t* __restrict__ probes, int64_t p, int P) {
   const int g = probes[p];
-  return (g >= 0 && g < G) ? g : -1;
+  if (g < 0 || g >= b.G) return -1;
+  if (b.pick == PICK_ALL || b.pick == PICK_SLOT0) return g;
+  bool take = (p % P == 0) == (b.pick == PICK_FIRST);
+  if (b.pick != PICK_REST && p % P != 0)
+    take = small_first_grain(probes, p / P, P, b.G, b.goff, b.need) == (b.pick == PICK_FIRST);
+  return take ? g : -1;
 }
 
 // Inclusive scan over the lanes of a wave, DPP moves only.
@@ -109,7 +121,7 @@ __device__ __forceinline__ void scan_ranks(const Buckets& b, const int* c0a, con
   __shared__ int tmp[5][16];
   const int G = b.G;
   const int t0 = b.lists.tile[LIST_SLOT0], t1 = b.lists.tile[LIST_REST], t2 = b.lists.tile[LIST_ALL];
-  int carry[5] = {0, 0, 0, 0, 0};
+  int carry[5] = {0, 0, 0, 0, b.lists_from ? *b.lists_from : 0};
   for (int base = 0; base < G; base += 8192) {
     const int r0 = base + 8 * (int)threadIdx.x;
     int c0[8], c1[8], sp[8];
@@ -159,6 +171,7 @@ __device__ __forceinline__ void scan_ranks(const Buckets& b, const int* c0a, con
     b.lists.ioff[LIST_SLOT0][G] = carry[1];
     b.lists.ioff[LIST_REST][G] = carry[2];
     b.lists.ioff[LIST_ALL][G] = carry[3];
+    if (b.lists_to) *b.lists_to = carry[4];
   }
 }
 
@@ -232,16 +245,16 @@ __device__ __forceinline__ void write_items(const Buckets& b, int64_t first, int
 // a global atomic per pair takes 31 us, and longer yet over fewer grains.
 template <bool LDS>
 __global__ __launch_bounds__(1024) void bucket_count_kernel(Buckets b, const int32_t* __restrict__ probes,
-                                                            int64_t npairs, int P) {
+                                                            int64_t n, int P) {
   __shared__ int cnt[LDS ? 2 * SMALL_GRAINS : 1];
   constexpr int U = 4;
   const int G = b.G;
-  const int64_t p0 = (int64_t)blockIdx.x * (U * 1024) + threadIdx.x;
+  const int64_t e0 = (int64_t)blockIdx.x * (U * 1024) + threadIdx.x;
   int at[U], key[U];  // key: the pair's counter
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const int64_t p = p0 + u * 1024;
-    const int g = p < npairs ? probe_of(probes, p, G) : -1;
+    const int64_t p = pair_of(b, e0 + u * 1024, P);
+    const int g = e0 + u * 1024 < n ? probe_of(b, probes, p, P) : -1;
     key[u] = g < 0 ? -1 : (b.grank ? b.grank[g] : g) + (p % P == 0 ? 0 : G);
   }
   if constexpr (LDS) {
@@ -258,11 +271,11 @@ __global__ __launch_bounds__(1024) void bucket_count_kernel(Buckets b, const int
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (key[u] >= 0) b.slot[p0 + u * 1024] = cnt[key[u]] + at[u];
+      if (key[u] >= 0) b.slot[e0 + u * 1024] = cnt[key[u]] + at[u];
   } else {
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (key[u] >= 0) b.slot[p0 + u * 1024] = atomicAdd(&b.cnt[key[u]], 1);
+      if (key[u] >= 0) b.slot[e0 + u * 1024] = atomicAdd(&b.cnt[key[u]], 1);
   }
 }
 
@@ -272,38 +285,40 @@ __global__ __launch_bounds__(1024) void bucket_scan_kernel(Buckets b) {
 
 // Workgroups below pair_wgs place pairs, the others write the item table.
 __global__ __launch_bounds__(256) void bucket_place_kernel(Buckets b, const int32_t* __restrict__ probes,
-                                                           int64_t npairs, int P, int pair_wgs) {
+                                                           int64_t n, int P, int pair_wgs) {
   if ((int)blockIdx.x >= pair_wgs) {
     write_items(b, (int64_t)((int)blockIdx.x - pair_wgs) * 256 + threadIdx.x,
                 (int64_t)((int)gridDim.x - pair_wgs) * 256);
     return;
   }
-  const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (p >= npairs) return;
-  const int g = probe_of(probes, p, b.G);
+  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (e >= n) return;
+  const int64_t p = pair_of(b, e, P);
+  const int g = probe_of(b, probes, p, P);
   if (g < 0) return;
   const int r = b.grank ? b.grank[g] : g;
-  const int at = b.slot[p] + ((p % P) == 0 ? 0 : b.cnt[r]);
+  const int at = b.slot[e] + ((p % P) == 0 ? 0 : b.cnt[r]);
   place_pair(b, (int)p, r, b.gstart[r], b.lbase ? b.glist[r] : 0, at);
 }
 
-__global__ __launch_bounds__(1024) void bucket_small_kernel(Buckets b, const int32_t* __restrict__ probes, int npairs,
+__global__ __launch_bounds__(1024) void bucket_small_kernel(Buckets b, const int32_t* __restrict__ probes, int n,
                                                             int P) {
   __shared__ __align__(16) int cnt[2][SMALL_GRAINS], first[SMALL_GRAINS], lists[SMALL_GRAINS];
   constexpr int U = SMALL_PAIRS / 1024;
   const int G = b.G;
-  int rank[U], at[U];
+  int pair[U], rank[U], at[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const int p = (int)threadIdx.x + u * 1024;
-    const int g = p < npairs ? probe_of(probes, p, G) : -1;
+    const int e = (int)threadIdx.x + u * 1024;
+    pair[u] = (int)pair_of(b, e, P);
+    const int g = e < n ? probe_of(b, probes, pair[u], P) : -1;
     rank[u] = g < 0 ? -1 : b.grank ? b.grank[g] : g;
   }
   for (int r = threadIdx.x; r < G; r += 1024) cnt[0][r] = cnt[1][r] = 0;
   __syncthreads();
 #pragma unroll
   for (int u = 0; u < U; ++u)
-    if (rank[u] >= 0) at[u] = atomicAdd(&cnt[((int)threadIdx.x + u * 1024) % P == 0 ? 0 : 1][rank[u]], 1);
+    if (rank[u] >= 0) at[u] = atomicAdd(&cnt[pair[u] % P == 0 ? 0 : 1][rank[u]], 1);
   __syncthreads();
   scan_ranks(b, cnt[0], cnt[1], true, first, lists);
   __syncthreads();
@@ -315,7 +330,7 @@ __global__ __launch_bounds__(1024) void bucket_small_kernel(Buckets b, const int
 #pragma unroll
   for (int u = 0; u < U; ++u)
     if (rank[u] >= 0) {
-      const int p = (int)threadIdx.x + u * 1024, r = rank[u];
+      const int p = pair[u], r = rank[u];
       place_pair(b, p, r, first[r], lists[r], at[u] + (p % P == 0 ? 0 : cnt[0][r]));
     }
   __syncthreads();  // the arrays written above are read back by other threads of this workgroup
@@ -352,31 +367,31 @@ void launch_fill_multi(const FillList& L, hipStream_t s) {
 }
 
 void launch_bucket(const int32_t* probes, int64_t nq, int P, const Buckets& b, hipStream_t s, bool counts_zeroed) {
-  const int64_t npairs = nq * P;
-  if (npairs <= 0) return;
-  if (npairs <= SMALL_PAIRS && b.G <= SMALL_GRAINS) {
+  const int64_t n = b.pick == PICK_SLOT0 ? nq : nq * P;
+  if (n <= 0) return;
+  if (n <= SMALL_PAIRS && b.G <= SMALL_GRAINS) {
     Buckets one = b;
     // a long item table is written by many workgroups
     const bool inside = b.items && b.items_cap <= SMALL_PAIRS;
     if (!inside) one.items = nullptr;
-    hipLaunchKernelGGL(bucket_small_kernel, dim3(1), dim3(1024), 0, s, one, probes, (int)npairs, P);
+    hipLaunchKernelGGL(bucket_small_kernel, dim3(1), dim3(1024), 0, s, one, probes, (int)n, P);
     HIP_TRY(hipGetLastError());
     if (!b.items || inside) return;
     const unsigned iwgs = (unsigned)std::min<int64_t>((b.items_cap + 255) / 256, ITEM_WGS);
-    hipLaunchKernelGGL(bucket_place_kernel, dim3(iwgs), dim3(256), 0, s, b, probes, npairs, P, 0);
+    hipLaunchKernelGGL(bucket_place_kernel, dim3(iwgs), dim3(256), 0, s, b, probes, n, P, 0);
     HIP_TRY(hipGetLastError());
     return;
   }
   if (!counts_zeroed) launch_fill_i32(b.cnt, 2 * (int64_t)b.G, 0, s);
-  const unsigned pwgs = (unsigned)((npairs + 255) / 256);
-  const dim3 cgrid((unsigned)((npairs + 4095) / 4096));
+  const unsigned pwgs = (unsigned)((n + 255) / 256);
+  const dim3 cgrid((unsigned)((n + 4095) / 4096));
   if (b.G <= SMALL_GRAINS)
-    hipLaunchKernelGGL(bucket_count_kernel<true>, cgrid, dim3(1024), 0, s, b, probes, npairs, P);
+    hipLaunchKernelGGL(bucket_count_kernel<true>, cgrid, dim3(1024), 0, s, b, probes, n, P);
   else
-    hipLaunchKernelGGL(bucket_count_kernel<false>, cgrid, dim3(1024), 0, s, b, probes, npairs, P);
+    hipLaunchKernelGGL(bucket_count_kernel<false>, cgrid, dim3(1024), 0, s, b, probes, n, P);
   hipLaunchKernelGGL(bucket_scan_kernel, dim3(1), dim3(1024), 0, s, b);
   const unsigned iwgs = b.items ? (unsigned)std::min<int64_t>((b.items_cap + 255) / 256, ITEM_WGS) : 0;
-  hipLaunchKernelGGL(bucket_place_kernel, dim3(pwgs + iwgs), dim3(256), 0, s, b, probes, npairs, P, (int)pwgs);
+  hipLaunchKernelGGL(bucket_place_kernel, dim3(pwgs + iwgs), dim3(256), 0, s, b, probes, n, P, (int)pwgs);
   HIP_TRY(hipGetLastError());
 }
 

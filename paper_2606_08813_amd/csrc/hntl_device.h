@@ -434,6 +434,14 @@ __device__ __forceinline__ bool item_grain(const int32_t* __restrict__ ioff, int
   return true;
 }
 
+// Whether the nearest probed grain of query q (probes: P per query) has fewer
+// than `need` members (or is invalid).
+__device__ __forceinline__ bool small_first_grain(const int32_t* __restrict__ probes, int64_t q, int P, int G,
+                                                  const int32_t* __restrict__ goff, int need) {
+  const int g = probes[q * P];
+  return g < 0 || g >= G || goff[g + 1] - goff[g] < need;
+}
+
 // ------------------------------------------------------------------- MFMA
 // v_mfma_f32_16x16x4_f32: lane l supplies A[l%16][l/16] and B[l/16][l%16] of a
 // 16x4 by 4x16 product and holds D[4*(l/16)+i][l%16] for i = 0..3.

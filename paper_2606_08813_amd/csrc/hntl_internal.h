@@ -80,6 +80,7 @@ struct Index {
   float* blo = nullptr;        // G x rp: per-grain minimum of each code coordinate
   float* bhi = nullptr;        // G x rp: per-grain maximum
   float* emin = nullptr;       // G: per-grain minimum eps_i
+  float* rmax = nullptr;       // G: per-grain upper bound of ||z_i||
   int32_t* gorder = nullptr;   // G: grains by size, largest first (made by the first search plan)
   int32_t* grank = nullptr;    // G: a grain's place in gorder
   uint16_t* cent_split = nullptr;  // G x 3d bf16: [hi | lo | hi] of the centroids (split-BF16 routing, on first use)
@@ -217,12 +218,23 @@ struct ItemLists {
   int32_t* ioff[3];  // G + 1 each: exclusive prefix of items per rank
   int tile[3];       // pairs per work item
 };
+// The pairs a bucketing takes: all; probe slot 0; the other slots; slot 0 and
+// every pair of a query whose nearest grain has fewer than `need` members (it
+// cannot bound the query); the pairs that leaves.
+enum { PICK_ALL = 0, PICK_SLOT0 = 1, PICK_REST = 2, PICK_FIRST = 3, PICK_LATER = 4 };
 struct Buckets {
   int G;
+  int pick;
+  const int32_t* goff;  // grain offsets (PICK_FIRST, PICK_LATER)
+  int need;
+  // candidate lists are numbered from *lists_from on (null: from 0); the number
+  // past the last goes to *lists_to (null: nowhere)
+  const int32_t* lists_from;
+  int32_t* lists_to;
   const int32_t* gorder;       // rank -> grain (null: the same)
   const int32_t* grank;        // grain -> rank
   const int32_t* nsplit_rank;  // block ranges per grain (null: 1)
-  int32_t* cnt;                // 2 G: pairs of probe slot 0, then of the other slots
+  int32_t* cnt;                // 2 G: pairs of probe slot 0, then of the other slots (16-byte aligned)
   int32_t* gstart;             // G: first place of the rank's pairs in `order`
   int32_t* glist;              // G: first candidate list of the rank's pairs (with lbase)
   int32_t* slot;               // npairs: a pair's number among its grain's pairs of its kind
@@ -248,6 +260,8 @@ struct ListRef {
 inline ListRef list_ref(const Buckets& b, int L) {
   return ListRef{b.lists.ioff[L], b.gstart, b.cnt, b.cnt + b.G, L};
 }
+// Counters of one bucketing, so that a second one's are 16-byte aligned too.
+inline int64_t bucket_counters(int64_t G) { return (2 * G + 3) / 4 * 4; }
 // counts_zeroed: b.cnt holds zeros (larger batches fill it first otherwise).
 void launch_bucket(const int32_t* probes, int64_t nq, int P, const Buckets& b, hipStream_t s,
                    bool counts_zeroed = false);
@@ -279,6 +293,25 @@ void launch_scan(const Index& ix, int codes, const float* T, const float* epsq, 
                  const Buckets& b, int list, uint64_t* part, const uint64_t* bound_lists, bool prune,
                  unsigned long long* scored, hipStream_t s);
 void launch_grain_bounds(Index& ix, hipStream_t s);
+// Exact pruning before projection: kept[p] = probes[p] for probe slot 0 and for
+// every pair of another slot whose lower bound of eq. 6 does not exceed its
+// query's bound, else -1 (kept may be probes).  The bound is qbound[q] (order
+// image, all ones: none), or the C-th key of the query's slot-0 list in part.
+// Queries whose nearest grain has fewer than `need` members keep every pair.
+// pdist: ||q - mu||^2 per pair (direct differences; null: computed here).
+struct PruneArgs {
+  const int32_t* probes;
+  int32_t* kept;
+  int64_t nq;
+  int P, C;
+  const float* pdist;
+  const uint32_t* qbound;
+  const uint64_t* part;
+  int need;
+};
+void launch_prune_pairs(const Index& ix, int codes, const float* Q, const PruneArgs& a, hipStream_t s);
+// Whether the pruning pays for a batch of nq queries.
+bool prune_pays(const Index& ix, const hntl_search_params& sp, int64_t nq);
 // Before the slot-0 pass of the staged scan: entry C - 1 of each query's
 // slot-0 list := KEY_NONE (part is nq x P x C keys).
 void launch_reset_slot0_tail(uint64_t* part, int64_t nq, int P, int C, hipStream_t s);

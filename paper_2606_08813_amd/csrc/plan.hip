@@ -11,7 +11,11 @@
 //                    distance epilogue), top-P + exact re-score
 //   bucketing        pairs grouped by grain, items numbered largest grain first,
 //                    per-pair list slots when grains are split into ranges
-//   fused kernel     projection + scan + per-list top-C (persistent)
+//   projection       with the schedule option proj = 1
+//   fused kernel     projection (proj = 0) + scan + per-list top-C (persistent);
+//                    with proj = 1 and batches where it pays, bucketing to scan
+//                    run for probe slot 0 first, and again for the other slots'
+//                    pairs that the exact pruning keeps
 //   merge + rerank   pool = exact top C over the query's lists, FP32 rerank
 //
 // The batch size lives in device memory (written by a one-thread kernel
@@ -155,6 +159,10 @@ struct Plan {
   RouteScratch route;
   // bucketing
   Buckets b{};
+  bool prune = false;              // slot 0 first, then what the pruning keeps (see enqueue)
+  int32_t* kept = nullptr;         // probes after the pruning
+  float* pdist = nullptr;          // routing distances for it (centroid routing)
+  int32_t* lists_end = nullptr;    // candidate lists of slot 0
   int32_t* nsplit = nullptr;       // block ranges per grain
   int32_t* nsplit_rank = nullptr;  // the same by rank
   // fused kernel state
@@ -209,7 +217,7 @@ struct Plan {
     b.G = (int)x.G;
     b.gorder = x.gorder;
     b.grank = x.grank;
-    b.cnt = L.take<int32_t>(2 * (size_t)x.G);
+    b.cnt = L.take<int32_t>(2 * (size_t)bucket_counters(x.G));  // two bucketings' counts
     b.gstart = L.take<int32_t>(x.G);
     b.glist = L.take<int32_t>(x.G);
     b.slot = L.take<int32_t>(np);
@@ -220,12 +228,15 @@ struct Plan {
     // separate projection launch, the shared-basis kernel's item where it applies
     b.lists.tile[LIST_ALL] = sch.proj ? project_tile(x, Q, (sp.flags & HNTL_FLAG_PROJECT_BF16) != 0) : 16;
     b.max_items[LIST_ALL] = (int)(np / b.lists.tile[LIST_ALL] + std::min<int64_t>(x.G, np) + 1);
+    kept = prune ? L.take<int32_t>(np) : probes;
+    pdist = prune && sp.route != HNTL_ROUTE_LEARNED ? L.take<float>(np) : nullptr;
+    lists_end = L.take<int32_t>(1);
     nsplit = L.take<int32_t>(x.G);
     nsplit_rank = L.take<int32_t>(x.G);
     b.nsplit_rank = sch.range ? nsplit_rank : nullptr;
     int32_t* lb = L.take<int32_t>(np);
     b.lbase = sch.range ? lb : nullptr;
-    args_dev = L.take<FusedArgs>(3);  // phases 0, 1, 2
+    args_dev = L.take<FusedArgs>(4);  // phases 0, 1, 2; the pruned rest
     ticket = L.take<int32_t>(2 * TICKET_INTS);  // counters of each launch (phases 0/1 and 2)
     proj_items = (int64_t)((np + 15) / 16) + x.G;  // at most sum over grains of ceil(pairs / 16)
     proj_done = L.take<int32_t>(proj_items);
@@ -309,27 +320,55 @@ struct Plan {
     f.seg[1] = FillSeg{reinterpret_cast<int32_t*>(scored), 2, 0};
     f.seg[2] = FillSeg{proj_done, proj_items, 0};
     f.seg[3] = FillSeg{reinterpret_cast<int32_t*>(qbound), (int64_t)max_nq, -1};
-    f.seg[4] = FillSeg{b.cnt, 2 * (int64_t)x.G, 0};
+    f.seg[4] = FillSeg{b.cnt, 2 * bucket_counters(x.G), 0};
     f.n = 5;
     launch_fill_multi(f, s);
     // routing reads the batch size from nq_dev: rows past it get probes -1
     if (sp.route == HNTL_ROUTE_LEARNED)
       launch_route_learned(x, Q, max_nq, P, sp.tau, probes, nullptr, rs, s, nq_dev, sp.mass);
     else
-      launch_route_centroid(x, Q, max_nq, P, route, probes, nullptr, s, nq_dev);
+      launch_route_centroid(x, Q, max_nq, P, route, probes, pdist, s, nq_dev);
     if (ev) HIP_TRY(hipEventRecord(ev[1], s));
-    launch_bucket(probes, max_nq, P, b, s, true);
-    if (ev) HIP_TRY(hipEventRecord(ev[2], s));
-    if (sch.proj) launch_project(x, Q, P, b, T, epsq, (sp.flags & HNTL_FLAG_PROJECT_BF16) != 0, s);
-    if (ev) HIP_TRY(hipEventRecord(ev[3], s));
-    for (int ph = sch.passes == 2 ? 1 : 0; ph <= (sch.passes == 2 ? 2 : 0); ++ph) {
-      if (!fused_launch((int)sp.codes, args_dev + ph, (int)x.rp, (int)sp.C, (int)sch.qt, (int)sch.nw, (int)sch.grid,
+    const bool bf16 = (sp.flags & HNTL_FLAG_PROJECT_BF16) != 0;
+    auto fused = [&](int args) {
+      if (!fused_launch((int)sp.codes, args_dev + args, (int)x.rp, (int)sp.C, (int)sch.qt, (int)sch.nw, (int)sch.grid,
                         s))
         throw ArgError{HNTL_EUNSUPPORTED, "no fused kernel for this rank / pool / schedule"};
       HIP_TRY(hipGetLastError());
+    };
+    // With `prune`, slot 0 is bucketed, projected and scanned first; a pair of
+    // another slot goes on only if its lower bound (from the routing distance, no
+    // projection) does not exceed the bound that slot 0 left for its query.
+    // Queries whose nearest grain cannot overfill a list (C members or fewer: such
+    // lists are written unsorted) get no bound from it: all their pairs go first, beside the long items of slot 0
+    // (alone in the second pass their short items left the GPU to a few waves:
+    // 250 us of 750 at 16,384 queries over Zipf-sized grains).
+    const int need = sch.range && sch.range * B <= sp.C ? INT32_MAX : (int)sp.C + 1;
+    Buckets pass = b;
+    pass.pick = prune ? PICK_FIRST : PICK_ALL;
+    pass.goff = x.goff;
+    pass.need = need;
+    pass.lists_to = lists_end;
+    launch_bucket(probes, max_nq, P, pass, s, true);
+    if (ev) HIP_TRY(hipEventRecord(ev[2], s));
+    if (sch.proj) launch_project(x, Q, P, pass, T, epsq, bf16, s);
+    if (ev) HIP_TRY(hipEventRecord(ev[3], s));
+    if (prune) {
+      fused(0);
+      launch_prune_pairs(x, (int)sp.codes, Q, 
+                         PruneArgs{probes, kept, (int64_t)max_nq, P, (int)sp.C, pdist, qbound, nullptr, need}, s);
+      pass.pick = PICK_LATER;
+      pass.lists_to = nullptr;
+      pass.cnt = b.cnt + bucket_counters(x.G);
+      pass.lists_from = lists_end;
+      launch_bucket(kept, max_nq, P, pass, s, true);
+      launch_project(x, Q, P, pass, T, epsq, bf16, s);
+      fused(3);
+    } else {
+      for (int ph = sch.passes == 2 ? 1 : 0; ph <= (sch.passes == 2 ? 2 : 0); ++ph) fused(ph);
     }
     if (ev) HIP_TRY(hipEventRecord(ev[4], s));
-    launch_merge_rerank(x, Q, max_nq, P, (int)sp.C, (int)sp.k, probes, part, nullptr, nullptr, nullptr, ids, dist, s,
+    launch_merge_rerank(x, Q, max_nq, P, (int)sp.C, (int)sp.k, kept, part, nullptr, nullptr, nullptr, ids, dist, s,
                         b.lbase, nsplit, (sp.flags & HNTL_FLAG_MODE_A) ? x.eps_id : nullptr, nq_dev);
     if (ev) HIP_TRY(hipEventRecord(ev[5], s));
   }
@@ -439,6 +478,7 @@ Plan* make_plan(Index& ix, const hntl_search_params& sp, uint32_t max_nq, const 
   }
   sch.grid = std::max<uint32_t>(sch.grid, MIN_GRID);
   pl->sch = sch;
+  pl->prune = sch.proj && prune_pays(ix, sp, max_nq);
   pl->arena_bytes = pl->layout(nullptr);
   HIP_TRY(hipMalloc((void**)&pl->arena, pl->arena_bytes));
   pl->layout(pl->arena);
@@ -449,11 +489,11 @@ Plan* make_plan(Index& ix, const hntl_search_params& sp, uint32_t max_nq, const 
   HIP_TRY(hipMemcpy(order.data(), ix.gorder, sizeof(int32_t) * ix.G, hipMemcpyDeviceToHost));
   for (uint32_t i = 0; i < ix.G; ++i) nsr[i] = ns[order[i]];
   HIP_TRY(hipMemcpyAsync(pl->nsplit_rank, nsr.data(), sizeof(int32_t) * ix.G, hipMemcpyHostToDevice, s));
-  FusedArgs a[3];
-  for (int ph = 0; ph < 3; ++ph) {
+  FusedArgs a[4];
+  for (int ph = 0; ph < 4; ++ph) {
     a[ph] = pl->make_args();
-    a[ph].phase = ph;
-    a[ph].ticket = pl->ticket + (ph == 2 ? TICKET_INTS : 0);
+    a[ph].phase = ph == 3 ? 0 : ph;
+    a[ph].ticket = pl->ticket + (ph >= 2 ? TICKET_INTS : 0);
   }
   HIP_TRY(hipMemcpyAsync(pl->args_dev, a, sizeof(a), hipMemcpyHostToDevice, s));
   HIP_TRY(hipStreamSynchronize(s));

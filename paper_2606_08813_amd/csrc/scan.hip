@@ -1,5 +1,8 @@
 // Scan dispatch by code form, and the per-grain code bounding boxes used by
 // the exact pruning of the scan.
+#include <algorithm>
+#include <cmath>
+
 #include "hntl_device.h"
 #include "hntl_internal.h"
 
@@ -16,13 +19,14 @@ void launch_scan_ct3(const Index&, const float*, const float*, int, int, const B
 
 namespace {
 
-// Per grain: minimum and maximum of every code coordinate and the smallest
-// eps over its members (one workgroup per grain).
+// Per grain: minimum and maximum of every code coordinate, the smallest eps and
+// an upper bound of the longest code over its members (one workgroup per grain).
 __global__ __launch_bounds__(256) void grain_bounds_kernel(const float* __restrict__ codes,
                                                            const float* __restrict__ eps, int rp, int r,
                                                            const int32_t* __restrict__ goff,
                                                            const int32_t* __restrict__ boff, float* __restrict__ blo,
-                                                           float* __restrict__ bhi, float* __restrict__ emin) {
+                                                           float* __restrict__ bhi, float* __restrict__ emin,
+                                                           float* __restrict__ rmax) {
   __shared__ float red[256];
   const int g = blockIdx.x;
   const int b0 = boff[g], nb = boff[g + 1] - b0, ng = goff[g + 1] - goff[g];
@@ -57,6 +61,121 @@ __global__ __launch_bounds__(256) void grain_bounds_kernel(const float* __restri
     __syncthreads();
   }
   if (threadIdx.x == 0) emin[g] = red[0];
+  __syncthreads();
+  float n2 = 0.f;  // the largest squared length; lanes run over members
+  for (int b = w; b < nb; b += 4)
+    if (b * B + lane < ng) {
+      float acc = 0.f;
+      for (int j = 0; j < r; ++j) {
+        const float v = codes[((size_t)(b0 + b) * rp + j) * B + lane];
+        acc = fmaf(v, v, acc);
+      }
+      n2 = fmaxf(n2, acc);
+    }
+  red[threadIdx.x] = n2;
+  __syncthreads();
+  for (int o = 128; o > 0; o >>= 1) {
+    if ((int)threadIdx.x < o) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + o]);
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) rmax[g] = sqrtf(red[0]) * (1.f + 1e-5f);
+}
+
+// ---------------------------------------------- pruning before projection
+// For a pair (q, g) let p = ||q - mu_g||^2, t = ||z_q|| and R >= ||z_i|| for
+// every member i.  The score's tangent part is at least (t - R)^2 when t >= R, and
+// eps_q = max(0, p - t^2), so
+//
+//   D_i >= (t - R)^2 + max(0, p - t^2) + eps_i >= (sqrt(p) - R)^2 + eps_min    for sqrt(p) > R
+//
+// (for t^2 <= p the left side is p + R^2 - 2 t R, smallest at t = sqrt(p); beyond
+// it, it grows).  This holds for any z_q that eps_q was computed from, whatever
+// the basis and the projection's precision, and needs no projection.  With
+// reduced codes R covers the decoded values (BF16 2^-8 relative; FP8 2^-4
+// relative plus the subnormal quantum per coordinate).  The int16 form clamps
+// z_q after eps_q is taken, so it has no such bound.  Margins: delta = 1e-5 +
+// 1e-8 d on both lengths and 4e-6 p on the square cover the FP32 sums (d terms
+// over 64 lanes), PRUNE_SLACK as in the scan.
+constexpr float PRUNE_SLACK = 1e-4f;
+
+struct PruneForm {
+  float rel;            // R grows by this factor ...
+  const float* scales;  // ... and with FP8 codes by scales[g] * quantum
+  float quantum;
+  float delta;
+};
+
+__device__ __forceinline__ bool pruned(float p, float bound, float rmax, float emin, const PruneForm& f, int g) {
+  const float R = rmax * f.rel + (f.scales ? f.scales[g] * f.quantum : 0.f);
+  const float a = sqrtf(p) * (1.f - f.delta) - R * (1.f + f.delta);
+  if (!(a > 0.f)) return false;
+  return (a * a - 4e-6f * p + emin) * (1.f - PRUNE_SLACK) > bound;
+}
+
+// The query's bound as a float (+inf: none).
+__device__ __forceinline__ float query_bound(const PruneArgs& a, int64_t q) {
+  if (a.qbound) return a.qbound[q] == 0xFFFFFFFFu ? __builtin_inff() : ord2f(a.qbound[q]);
+  return key_ceil(a.part[(size_t)q * a.P * a.C + a.C - 1]);
+}
+
+__global__ __launch_bounds__(256) void prune_pairs_kernel(PruneArgs a, int G, const float* __restrict__ rmax,
+                                                          const float* __restrict__ emin, PruneForm f,
+                                                          const int32_t* __restrict__ goff) {
+  const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (p >= a.nq * a.P) return;
+  const int64_t q = p / a.P;
+  int g = a.probes[p];
+  if (p % a.P != 0 && (g < 0 || g >= G || (pruned(a.pdist[p], query_bound(a, q), rmax[g], emin[g], f, g) &&
+                                           !small_first_grain(a.probes, q, a.P, G, goff, a.need))))
+    g = -1;
+  a.kept[p] = g;
+}
+
+// Without routing distances (learned routing, injected probes): one wave per
+// query computes its pairs' ||q - mu||^2 by direct differences, four at a time.
+__global__ __launch_bounds__(256) void prune_pairs_dist_kernel(PruneArgs a, int G, const float* __restrict__ rmax,
+                                                               const float* __restrict__ emin, PruneForm f,
+                                                               const int32_t* __restrict__ goff,
+                                                               const float* __restrict__ Q, int d,
+                                                               const float* __restrict__ centroids) {
+  const int lane = lane_id();
+  const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (q >= a.nq) return;
+  const float bound =
+      small_first_grain(a.probes, q, a.P, G, goff, a.need) ? __builtin_inff() : query_bound(a, q);
+  const int own = lane < a.P ? a.probes[q * a.P + lane] : -1;  // HNTL_MAX_P < 64
+  int keep = own;
+  uint64_t m = __ballot(lane > 0 && own >= 0 && own < G && bound < __builtin_inff());
+  if (lane > 0 && (own < 0 || own >= G)) keep = -1;
+  const float* x = Q + q * d;
+  constexpr int U = 4;
+  while (m) {  // wave-uniform
+    int s[U], g[U];
+    const float* mu[U];
+    float acc[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      s[u] = m ? __builtin_ctzll(m) : s[0];
+      m &= m - 1;
+      g[u] = __builtin_amdgcn_readlane(own, s[u]);
+      mu[u] = centroids + (size_t)g[u] * d;
+      acc[u] = 0.f;
+    }
+    for (int t = lane; t < d; t += HNTL_WAVE) {
+      const float v = x[t];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const float df = v - mu[u][t];
+        acc[u] = fmaf(df, df, acc[u]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float p = wave_sum(acc[u]);
+      if (pruned(p, bound, rmax[g[u]], emin[g[u]], f, g[u]) && lane == s[u]) keep = -1;
+    }
+  }
+  if (lane < a.P) a.kept[q * a.P + lane] = keep;
 }
 
 // Entry C - 1 of every query's probe-slot-0 list set to KEY_NONE: a list that
@@ -93,8 +212,36 @@ void launch_grain_bounds(Index& ix, hipStream_t s) {
   if (!ix.blo) ix.blo = dev_alloc<float>(&ix, (size_t)ix.G * ix.rp);
   if (!ix.bhi) ix.bhi = dev_alloc<float>(&ix, (size_t)ix.G * ix.rp);
   if (!ix.emin) ix.emin = dev_alloc<float>(&ix, ix.G);
+  if (!ix.rmax) ix.rmax = dev_alloc<float>(&ix, ix.G);
   hipLaunchKernelGGL(grain_bounds_kernel, dim3(ix.G), dim3(256), 0, s, ix.codes, ix.eps, (int)ix.rp, (int)ix.r,
-                     ix.goff, ix.boff, ix.blo, ix.bhi, ix.emin);
+                     ix.goff, ix.boff, ix.blo, ix.bhi, ix.emin, ix.rmax);
+  HIP_TRY(hipGetLastError());
+}
+
+// Scanning slot 0 first, pruning, then bucketing, projecting and scanning what is
+// left takes four more launches (about 20 us) than one projection of every
+// pair; that projection reads the probed grains' bases and a query row per
+// pair.  From MEAS_PAYS of them on the pruning pays where it prunes.
+bool prune_pays(const Index& ix, const hntl_search_params& sp, int64_t nq) {
+  if (sp.P < 2 || (sp.flags & HNTL_FLAG_NO_PRUNE) || sp.codes == HNTL_CODES_INT16) return false;
+  // the learned router's probe budget has dropped most of them already
+  if (sp.route == HNTL_ROUTE_LEARNED && sp.mass > 0.f && sp.mass < 1.f) return false;
+  const int64_t rest = nq * (sp.P - 1);
+  const int64_t basis = std::min<int64_t>(ix.G, rest) * ix.r * ((sp.flags & HNTL_FLAG_PROJECT_BF16) ? 2 : 4);
+  return (basis + rest * 4) * ix.d >= ((int64_t)64 << 20);
+}
+
+void launch_prune_pairs(const Index& ix, int codes, const float* Q, const PruneArgs& a, hipStream_t s) {
+  if (a.nq <= 0) return;
+  PruneForm f{1.f, nullptr, 0.f, 1e-5f + 1e-8f * (float)ix.d};
+  if (codes == HNTL_CODES_BF16) f.rel = 1.f + 0.00390625f;
+  if (codes == HNTL_CODES_FP8_E4M3) f = PruneForm{1.0625f, ix.scales, sqrtf((float)ix.rp) * 0.0009765625f, f.delta};
+  if (a.pdist)
+    hipLaunchKernelGGL(prune_pairs_kernel, dim3((unsigned)((a.nq * a.P + 255) / 256)), dim3(256), 0, s, a, (int)ix.G,
+                       ix.rmax, ix.emin, f, ix.goff);
+  else
+    hipLaunchKernelGGL(prune_pairs_dist_kernel, dim3((unsigned)((a.nq + 3) / 4)), dim3(256), 0, s, a, (int)ix.G,
+                       ix.rmax, ix.emin, f, ix.goff, Q, (int)ix.d, ix.centroids);
   HIP_TRY(hipGetLastError());
 }
 

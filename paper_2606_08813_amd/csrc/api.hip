@@ -281,7 +281,7 @@ struct StagedScratch {
     }
     part = (uint64_t*)take(8 * (size_t)npairs * sp.C);
     // tangents that the caller observes or injects are of every pair
-    prune = !io.tangent_in && !io.tangent_out && !io.epsq_out && prune_pays(ix, sp, nq);
+    prune = !io.tangent_in && !io.tangent_out && !io.epsq_out && prune_pays(ix, sp, nq, false);
     kept = prune && (io.probes_in || io.probes_out) ? (int32_t*)take(4 * (size_t)npairs)
                                                     : probes;  // own probes are cut in place
     b.slot = (int32_t*)part;  // read before the first list is written
@@ -354,7 +354,7 @@ void run_staged(const Index& ix, const float* Q, uint32_t nq, const hntl_search_
     //    bounded by it (and pruned by the exact lower bound unless disabled)
     clk.at(HNTL_STAGE_SCAN);
     if (P > 1) launch_reset_slot0_tail(pt, nq, (int)P, (int)C, s);
-    launch_scan(ix, (int)sp.codes, T, eq, (int)P, (int)C, b, LIST_SLOT0, pt, nullptr, false, scored, s);
+    launch_scan(ix, (int)sp.codes, T, eq, (int)P, (int)C, b, LIST_SLOT0, pt, nullptr, false, true, scored, s);
     if (w.prune) {
       // the other slots' pairs that slot 0's C-th key leaves: bucketed, projected
       PruneArgs pa{probes, w.kept, nq, (int)P, (int)C, pdist, nullptr, pt, 0};
@@ -369,7 +369,7 @@ void run_staged(const Index& ix, const float* Q, uint32_t nq, const hntl_search_
     }
     if (P > 1)
       launch_scan(ix, (int)sp.codes, T, eq, (int)P, (int)C, b, LIST_REST, pt, bounded ? pt : nullptr, bounded,
-                  scored, s);
+                  !bounded || w.prune, scored, s);
     part = pt;
   }
   // 5. pool merge + exact rerank

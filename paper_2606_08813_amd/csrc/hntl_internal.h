@@ -90,6 +90,7 @@ struct Index {
   std::vector<int64_t> offsets_h;
   std::vector<int32_t> boff_h;
   std::vector<double> captured;  // per grain (build only)
+  float small_share[9] = {};     // share of the members in grains of at most 2^k members, k = 0..8
   uint64_t device_bytes = 0;
 
   ~Index();
@@ -288,9 +289,10 @@ void launch_project(const Index& ix, const float* Q, int P, const Buckets& b, fl
 // Scan of the bucketed pairs.  With `bound_lists` (the lists of probe slot 0,
 // already written into part), each pair starts from its query's C-th key of
 // slot 0 as threshold and, when `prune`, is skipped outright if an exact
-// lower bound of eq. 6 over its grain exceeds that threshold.
+// lower bound of eq. 6 over its grain exceeds that threshold.  narrow: 4 pairs
+// per wave, for lists that fill (wide: 16, or 8 for C > 128).
 void launch_scan(const Index& ix, int codes, const float* T, const float* epsq, int P, int C,
-                 const Buckets& b, int list, uint64_t* part, const uint64_t* bound_lists, bool prune,
+                 const Buckets& b, int list, uint64_t* part, const uint64_t* bound_lists, bool prune, bool narrow,
                  unsigned long long* scored, hipStream_t s);
 void launch_grain_bounds(Index& ix, hipStream_t s);
 // Exact pruning before projection: kept[p] = probes[p] for probe slot 0 and for
@@ -310,8 +312,9 @@ struct PruneArgs {
   int need;
 };
 void launch_prune_pairs(const Index& ix, int codes, const float* Q, const PruneArgs& a, hipStream_t s);
-// Whether the pruning pays for a batch of nq queries.
-bool prune_pays(const Index& ix, const hntl_search_params& sp, int64_t nq);
+// Whether the pruning pays for a batch of nq queries (plan: one whose schedule
+// takes the queries it cannot bound into the first pass).
+bool prune_pays(const Index& ix, const hntl_search_params& sp, int64_t nq, bool plan);
 // Before the slot-0 pass of the staged scan: entry C - 1 of each query's
 // slot-0 list := KEY_NONE (part is nq x P x C keys).
 void launch_reset_slot0_tail(uint64_t* part, int64_t nq, int P, int C, hipStream_t s);

@@ -9,13 +9,13 @@
 namespace hntl {
 
 void launch_scan_ct0(const Index&, const float*, const float*, int, int, const Buckets&, int, uint64_t*,
-                     const uint64_t*, bool, unsigned long long*, hipStream_t);
+                     const uint64_t*, bool, bool, unsigned long long*, hipStream_t);
 void launch_scan_ct1(const Index&, const float*, const float*, int, int, const Buckets&, int, uint64_t*,
-                     const uint64_t*, bool, unsigned long long*, hipStream_t);
+                     const uint64_t*, bool, bool, unsigned long long*, hipStream_t);
 void launch_scan_ct2(const Index&, const float*, const float*, int, int, const Buckets&, int, uint64_t*,
-                     const uint64_t*, bool, unsigned long long*, hipStream_t);
+                     const uint64_t*, bool, bool, unsigned long long*, hipStream_t);
 void launch_scan_ct3(const Index&, const float*, const float*, int, int, const Buckets&, int, uint64_t*,
-                     const uint64_t*, bool, unsigned long long*, hipStream_t);
+                     const uint64_t*, bool, bool, unsigned long long*, hipStream_t);
 
 namespace {
 
@@ -194,17 +194,17 @@ void launch_reset_slot0_tail(uint64_t* part, int64_t nq, int P, int C, hipStream
 }
 
 void launch_scan(const Index& ix, int codes, const float* T, const float* epsq, int P, int C, const Buckets& b,
-                 int list, uint64_t* part, const uint64_t* bound_lists, bool prune, unsigned long long* scored,
-                 hipStream_t s) {
+                 int list, uint64_t* part, const uint64_t* bound_lists, bool prune, bool narrow,
+                 unsigned long long* scored, hipStream_t s) {
   if (b.max_items[list] <= 0) return;
   if (codes == HNTL_CODES_FP32)
-    launch_scan_ct0(ix, T, epsq, P, C, b, list, part, bound_lists, prune, scored, s);
+    launch_scan_ct0(ix, T, epsq, P, C, b, list, part, bound_lists, prune, narrow, scored, s);
   else if (codes == HNTL_CODES_BF16)
-    launch_scan_ct1(ix, T, epsq, P, C, b, list, part, bound_lists, prune, scored, s);
+    launch_scan_ct1(ix, T, epsq, P, C, b, list, part, bound_lists, prune, narrow, scored, s);
   else if (codes == HNTL_CODES_FP8_E4M3)
-    launch_scan_ct2(ix, T, epsq, P, C, b, list, part, bound_lists, prune, scored, s);
+    launch_scan_ct2(ix, T, epsq, P, C, b, list, part, bound_lists, prune, narrow, scored, s);
   else
-    launch_scan_ct3(ix, T, epsq, P, C, b, list, part, bound_lists, prune, scored, s);
+    launch_scan_ct3(ix, T, epsq, P, C, b, list, part, bound_lists, prune, narrow, scored, s);
   HIP_TRY(hipGetLastError());
 }
 
@@ -213,22 +213,44 @@ void launch_grain_bounds(Index& ix, hipStream_t s) {
   if (!ix.bhi) ix.bhi = dev_alloc<float>(&ix, (size_t)ix.G * ix.rp);
   if (!ix.emin) ix.emin = dev_alloc<float>(&ix, ix.G);
   if (!ix.rmax) ix.rmax = dev_alloc<float>(&ix, ix.G);
+  for (int k = 0; k <= 8; ++k) {
+    int64_t n = 0;
+    for (uint32_t g = 0; g < ix.G; ++g) {
+      const int64_t ng = ix.offsets_h[g + 1] - ix.offsets_h[g];
+      if (ng <= (1 << k)) n += ng;
+    }
+    ix.small_share[k] = (float)((double)n / (double)std::max<uint64_t>(ix.N, 1));
+  }
   hipLaunchKernelGGL(grain_bounds_kernel, dim3(ix.G), dim3(256), 0, s, ix.codes, ix.eps, (int)ix.rp, (int)ix.r,
                      ix.goff, ix.boff, ix.blo, ix.bhi, ix.emin, ix.rmax);
   HIP_TRY(hipGetLastError());
 }
 
 // Scanning slot 0 first, pruning, then bucketing, projecting and scanning what is
-// left takes four more launches (about 20 us) than one projection of every
-// pair; that projection reads the probed grains' bases and a query row per
-// pair.  From MEAS_PAYS of them on the pruning pays where it prunes.
-bool prune_pays(const Index& ix, const hntl_search_params& sp, int64_t nq) {
+// left takes four more launches (10 us in a plan's graph, less where a stream of
+// single launches waits for the GPU) than one projection of every pair.  Measured
+// with and without on 20 to 10,000 queries over five indexes of 20,000 to 300,000
+// rows, uniform and Zipf sizes:
+//  - plans: even near 64 MB of bases and query rows or 12,000 pairs (100 x 12 over
+//    1,024 x 768: 165 -> 158 us; 3,000 x 8 over 256 x 256: 220 -> 196; 100 x 8 over
+//    256 x 256: 89 -> 98);
+//  - staged searches: even near 700 pairs (100 x 8 over 256 x 768: 130 -> 119 us; 20 x 8:
+//    107 -> 111) where few queries' nearest grain is too small to bound them;
+//    their pairs are all left, and packed 16 or 4 to a wave they run longer
+//    (3,000 x 8 over 1,024 Zipf-sized grains, 5% of the members in grains of at
+//    most C: 457 -> 471), until the projection saved outweighs it.
+bool prune_pays(const Index& ix, const hntl_search_params& sp, int64_t nq, bool plan) {
   if (sp.P < 2 || (sp.flags & HNTL_FLAG_NO_PRUNE) || sp.codes == HNTL_CODES_INT16) return false;
   // the learned router's probe budget has dropped most of them already
   if (sp.route == HNTL_ROUTE_LEARNED && sp.mass > 0.f && sp.mass < 1.f) return false;
   const int64_t rest = nq * (sp.P - 1);
   const int64_t basis = std::min<int64_t>(ix.G, rest) * ix.r * ((sp.flags & HNTL_FLAG_PROJECT_BF16) ? 2 : 4);
-  return (basis + rest * 4) * ix.d >= ((int64_t)64 << 20);
+  const int64_t bytes = (basis + rest * 4) * ix.d;
+  if (plan) return bytes >= ((int64_t)64 << 20) || rest >= 12288;
+  int k = 0;
+  while (k < 8 && (1u << k) < sp.C) ++k;
+  if (ix.small_share[k] <= 0.02f) return rest >= 704;
+  return bytes >= ((int64_t)128 << 20) && rest >= 8192;
 }
 
 void launch_prune_pairs(const Index& ix, int codes, const float* Q, const PruneArgs& a, hipStream_t s) {

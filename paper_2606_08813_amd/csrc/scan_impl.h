@@ -373,9 +373,12 @@ __global__ __launch_bounds__(64 * (ITEM / QT)) void scan_f32_kernel(
 
 template <int RP, int CAP, int CT>
 void launch_rp_cap(const Index& ix, const float* T, const float* epsq, int P, int C, const Buckets& b, int list,
-                   uint64_t* part, const uint64_t* bound_lists, bool prune, unsigned long long* scored, hipStream_t s) {
-  // unbounded lists (nearest grain) insert often: 4 pairs per wave for more
-  // waves in flight; bounded lists insert rarely: 16 pairs share every code load
+                   uint64_t* part, const uint64_t* bound_lists, bool prune, bool narrow,
+                   unsigned long long* scored, hipStream_t s) {
+  // unbounded lists (nearest grain) insert often, and pairs that a pruning has
+  // left are nearly all scanned: 4 pairs per wave for more waves in flight (16
+  // of the latter: 953 against 585 us for 1,000 queries x 12 over 1,024 Zipf-sized
+  // grains); other bounded lists insert rarely: 16 pairs share every code load
   constexpr int QT_WIDE = CAP <= 128 ? 16 : 8;
   const dim3 grid((unsigned)b.max_items[list]);
   const void* codes = CT == 0 ? (const void*)ix.codes
@@ -385,7 +388,7 @@ void launch_rp_cap(const Index& ix, const float* T, const float* epsq, int P, in
   const float* scales = CT == 3 ? ix.i16_steps : ix.scales;
   const float* eps = CT == 3 ? ix.eps_i16 : ix.eps;
   const ListRef ref = list_ref(b, list);
-  if (bound_lists == nullptr)
+  if (narrow)
     hipLaunchKernelGGL((scan_f32_kernel<RP, CAP, 4, CT>), grid, dim3(64 * (ITEM / 4)), 0, s, codes, scales, eps,
                        ix.goff,
                        ix.boff, ix.perm, (int)ix.r, T, epsq, P, C, ref, (int)ix.G, b.order, part, bound_lists, prune ? 1 : 0, ix.blo, ix.bhi, ix.emin, scored);
@@ -397,29 +400,30 @@ void launch_rp_cap(const Index& ix, const float* T, const float* epsq, int P, in
 
 template <int RP, int CT>
 void launch_rp(const Index& ix, const float* T, const float* epsq, int P, int C, const Buckets& b, int list,
-               uint64_t* part,
-               const uint64_t* bound_lists, bool prune, unsigned long long* scored, hipStream_t s) {
+               uint64_t* part, const uint64_t* bound_lists, bool prune, bool narrow, unsigned long long* scored,
+               hipStream_t s) {
   const int cap = pow2_at_least(C < 64 ? 64 : C);
   if (cap == 64)
-    launch_rp_cap<RP, 64, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, scored, s);
+    launch_rp_cap<RP, 64, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, narrow, scored, s);
   else if (cap == 128)
-    launch_rp_cap<RP, 128, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, scored, s);
+    launch_rp_cap<RP, 128, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, narrow, scored, s);
   else
-    launch_rp_cap<RP, 256, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, scored, s);
+    launch_rp_cap<RP, 256, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, narrow, scored, s);
 }
 
 template <int CT>
 void launch_ct(const Index& ix, const float* T, const float* epsq, int P, int C, const Buckets& b, int list,
-               uint64_t* part, const uint64_t* bound_lists, bool prune, unsigned long long* scored, hipStream_t s) {
+               uint64_t* part, const uint64_t* bound_lists, bool prune, bool narrow, unsigned long long* scored,
+               hipStream_t s) {
   switch (ix.rp) {
-    case 8: launch_rp<8, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, scored, s); break;
-    case 16: launch_rp<16, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, scored, s); break;
-    case 24: launch_rp<24, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, scored, s); break;
-    case 32: launch_rp<32, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, scored, s); break;
-    case 40: launch_rp<40, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, scored, s); break;
-    case 48: launch_rp<48, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, scored, s); break;
-    case 56: launch_rp<56, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, scored, s); break;
-    case 64: launch_rp<64, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, scored, s); break;
+    case 8: launch_rp<8, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, narrow, scored, s); break;
+    case 16: launch_rp<16, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, narrow, scored, s); break;
+    case 24: launch_rp<24, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, narrow, scored, s); break;
+    case 32: launch_rp<32, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, narrow, scored, s); break;
+    case 40: launch_rp<40, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, narrow, scored, s); break;
+    case 48: launch_rp<48, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, narrow, scored, s); break;
+    case 56: launch_rp<56, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, narrow, scored, s); break;
+    case 64: launch_rp<64, CT>(ix, T, epsq, P, C, b, list, part, bound_lists, prune, narrow, scored, s); break;
     default: throw ArgError{HNTL_EUNSUPPORTED, "padded rank must be a multiple of 8 up to 64"};
   }
 }

@@ -20,7 +20,7 @@ hntl_status fail(hntl_status s, const std::string& msg) {
 }
 
 Index::~Index() {
-  void* ptrs[] = {centroids, cnorm,    basis,   goff,      boff,     perm,       codes,  eps,
+  void* ptrs[] = {centroids, cnorm,    cnmax,   basis,   goff,      boff,     perm,       codes,  eps,
                   codes_bf16, codes_fp8, scales, basis_bf16, codes_i16, i16_steps, eps_i16, X,
                   blo,       bhi,       emin,   rmax,   gorder,     grank,  cent_split, eps_id};
   int prev = 0;

@@ -63,6 +63,7 @@ struct Index {
 
   float* centroids = nullptr;  // G x d
   float* cnorm = nullptr;      // G, ||mu_g||^2
+  float* cnmax = nullptr;      // 1: the largest of them
   float* basis = nullptr;      // G x r x d
   int32_t* goff = nullptr;     // G + 1 grain-order offsets
   int32_t* boff = nullptr;     // G + 1 block offsets
@@ -173,10 +174,11 @@ void launch_argmin_rows(const float* A, const float* an, int64_t rows, const flo
 // error is at most err (an[row] + bn[col]) and the winners are re-scored by
 // exact direct differences (routing).  Rows beyond *nlim - row_base get probes
 // -1.  overflow (optional, device) counts rows whose error window reached the
-// end of the shortlist and were re-read whole.
+// end of the shortlist and were re-read whole.  bmax: the largest bn (device).
+void launch_norm_max(const float* norms, int n, float* out, hipStream_t s);
 void launch_topk_rows(const float* D, int64_t rows, int cols, int P, int32_t* idx, float* val, hipStream_t s,
                       const float* A = nullptr, const float* an = nullptr, const float* Bm = nullptr,
-                      const float* bn = nullptr, int d = 0, float err = 0.f, const int32_t* nlim = nullptr,
+                      const float* bn = nullptr, const float* bmax = nullptr, int d = 0, float err = 0.f, const int32_t* nlim = nullptr,
                       int64_t row_base = 0, unsigned int* overflow = nullptr, float2* znorm = nullptr);
 
 // Centroid routing (Section 2.1 step 1): the P nearest centroids of every row

@@ -10,6 +10,7 @@
 // that the bound leaves in reach of the P-th by direct differences before it
 // picks the P probes.
 #include <algorithm>
+#include <type_traits>
 
 #include "hntl_device.h"
 #include "hntl_internal.h"
@@ -436,8 +437,9 @@ __global__ __launch_bounds__(256) void argmin_rows_kernel(const float* __restric
 // Top-P per row of D.  Without A/Bm: the P smallest entries of D.  With them
 // (routing), D holds expansion distances ||a||^2 + ||b||^2 - 2 <a, b> whose
 // error against the exact distance is at most err (||a||^2 + ||b||^2) per
-// entry (the caller's bound for its product form).  A shortlist of the M
-// smallest expansion values is kept; every entry j whose interval
+// entry (the caller's bound for its product form).  A shortlist of the
+// smallest expansion values is kept (all that the bounds leave in reach of the
+// P-th, or the M smallest where those are too many); every entry j whose interval
 // [D_j - bound_j, D_j + bound_j] reaches the P-th entry's upper end can still
 // be among the P nearest, so exactly those are re-scored by direct
 // differences ||a - b||^2 in FP32 and the P smallest exact distances are kept
@@ -448,7 +450,7 @@ __global__ __launch_bounds__(256) void argmin_rows_kernel(const float* __restric
 // inside the window is re-scored.
 //
 // Rows per workgroup, one per wave.
-constexpr int TOPK_ROWS = 8;
+constexpr int TOPK_ROWS = 4;
 
 // Direct FP32 squared distance of row a and column row b (both d long), one
 // wave, every lane ends with the total.
@@ -479,33 +481,18 @@ __device__ __forceinline__ float wave_dist(const float* __restrict__ a, const fl
   return wave_sum(acc);
 }
 
-__global__ __launch_bounds__(TOPK_ROWS * 64) void topk_rows_kernel(
-    const float* __restrict__ D, int64_t rows, int cols, int P, int M, const float* __restrict__ A,
-    const float* __restrict__ an, const float* __restrict__ Bm, const float* __restrict__ bn, int d, float err,
-    int32_t* __restrict__ idx, float* __restrict__ val, const int32_t* __restrict__ nlim, int64_t row_base,
-    unsigned int* __restrict__ overflow, float2* __restrict__ znorm, bool vec4) {
-  __shared__ uint64_t stage[TOPK_ROWS][64];
-  const int lane = lane_id(), wave = threadIdx.x >> 6;
-  const int64_t row = (int64_t)blockIdx.x * TOPK_ROWS + wave;
-  if (row >= rows) return;
-  if (nlim && row >= (int64_t)*nlim - row_base) {  // not part of this batch: no probes
-    if (lane < P) {
-      idx[row * P + lane] = -1;
-      if (val) val[row * P + lane] = __builtin_inff();
-    }
-    return;
-  }
-  const bool exact = A != nullptr;
+// The M smallest entries of a row of any length by a streamed top-64 list (one
+// wave; lane i of the result holds the i-th smallest key).  Segments of U chunks
+// of 64 columns, loaded together.  The 64 lanes' minima over a segment are 64
+// entries of the row, so their maximum bounds the row's 64th smallest value (>=
+// its M-th and P-th) from above: entries above the smallest such bound so far
+// cannot be selected and are not offered (fewer list flushes; the selection is
+// unchanged).
+__device__ __forceinline__ uint64_t row_smallest(const float* __restrict__ drow, int cols, int M, uint64_t* stage,
+                                                 bool znorm, float& mn, float& z) {
+  const int lane = lane_id();
   WaveTop64 L;
-  L.init(stage[wave], exact ? M : P);
-  const float* drow = D + row * cols;
-  // Segments of U chunks of 64 columns, loaded together.  The 64 lanes'
-  // minima over a segment are 64 entries of the row, so their maximum bounds
-  // the row's 64th smallest value (>= its M-th and P-th) from above: entries
-  // above the smallest such bound so far cannot be selected and are not
-  // offered (fewer list flushes; the selection is unchanged).  Segments of
-  // 16 chunks measured best (0.573 against 0.588 ms of routing without the
-  // bound at 16,384 x 8,192; longer segments cost more in occupancy).
+  L.init(stage, M);
   constexpr int U = 16;
   float T = __builtin_inff();  // uniform
   // znorm (negated scores): the row's smallest value mn and z = sum exp(mn - D_c),
@@ -547,31 +534,141 @@ __global__ __launch_bounds__(TOPK_ROWS * 64) void topk_rows_kernel(
   }
   L.finish();
   if (znorm) {
-    float mn = lmn;
+    mn = lmn;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) mn = fminf(mn, __shfl_xor(mn, o, 64));
-    const float z = wave_sum(lmn < __builtin_inff() ? lz * expf(mn - lmn) : 0.f);
-    if (lane == 0) znorm[row] = make_float2(mn, z);
+    z = wave_sum(lmn < __builtin_inff() ? lz * expf(mn - lmn) : 0.f);
   }
+  return L.best;
+}
+
+// Bitonic sort of one float per lane, ascending (no NaN).
+__device__ __forceinline__ float wave_sort64f(float v) {
+  const int lane = lane_id();
+  auto step = [&](auto jc, int k) {
+    constexpr int J = decltype(jc)::value;
+    const float o = __uint_as_float(lane_xor<J>(__float_as_uint(v)));
+    v = (((lane & k) == 0) == ((lane & J) == 0)) ? fminf(v, o) : fmaxf(v, o);
+  };
+#pragma unroll
+  for (int k = 2; k <= 64; k <<= 1) {
+    if (k >= 64) step(std::integral_constant<int, 32>{}, k);
+    if (k >= 32) step(std::integral_constant<int, 16>{}, k);
+    if (k >= 16) step(std::integral_constant<int, 8>{}, k);
+    if (k >= 8) step(std::integral_constant<int, 4>{}, k);
+    if (k >= 4) step(std::integral_constant<int, 2>{}, k);
+    step(std::integral_constant<int, 1>{}, k);
+  }
+  return v;
+}
+
+// The same for rows of up to 64 NCH columns, held in registers (NCH values per
+// lane, every load in flight at once).  The P-th smallest of the 64 lanes'
+// minima is at least the row's P-th smallest value T; every entry up to it plus
+// `slack` is collected (a compare and a ballot per chunk), and one sort orders
+// them.  Returns their number, or -1 if they are more than 64 (the caller
+// streams the row instead); lane i < number holds the i-th smallest key.
+template <int NCH>
+__device__ __forceinline__ int row_window(const float* __restrict__ drow, int cols, int P, float slack,
+                                          uint64_t* stage, bool znorm, float& mn, float& z, uint64_t& out) {
+  const int lane = lane_id();
+  float v[NCH];
+  // bounds-checked buffer loads: one address register, past the row's end reads 0
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(drow), 0, 4 * cols, 0x00027000);
+#pragma unroll
+  for (int u = 0; u < NCH; ++u)
+    v[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, 4 * lane + 4 * HNTL_WAVE * u, 0, 0));
+#pragma unroll
+  for (int u = 0; u < NCH; ++u)
+    if (lane >= cols - u * HNTL_WAVE) v[u] = __builtin_inff();
+  float own = v[0];
+#pragma unroll
+  for (int u = 1; u < NCH; ++u) own = fminf(own, v[u]);
+  const float srt = wave_sort64f(own == own ? own : __builtin_inff());
+  mn = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(srt), 0));
+  if (znorm) {
+    float lz = 0.f;
+    if (mn < __builtin_inff()) {
+#pragma unroll
+      for (int u = 0; u < NCH; ++u) lz += expf(mn - v[u]);
+    }
+    z = wave_sum(lz);
+  }
+  float T = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(srt), P - 1)) + slack;
+  T += 1e-6f * fabsf(T);
+  if (!(T < __builtin_inff())) return -1;  // padding must not qualify
+  int n = 0;
+#pragma unroll
+  for (int u = 0; u < NCH; ++u) {
+    const bool in = v[u] <= T;
+    const uint64_t m = __ballot(in);
+    if (m) {
+      const int at = n + mbcnt64(m);
+      if (in && at < 64) stage[at] = make_key(v[u], (uint32_t)(u * HNTL_WAVE + lane));
+      n += __popcll(m);
+    }
+  }
+  if (n > 64) return -1;
+  wave_sync();
+  const uint64_t k = lane < n ? stage[lane] : KEY_NONE;
+  wave_sync();
+  out = wave_sort64(k);
+  return n;
+}
+
+// Bound by memory (the row is read once: 135 us of 16,384 x 8,192 at 4 TB/s, then
+// 3 KB a re-scored entry from cache) with one row per wave and its whole row in
+// flight.  At 16,384 x 8,192: scores 144 us, distances with 27 re-scored entries
+// a row 217 us; a streamed list (16 chunks a segment, about ten flushes a row)
+// took 185 and 273.  256 such rows 29 us (49), 10,000 x 1,024 30 us (49), one row
+// of 1,024 5.8 us (10.8).
+// bmax: the largest bn (device).
+template <int NCH>
+__global__ __launch_bounds__(TOPK_ROWS * 64, NCH > 64 ? 3 : 4) void topk_rows_kernel(
+    const float* __restrict__ D, int64_t rows, int cols, int P, int M, const float* __restrict__ A,
+    const float* __restrict__ an, const float* __restrict__ Bm, const float* __restrict__ bn,
+    const float* __restrict__ bmax, int d, float err, int32_t* __restrict__ idx, float* __restrict__ val,
+    const int32_t* __restrict__ nlim, int64_t row_base, unsigned int* __restrict__ overflow,
+    float2* __restrict__ znorm, bool vec4) {
+  __shared__ uint64_t stage[TOPK_ROWS][64];
+  const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t row = (int64_t)blockIdx.x * TOPK_ROWS + wave;
+  if (row >= rows) return;
+  if (nlim && row >= (int64_t)*nlim - row_base) {  // not part of this batch: no probes
+    if (lane < P) {
+      idx[row * P + lane] = -1;
+      if (val) val[row * P + lane] = __builtin_inff();
+    }
+    return;
+  }
+  const bool exact = A != nullptr;
+  const float* drow = D + row * cols;
+  const float arow = exact ? an[row] : 0.f;
+  float mn = __builtin_inff(), z = 0.f;
+  uint64_t mine = KEY_NONE;  // lane i: the i-th smallest key of the shortlist
+  int have = -1;             // its length; every entry of the window is in it (-1: only the M smallest are)
+  if constexpr (NCH > 0)
+    have = row_window<NCH>(drow, cols, P, exact ? 2.f * err * (arow + *bmax) : 0.f, stage[wave], znorm != nullptr, mn,
+                           z, mine);
+  if (have < 0) mine = row_smallest(drow, cols, exact ? M : P, stage[wave], znorm != nullptr, mn, z);
+  if (znorm && lane == 0) znorm[row] = make_float2(mn, z);
   if (!exact) {
     if (lane < P) {
-      idx[row * P + lane] = L.best == KEY_NONE ? -1 : (int32_t)key_id(L.best);
-      if (val) val[row * P + lane] = L.best == KEY_NONE ? __builtin_inff() : key_dist(L.best);
+      idx[row * P + lane] = mine == KEY_NONE ? -1 : (int32_t)key_id(mine);
+      if (val) val[row * P + lane] = mine == KEY_NONE ? __builtin_inff() : key_dist(mine);
     }
     return;
   }
   // entries j >= P qualify while D_j - bound_j <= D_{P-1} + bound_{P-1}
-  const float arow = an[row];
-  const uint64_t mine = L.best;
   const uint64_t kp = shfl_u64(mine, P - 1);
-  const float hiP = key_dist(kp) + err * (arow + bn[key_id(kp)]);
-  const bool in = lane >= P && lane < M && mine != KEY_NONE &&
+  const float hiP = key_dist(kp) + err * (arow + bn[min(key_id(kp), (uint32_t)cols - 1)]);
+  const bool in = lane >= P && lane < (have < 0 ? M : 64) && mine != KEY_NONE &&
                   key_dist(mine) - err * (arow + bn[key_id(mine)]) <= hiP;
   const uint64_t qual = __ballot(in);
   const int Mr = qual ? 64 - __clzll(qual) : P;  // re-score the prefix [0, Mr)
   const float* a = A + row * d;
   uint64_t ex = KEY_NONE;
-  if (Mr == M && M < cols) {
+  if (have < 0 && Mr == M && M < cols) {
     // the window may extend past the shortlist: every column of the row whose
     // interval reaches hiP is re-scored, into a fresh top-P list
     if (overflow && lane == 0) atomicAdd(overflow, 1u);
@@ -602,14 +699,13 @@ __global__ __launch_bounds__(TOPK_ROWS * 64) void topk_rows_kernel(
 #pragma unroll
       for (int u = 0; u < RB; ++u) {
         const int j = j0 + u < Mr ? j0 + u : j0;
-        cs[u] = (int)key_id(shfl_u64(mine, j));
+        cs[u] = (int)min(key_id(shfl_u64(mine, j)), (uint32_t)cols - 1);  // (NaN rows have no entries)
         bp[u] = Bm + (size_t)cs[u] * d;
         acc[u] = 0.f;
       }
       if (vec4) {
-        // 16-byte loads: a round of RB entries covers 256 depths per load
-        // instruction (3 rounds for d = 768 instead of 12 with 4-byte loads)
-        constexpr int CH = 1;
+        // 16-byte loads, the whole rows' in flight up to 768 depths
+        constexpr int CH = NCH > 64 ? 3 : 1;
         for (int t0 = lane * 4; t0 < d; t0 += CH * 4 * HNTL_WAVE) {
           float4 av[CH], bv[CH][RB];
 #pragma unroll
@@ -622,7 +718,6 @@ __global__ __launch_bounds__(TOPK_ROWS * 64) void topk_rows_kernel(
           }
 #pragma unroll
           for (int i = 0; i < CH; ++i) {
-            if (t0 + i * 4 * HNTL_WAVE >= d) break;  // uniform
 #pragma unroll
             for (int u = 0; u < RB; ++u) {
               float df = av[i].x - bv[i][u].x;
@@ -658,6 +753,19 @@ __global__ __launch_bounds__(TOPK_ROWS * 64) void topk_rows_kernel(
     idx[row * P + lane] = (int32_t)key_id(ex);
     if (val) val[row * P + lane] = key_dist(ex);
   }
+}
+
+__global__ __launch_bounds__(1024) void max_kernel(const float* __restrict__ a, int n, float* __restrict__ out) {
+  __shared__ float red[1024];
+  float v = 0.f;
+  for (int i = threadIdx.x; i < n; i += 1024) v = fmaxf(v, a[i]);
+  red[threadIdx.x] = v;
+  __syncthreads();
+  for (int o = 512; o > 0; o >>= 1) {
+    if ((int)threadIdx.x < o) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + o]);
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *out = red[0];
 }
 
 // ------------------------------------------------------- brute-force kNN
@@ -1033,20 +1141,40 @@ void launch_argmin_rows(const float* A, const float* an, int64_t rows, const flo
   HIP_TRY(hipGetLastError());
 }
 
+void launch_norm_max(const float* norms, int n, float* out, hipStream_t s) {
+  hipLaunchKernelGGL(max_kernel, dim3(1), dim3(1024), 0, s, norms, n, out);
+  HIP_TRY(hipGetLastError());
+}
+
 void launch_topk_rows(const float* D, int64_t rows, int cols, int P, int32_t* idx, float* val, hipStream_t s,
-                      const float* A, const float* an, const float* Bm, const float* bn, int d, float err,
-                      const int32_t* nlim, int64_t row_base, unsigned int* overflow, float2* znorm) {
-  if (A && (!an || !bn || !Bm)) throw ArgError{HNTL_EINVAL, "routing re-score needs both norm vectors and the centroids"};
+                      const float* A, const float* an, const float* Bm, const float* bn, const float* bmax, int d,
+                      float err, const int32_t* nlim, int64_t row_base, unsigned int* overflow, float2* znorm) {
+  if (A && (!an || !bn || !Bm || !bmax))
+    throw ArgError{HNTL_EINVAL, "routing re-score needs both norm vectors, their bound and the centroids"};
   if (A && znorm) throw ArgError{HNTL_EINVAL, "the softmax normaliser is for score rows (no re-score)"};
   if (rows <= 0) return;
   if (P > HNTL_MAX_P) throw ArgError{HNTL_EUNSUPPORTED, "routing supports P <= 48"};
-  // shortlist: the window of the P-th entry plus 48 more (one key per lane)
+  // shortlist of a streamed row: the window of the P-th entry plus 48 more (one key per lane)
   const int M = A ? std::min(cols, std::min(64, P + 48)) : P;
   // float4 re-score loads where rows allow them
   const bool vec4 = A && (d % 4) == 0 && ((uintptr_t)A % 16) == 0 && ((uintptr_t)Bm % 16) == 0;
   dim3 grid((unsigned)((rows + TOPK_ROWS - 1) / TOPK_ROWS)), block(TOPK_ROWS * 64);
-  hipLaunchKernelGGL(topk_rows_kernel, grid, block, 0, s, D, rows, cols, P, M, A, an, Bm, bn, d, err, idx, val, nlim,
-                     row_base, overflow, znorm, vec4);
+#define HNTL_TOPK(NCH)                                                                                             \
+  hipLaunchKernelGGL(topk_rows_kernel<NCH>, grid, block, 0, s, D, rows, cols, P, M, A, an, Bm, bn, bmax, d, err, idx, \
+                     val, nlim, row_base, overflow, znorm, vec4)
+  // a row in registers up to 128 values a lane (162 VGPRs, three waves a SIMD;
+  // longer rows are streamed: twice the registers would leave one)
+  if (cols <= 1024)
+    HNTL_TOPK(16);
+  else if (cols <= 2048)
+    HNTL_TOPK(32);
+  else if (cols <= 4096)
+    HNTL_TOPK(64);
+  else if (cols <= 8192)
+    HNTL_TOPK(128);
+  else
+    HNTL_TOPK(0);
+#undef HNTL_TOPK
   HIP_TRY(hipGetLastError());
 }
 

@@ -984,7 +984,7 @@ void launch_route_centroid(const Index& ix, const float* Q, int64_t nq, int P, c
     else
       launch_dist_bf16(ix, Qc, w.qn + q0, rows, w.As, w.D, s, nlim, q0);
     launch_topk_rows(w.D, rows, G, P, probes + q0 * P, pdist ? pdist + q0 * P : nullptr, s, Qc, w.qn + q0,
-                     ix.centroids, ix.cnorm, d, route_err(w.form), nlim, q0, overflow);
+                     ix.centroids, ix.cnorm, ix.cnmax, d, route_err(w.form), nlim, q0, overflow);
   }
 }
 
@@ -1011,7 +1011,7 @@ void launch_route_learned(const Index& ix, const float* Q, int64_t nq, int P, fl
   o.scale = -1.f;
   gemm<false, false, EPI_BIAS_F32>(w.h2, rt.h2, rt.Wb[2], rt.h2, (int)nq, rt.G, rt.h2, o, s, nlim);
   const bool budget = mass > 0.f && mass < 1.f && P > 1;
-  launch_topk_rows(w.negS, nq, rt.G, P, probes, pdist, s, nullptr, nullptr, nullptr, nullptr, 0, 0.f, nlim, 0,
+  launch_topk_rows(w.negS, nq, rt.G, P, probes, pdist, s, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0.f, nlim, 0,
                    nullptr, (budget || tau > 0.f) ? w.znorm : nullptr);
   if (budget) {
     hipLaunchKernelGGL(mass_cut_kernel, dim3(blocks(nq, 4)), dim3(256), 0, s, w.negS, w.znorm, nq, rt.G, P, mass,
@@ -1031,7 +1031,7 @@ void launch_route_learned(const Index& ix, const float* Q, int64_t nq, int P, fl
       launch_dist_matrix(w.fb_Q + q0 * ix.d, w.fb_qn + q0, rows, ix.centroids, ix.cnorm, (int)ix.G, (int)ix.d,
                          w.negS, s, w.fb_count, q0);  // the scores are no longer needed: reuse as scratch
       launch_topk_rows(w.negS, rows, (int)ix.G, P, w.fb_probes + q0 * P, w.fb_pdist + q0 * P, s,
-                       w.fb_Q + q0 * ix.d, w.fb_qn + q0, ix.centroids, ix.cnorm, (int)ix.d, route_err(ROUTE_F32),
+                       w.fb_Q + q0 * ix.d, w.fb_qn + q0, ix.centroids, ix.cnorm, ix.cnmax, (int)ix.d, route_err(ROUTE_F32),
                        w.fb_count, q0, nullptr);
     }
     hipLaunchKernelGGL(scatter_probes_kernel, dim3((unsigned)nq), dim3(64), 0, s, w.fb_rows, w.fb_count, P,

@@ -213,6 +213,8 @@ void launch_grain_bounds(Index& ix, hipStream_t s) {
   if (!ix.bhi) ix.bhi = dev_alloc<float>(&ix, (size_t)ix.G * ix.rp);
   if (!ix.emin) ix.emin = dev_alloc<float>(&ix, ix.G);
   if (!ix.rmax) ix.rmax = dev_alloc<float>(&ix, ix.G);
+  if (!ix.cnmax) ix.cnmax = dev_alloc<float>(&ix, 1);
+  launch_norm_max(ix.cnorm, (int)ix.G, ix.cnmax, s);
   for (int k = 0; k <= 8; ++k) {
     int64_t n = 0;
     for (uint32_t g = 0; g < ix.G; ++g) {

@@ -87,24 +87,120 @@ __global__ void gather_rows_kernel(const float* __restrict__ X, int d, const int
 // sampled candidates per step and the one that lowers the potential most kept).
 // State: closest[i] = squared distance of seeding row i to its nearest chosen
 // centroid; partial[blk] = sum of closest over 256-row blocks (FP64).
+// Bound by latency: a step's row reads take 2 us from the L2 (32,768 x 128), but
+// its draws, distances, choice and update wait for each other.  Three launches
+// a step (sample, evaluate, choose and apply), every sum in a fixed order.  127
+// steps over 32,768 x 128 took 10.7 ms in seven launches each, the draws alone
+// 47 us of dependent loads by one thread per candidate; now 3.7 ms (11 us to draw, 13 to
+// evaluate, 5 to apply).
 constexpr int KPP_MAXL = 16;
+constexpr int KPP_ROWS = 256;        // rows of a block
+constexpr int KPP_MAXBLK = 1024;     // blocks: at most 262,144 seeding rows
+constexpr int KPP_DIRECT_ROWS = 16;  // up to so many rows: distances by direct differences
 
-// Per-block potentials potpart[blk][t] = sum_i min(closest[i], dcand[i][t])
-// over 256-row blocks, from the candidate distances dcand (n x L, computed by
-// the MFMA distance kernel).
-__global__ __launch_bounds__(256) void kpp_pot_kernel(int64_t n, int L, const float* __restrict__ dcand,
-                                                      const float* __restrict__ closest, int first,
-                                                      double* __restrict__ potpart) {
+// lane (i, kq)'s depths 4 kq .. 4 kq + 3 of row i -> depths kq, 4 + kq, 8 + kq, 12 + kq
+// (the four depths a lane feeds to successive MFMA steps of K = 4)
+__device__ __forceinline__ void transpose_depths(float4& v) {
+  auto swap32 = [](float& x, float& y) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    x = __uint_as_float(r[0]);
+    y = __uint_as_float(r[1]);
+  };
+  auto swap16 = [](float& x, float& y) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    x = __uint_as_float(r[0]);
+    y = __uint_as_float(r[1]);
+  };
+  swap32(v.x, v.z);
+  swap32(v.y, v.w);
+  swap16(v.x, v.y);
+  swap16(v.z, v.w);
+}
+
+// Distances of a block's 256 rows to the L candidate rows (16 rows x 16
+// candidates per wave on the FP32 matrix cores, operands straight from global
+// memory; the depth order of tile_dot), dcand[t * n + i], and the block's
+// potentials potpart[blk][t] = sum_i min(closest[i], dcand[t][i]).
+template <bool VEC>
+__global__ __launch_bounds__(1024) void kpp_eval_kernel(const float* __restrict__ Xs, const float* __restrict__ xn,
+                                                        int64_t n, int d, const int32_t* __restrict__ cand, int L,
+                                                        const float* __restrict__ closest, int first,
+                                                        float* __restrict__ dcand, double* __restrict__ potpart) {
+  __shared__ float ds[KPP_MAXL][KPP_ROWS + 4];
   __shared__ double red[4][KPP_MAXL];
   const int lane = lane_id(), wave = threadIdx.x >> 6;
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const float ci = (i < n && !first) ? closest[i] : __builtin_inff();
+  const int i = lane & 15, kq = lane >> 4;
+  const int64_t blk0 = (int64_t)blockIdx.x * KPP_ROWS;
+  // for the potentials: 64 rows and 4 candidates a wave
+  const int rg = wave & 3, tg = wave >> 2;
+  const int64_t prow = blk0 + rg * 64 + lane;
+  const float ci = (prow < n && !first) ? closest[prow] : __builtin_inff();
+  if (n <= KPP_DIRECT_ROWS && d <= 16 * HNTL_WAVE) {
+    for (int p = wave; p < (int)n * L; p += 16) {
+      const float* a = Xs + (size_t)(p / L) * d;
+      const float* b = Xs + (size_t)cand[p % L] * d;
+      float acc = 0.f;
+      for (int j = lane; j < d; j += HNTL_WAVE) {
+        const float df = a[j] - b[j];
+        acc = fmaf(df, df, acc);
+      }
+      acc = wave_sum(acc);
+      if (lane == 0) ds[p % L][p / L] = acc;
+    }
+  } else {
+    const int64_t row = blk0 + wave * 16 + i < n ? blk0 + wave * 16 + i : n - 1;
+    const float* a = Xs + row * d;
+    const int cr = cand[i < L ? i : 0];
+    const float* b = Xs + (size_t)cr * d;
+    const float bn = xn[cr];
+    float an[4];
 #pragma unroll
-  for (int t = 0; t < KPP_MAXL; ++t) {
+    for (int t = 0; t < 4; ++t) {
+      const int64_t r = blk0 + wave * 16 + 4 * kq + t;
+      an[t] = xn[r < n ? r : n - 1];
+    }
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    constexpr int U = 8;  // 16 depths each
+    for (int k0 = 0; k0 < d; k0 += 16 * U) {
+      float4 av[U], bv[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if constexpr (VEC) {
+          const int k = k0 + 16 * u + 4 * kq;
+          av[u] = k < d ? *reinterpret_cast<const float4*>(a + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+          bv[u] = k < d ? *reinterpret_cast<const float4*>(b + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+        } else {
+          const int k = k0 + 16 * u + kq;
+          av[u] = make_float4(k < d ? a[k] : 0.f, k + 4 < d ? a[k + 4] : 0.f, k + 8 < d ? a[k + 8] : 0.f,
+                              k + 12 < d ? a[k + 12] : 0.f);
+          bv[u] = make_float4(k < d ? b[k] : 0.f, k + 4 < d ? b[k + 4] : 0.f, k + 8 < d ? b[k + 8] : 0.f,
+                              k + 12 < d ? b[k + 12] : 0.f);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if constexpr (VEC) {
+          transpose_depths(av[u]);
+          transpose_depths(bv[u]);
+        }
+        acc = mfma16x16x4(av[u].x, bv[u].x, acc);
+        acc = mfma16x16x4(av[u].y, bv[u].y, acc);
+        acc = mfma16x16x4(av[u].z, bv[u].z, acc);
+        acc = mfma16x16x4(av[u].w, bv[u].w, acc);
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) ds[i][wave * 16 + 4 * kq + t] = fmaxf(an[t] + bn - 2.f * acc[t], 0.f);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int t = 4 * tg + q;
     if (t < L) {
-      const double v = i < n ? (double)fminf(ci, dcand[(size_t)i * L + t]) : 0.0;
-      const double w = wave_sum_d(v);
-      if (lane == 0) red[wave][t] = w;
+      const float dc = ds[t][rg * 64 + lane];
+      if (prow < n) dcand[(size_t)t * n + prow] = dc;
+      const double w = wave_sum_d(prow < n ? (double)fminf(ci, dc) : 0.0);
+      if (lane == 0) red[rg][t] = w;
     }
   }
   __syncthreads();
@@ -113,95 +209,137 @@ __global__ __launch_bounds__(256) void kpp_pot_kernel(int64_t n, int L, const fl
         red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x];
 }
 
-// Single workgroup: the candidate with the lowest potential (ties to the lower
-// candidate slot) becomes centroid `step`.
-__global__ __launch_bounds__(64) void kpp_choose_kernel(const float* __restrict__ Xs, int d,
-                                                        const int32_t* __restrict__ cand, int L,
-                                                        const double* __restrict__ potpart, int nblk,
-                                                        int32_t* __restrict__ tstar, float* __restrict__ cent,
-                                                        int step) {
-  __shared__ int best_t;
-  // potential of each candidate: the 64 lanes sum strided block partials, then
-  // a butterfly reduction (fixed order, so the choice is reproducible)
-  double acc[KPP_MAXL];
+// The candidate with the lowest potential (ties to the lower candidate slot)
+// becomes centroid `step`: every workgroup sums the block partials (64 strided
+// sums, then a butterfly) and makes the same choice t*.  Then closest[i] =
+// min(closest[i], dcand[t*][i]) and per-block sums of closest.
+__global__ __launch_bounds__(KPP_ROWS) void kpp_apply_kernel(const float* __restrict__ Xs, int64_t n, int d,
+                                                             const int32_t* __restrict__ cand, int L,
+                                                             const float* __restrict__ dcand,
+                                                             const double* __restrict__ potpart, int nblk, int first,
+                                                             float* __restrict__ closest,
+                                                             double* __restrict__ partial, float* __restrict__ cent) {
+  __shared__ double pot[KPP_MAXL];
+  __shared__ double red[KPP_ROWS];
+  const int lane = lane_id(), wave = threadIdx.x >> 6;
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int b = lane; b < nblk; b += 64)
 #pragma unroll
-  for (int t = 0; t < KPP_MAXL; ++t) acc[t] = 0.0;
-  for (int b = threadIdx.x; b < nblk; b += 64)
+    for (int q = 0; q < 4; ++q)
+      if (4 * wave + q < L) acc[q] += potpart[(size_t)b * L + 4 * wave + q];
 #pragma unroll
-    for (int t = 0; t < KPP_MAXL; ++t)
-      if (t < L) acc[t] += potpart[(size_t)b * L + t];
-#pragma unroll
-  for (int t = 0; t < KPP_MAXL; ++t) acc[t] = wave_sum_d(acc[t]);
-  if (threadIdx.x == 0) {
-    double best = 0.0;
-    int bt = 0;
-    for (int t = 0; t < L; ++t)
-      if (t == 0 || acc[t] < best) {
-        best = acc[t];
-        bt = t;
-      }
-    best_t = bt;
-    *tstar = bt;
+  for (int q = 0; q < 4; ++q) {
+    acc[q] = wave_sum_d(acc[q]);
+    if (lane == 0) pot[4 * wave + q] = acc[q];
   }
   __syncthreads();
-  const float* src = Xs + (size_t)cand[best_t] * d;
-  for (int j = threadIdx.x; j < d; j += blockDim.x) cent[(size_t)step * d + j] = src[j];
-}
-
-// closest[i] = min(closest[i], dcand[i][t*]); per-block sums of closest.
-__global__ __launch_bounds__(256) void kpp_apply_kernel(int64_t n, int L, const float* __restrict__ dcand,
-                                                        const int32_t* __restrict__ tstar, int first,
-                                                        float* __restrict__ closest, double* __restrict__ partial) {
-  __shared__ double red[256];
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  double best = pot[0];
+  int bt = 0;
+  for (int t = 1; t < L; ++t)
+    if (pot[t] < best) {
+      best = pot[t];
+      bt = t;
+    }
+  if (blockIdx.x == 0) {
+    const float* src = Xs + (size_t)cand[bt] * d;
+    for (int j = threadIdx.x; j < d; j += KPP_ROWS) cent[j] = src[j];
+  }
+  const int64_t i = (int64_t)blockIdx.x * KPP_ROWS + threadIdx.x;
   double v = 0.0;
   if (i < n) {
-    const float dc = dcand[(size_t)i * L + *tstar];
+    const float dc = dcand[(size_t)bt * n + i];
     const float c = first ? dc : fminf(closest[i], dc);
     closest[i] = c;
     v = (double)c;
   }
   red[threadIdx.x] = v;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
+  for (int o = KPP_ROWS / 2; o > 0; o >>= 1) {
     if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
     __syncthreads();
   }
   if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
 }
 
+// Value of lane q (uniform).
+__device__ __forceinline__ double from_lane(double v, int q) {
+  const uint64_t u = __double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, q), hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), q);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
 // Single workgroup: L candidates sampled with probability proportional to
-// closest[] (thread t draws candidate t from uniform u[t]).
-__global__ __launch_bounds__(64) void kpp_sample_kernel(int64_t n, const float* __restrict__ closest,
-                                                        const double* __restrict__ partial, int nblk,
-                                                        const double* __restrict__ u, int L,
-                                                        int32_t* __restrict__ cand) {
-  const int t = threadIdx.x;
-  if (t >= L) return;
-  double tot = 0.0;
-  for (int b = 0; b < nblk; ++b) tot += partial[b];
-  int64_t pick = (int64_t)(u[t] * (double)n);
-  if (tot > 0.0) {
-    const double target = u[t] * tot;
+// closest[], candidate t from uniform u[t] by wave t.  The running sums over the
+// blocks are formed once, in order, and kept in the LDS; a wave finds its block
+// in them and adds that block's rows up in order.  Both chains take their terms
+// from other lanes' registers: nothing but the additions is on them.
+__global__ __launch_bounds__(KPP_MAXL * 64) void kpp_sample_kernel(int64_t n, const float* __restrict__ closest,
+                                                                   const double* __restrict__ partial, int nblk,
+                                                                   const double* __restrict__ u, int L,
+                                                                   int32_t* __restrict__ cand) {
+  __shared__ double incl[KPP_MAXBLK];  // sum of the blocks up to and including b
+  const int lane = lane_id(), wave = threadIdx.x >> 6;
+  const double ut = wave < L ? u[wave] : 0.0;
+  if (wave == 0) {
     double run = 0.0;
-    int b = 0;
-    for (; b < nblk - 1; ++b) {
-      if (run + partial[b] > target) break;
-      run += partial[b];
+    double next = lane < nblk ? partial[lane] : 0.0;
+    for (int b0 = 0; b0 < nblk; b0 += 64) {
+      const double p = next;
+      if (b0 + 64 < nblk) next = b0 + 64 + lane < nblk ? partial[b0 + 64 + lane] : 0.0;
+      double mine = 0.0;
+#pragma unroll
+      for (int q = 0; q < 64; ++q) {
+        run += from_lane(p, q);  // blocks past the last repeat its sum
+        mine = lane == q ? run : mine;
+      }
+      incl[b0 + lane] = mine;
     }
-    const int64_t lo = (int64_t)b * 256, hi = n < lo + 256 ? n : lo + 256;
-    pick = hi - 1;
-    for (int64_t i = lo; i < hi; ++i) {
-      run += (double)closest[i];
-      if (run > target) {
-        pick = i;
+  }
+  __syncthreads();
+  if (wave >= L) return;
+  const double tot = incl[nblk - 1];
+  int64_t pick = (int64_t)(ut * (double)n);
+  if (tot > 0.0) {
+    const double target = ut * tot;
+    int b = nblk - 1;
+    for (int b0 = 0; b0 < nblk - 1; b0 += 64) {
+      const uint64_t m = __ballot(b0 + lane < nblk - 1 && incl[b0 + lane] > target);
+      if (m) {
+        b = b0 + __builtin_ctzll(m);
         break;
       }
     }
+    double run = b ? incl[b - 1] : 0.0;
+    const int64_t lo = (int64_t)b * KPP_ROWS;
+    const int cnt = (int)(n - lo < KPP_ROWS ? n - lo : KPP_ROWS);
+    float v[KPP_ROWS / 64];
+#pragma unroll
+    for (int q = 0; q < KPP_ROWS / 64; ++q) v[q] = q * 64 + lane < cnt ? closest[lo + q * 64 + lane] : 0.f;
+    int hit = cnt - 1;
+    bool found = false;
+#pragma unroll
+    for (int q = 0; q < KPP_ROWS / 64; ++q) {
+      for (int j0 = 0; j0 < 64 && !found; j0 += 16) {
+        const double before = run;
+#pragma unroll
+        for (int j = 0; j < 16; ++j)
+          run += (double)__uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v[q]), j0 + j));
+        if (run > target) {  // the sums never fall: the first above it is one of these 16
+          found = true;
+          run = before;
+          hit = q * 64 + j0 - 1;
+          do {
+            ++hit;
+            run += (double)__uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v[q]), hit & 63));
+          } while (!(run > target));
+        }
+      }
+    }
+    pick = lo + hit;
   }
   if (pick >= n) pick = n - 1;
   if (pick < 0) pick = 0;
-  cand[t] = (int32_t)pick;
+  if (lane == 0) cand[wave] = (int32_t)pick;
 }
 
 // FP64 mean of the rows listed in order[off[g]..off[g+1]) (fixed summation
@@ -655,7 +793,7 @@ extern "C" hntl_status hntl_build(const float* X, uint64_t N, uint32_t d, const 
 
     // ---------------- k-means: training subset (partial Fisher-Yates)
     const int64_t n_train = std::min<int64_t>((int64_t)N, (int64_t)tpg * G);
-    const int64_t n_seed = std::min<int64_t>(n_train, (int64_t)262144);
+    const int64_t n_seed = std::min<int64_t>(n_train, (int64_t)KPP_MAXBLK * KPP_ROWS);
     std::vector<int32_t> tr_idx(n_train);
     {
       std::vector<int32_t> all(N);
@@ -688,16 +826,15 @@ extern "C" hntl_status hntl_build(const float* X, uint64_t N, uint32_t d, const 
     if (params->init_centroids) {
       HIP_TRY(hipMemcpyAsync(ix->centroids, params->init_centroids, sizeof(float) * G * d, hipMemcpyDefault, s));
     } else {
-      const int nblk = (int)((n_seed + 255) / 256);
+      const int nblk = (int)((n_seed + KPP_ROWS - 1) / KPP_ROWS);
       const int L = KPP_MAXL;  // 2 + ln G candidates still merge well-separated clusters in about 1 run of 4
       float* closest = dev_alloc<float>(nullptr, n_seed);
       double* partial = dev_alloc<double>(nullptr, nblk);
       float* dcand = dev_alloc<float>(nullptr, (size_t)n_seed * L);
       double* potpart = dev_alloc<double>(nullptr, (size_t)nblk * L);
       int32_t* cand = dev_alloc<int32_t>(nullptr, KPP_MAXL);
-      int32_t* tstar = dev_alloc<int32_t>(nullptr, 1);
       double* uu = dev_alloc<double>(nullptr, (size_t)G * KPP_MAXL);
-      tmp.p.insert(tmp.p.end(), {closest, partial, dcand, potpart, cand, tstar, uu});
+      tmp.p.insert(tmp.p.end(), {closest, partial, dcand, potpart, cand, uu});
       // all uniforms of the seeding, drawn up front from the counter-based hash
       std::vector<double> uh((size_t)G * KPP_MAXL);
       for (uint32_t st = 0; st < G; ++st)
@@ -706,29 +843,20 @@ extern "C" hntl_status hntl_build(const float* X, uint64_t N, uint32_t d, const 
       // first centroid: a uniformly drawn seeding row
       const int32_t first = (int32_t)std::min<int64_t>(n_seed - 1, (int64_t)(uh[0] * (double)n_seed));
       HIP_TRY(hipMemcpyAsync(cand, &first, sizeof(int32_t), hipMemcpyHostToDevice, s));
-      float* cand_rows = dev_alloc<float>(nullptr, (size_t)KPP_MAXL * d);
-      float* cand_norm = dev_alloc<float>(nullptr, KPP_MAXL);
-      tmp.p.insert(tmp.p.end(), {cand_rows, cand_norm});
-      // candidate distances on the MFMA distance kernel, then potentials
-      auto evaluate = [&](int Lc, int first_step) {
-        hipLaunchKernelGGL(gather_rows_kernel, dim3(Lc), dim3(256), 0, s, Xt, (int)d, cand, (int64_t)Lc, cand_rows);
-        launch_row_norms(cand_rows, Lc, (int)d, cand_norm, s);
-        launch_dist_candidates(Xt, xtn, n_seed, cand_rows, cand_norm, Lc, (int)d, dcand, s);
-        hipLaunchKernelGGL(kpp_pot_kernel, dim3(nblk), dim3(256), 0, s, n_seed, Lc, dcand, closest, first_step,
-                           potpart);
-      };
-      evaluate(1, 1);
-      hipLaunchKernelGGL(kpp_choose_kernel, dim3(1), dim3(64), 0, s, Xt, (int)d, cand, 1, potpart, nblk, tstar,
-                         ix->centroids, 0);
-      hipLaunchKernelGGL(kpp_apply_kernel, dim3(nblk), dim3(256), 0, s, n_seed, 1, dcand, tstar, 1, closest, partial);
-      for (uint32_t step = 1; step < G; ++step) {
-        hipLaunchKernelGGL(kpp_sample_kernel, dim3(1), dim3(64), 0, s, n_seed, closest, partial, nblk,
-                           uu + (size_t)step * KPP_MAXL, L, cand);
-        evaluate(L, 0);
-        hipLaunchKernelGGL(kpp_choose_kernel, dim3(1), dim3(64), 0, s, Xt, (int)d, cand, L, potpart, nblk, tstar,
-                           ix->centroids, (int)step);
-        hipLaunchKernelGGL(kpp_apply_kernel, dim3(nblk), dim3(256), 0, s, n_seed, L, dcand, tstar, 0, closest,
-                           partial);
+      const bool vec4 = (d % 4) == 0;  // dev_alloc rows
+      for (uint32_t step = 0; step < G; ++step) {
+        const int Lc = step ? L : 1;
+        if (step)
+          hipLaunchKernelGGL(kpp_sample_kernel, dim3(1), dim3(KPP_MAXL * 64), 0, s, n_seed, closest, partial, nblk,
+                             uu + (size_t)step * KPP_MAXL, Lc, cand);
+        if (vec4)
+          hipLaunchKernelGGL(kpp_eval_kernel<true>, dim3(nblk), dim3(1024), 0, s, Xt, xtn, n_seed, (int)d, cand, Lc,
+                             closest, step == 0, dcand, potpart);
+        else
+          hipLaunchKernelGGL(kpp_eval_kernel<false>, dim3(nblk), dim3(1024), 0, s, Xt, xtn, n_seed, (int)d, cand, Lc,
+                             closest, step == 0, dcand, potpart);
+        hipLaunchKernelGGL(kpp_apply_kernel, dim3(nblk), dim3(KPP_ROWS), 0, s, Xt, n_seed, (int)d, cand, Lc, dcand,
+                           potpart, nblk, step == 0, closest, partial, ix->centroids + (size_t)step * d);
       }
       HIP_TRY(hipGetLastError());
     }

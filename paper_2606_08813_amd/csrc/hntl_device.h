@@ -65,12 +65,6 @@ __device__ __forceinline__ int mbcnt64(uint64_t m) {
   return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-__device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
 // ------------------------------------------- register-resident top-64 list
 // One wave keeps the C <= 64 smallest keys of a stream, the sorted list held
 // in registers, one key per lane (lane i holds the i-th smallest).  A key is
@@ -185,6 +179,22 @@ __device__ __forceinline__ float wave_sum(float v) {
   v += __uint_as_float(lane_xor<4>(__float_as_uint(v)));
   v += __uint_as_float(lane_xor<2>(__float_as_uint(v)));
   v += __uint_as_float(lane_xor<1>(__float_as_uint(v)));
+  return v;
+}
+
+template <int J>
+__device__ __forceinline__ double lane_xor_d(double v) {
+  const uint64_t u = __double_as_longlong(v);
+  return __longlong_as_double((long long)(((uint64_t)lane_xor<J>((uint32_t)(u >> 32)) << 32) | lane_xor<J>((uint32_t)u)));
+}
+
+__device__ __forceinline__ double wave_sum_d(double v) {
+  v += lane_xor_d<32>(v);
+  v += lane_xor_d<16>(v);
+  v += lane_xor_d<8>(v);
+  v += lane_xor_d<4>(v);
+  v += lane_xor_d<2>(v);
+  v += lane_xor_d<1>(v);
   return v;
 }
 

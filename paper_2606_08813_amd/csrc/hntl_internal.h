@@ -165,9 +165,6 @@ void launch_dist_bf16(const Index& ix, const float* A, const float* an, int64_t 
 void launch_dist_matrix(const float* A, const float* an, int64_t rows, const float* Bm, const float* bn,
                         int cols, int d, float* D, hipStream_t s, const int32_t* nlim = nullptr,
                         int64_t row_base = 0);
-// Distances of the seeding rows to a few k-means++ candidates (more rows than a direct pass takes).
-void launch_dist_candidates(const float* A, const float* an, int64_t rows, const float* Bm, const float* bn, int cols,
-                            int d, float* D, hipStream_t s);
 void launch_argmin_rows(const float* A, const float* an, int64_t rows, const float* Bm, const float* bn,
                         int cols, int d, int32_t* label, float* dmin, hipStream_t s);
 // top-P per row of D; with A and Bm given, D holds expansion distances whose

@@ -275,9 +275,8 @@ __global__ __launch_bounds__(64 * WR * WC) void dist_tile_kernel(const float* __
     }
 }
 
-// The same distances on tile_dot: short rows, rows that allow no 16-byte loads
-// (odd depths, unaligned operands), and the k-means seeding, whose picks
-// follow the values' last bits.
+// The same distances on tile_dot: short rows and rows that allow no 16-byte
+// loads (odd depths, unaligned operands).
 __global__ __launch_bounds__(256) void dist_matrix_kernel(const float* __restrict__ A, const float* __restrict__ an,
                                                           int64_t rows, const float* __restrict__ Bm,
                                                           const float* __restrict__ bn, int cols, int d,
@@ -1120,15 +1119,6 @@ void launch_dist_matrix(const float* A, const float* an, int64_t rows, const flo
   }
   dim3 grid((unsigned)((rows + TM - 1) / TM), (unsigned)((cols + TN - 1) / TN));
   hipLaunchKernelGGL(dist_matrix_kernel, grid, dim3(256), 0, s, A, an, rows, Bm, bn, cols, d, D, vec4, nlim, row_base);
-  HIP_TRY(hipGetLastError());
-}
-
-void launch_dist_candidates(const float* A, const float* an, int64_t rows, const float* Bm, const float* bn, int cols,
-                            int d, float* D, hipStream_t s) {
-  if (rows <= DIRECT_ROWS && d <= 16 * HNTL_WAVE) return launch_dist_matrix(A, an, rows, Bm, bn, cols, d, D, s);
-  const bool vec4 = (d % 4) == 0 && ((uintptr_t)A % 16) == 0 && ((uintptr_t)Bm % 16) == 0;
-  dim3 grid((unsigned)((rows + TM - 1) / TM), (unsigned)((cols + TN - 1) / TN));
-  hipLaunchKernelGGL(dist_matrix_kernel, grid, dim3(256), 0, s, A, an, rows, Bm, bn, cols, d, D, vec4, nullptr, 0);
   HIP_TRY(hipGetLastError());
 }
 

@@ -446,6 +446,93 @@ __global__ void randn_kernel(double* __restrict__ V, int64_t n, uint64_t seed, u
   if (i < n) V[i] = 2.0 * u01(seed, stream, (uint64_t)i) - 1.0;
 }
 
+// Cholesky factor of a grain's Gram matrix M = Y^T Y = R^T R and Y := Y R^-1, one
+// thread per row of Y (column-major d x b, b <= NB; M is read as b x b).
+// grid (ceil(d / 256), chunk); every workgroup of a grain factors M for itself.
+// Bound by latency: the b elimination steps wait for each other (a reciprocal and
+// a row each), the rows then take b^2 / 2 FP64 products each from registers and
+// the LDS.  Up to 32 columns one wave eliminates with a column per lane, in
+// registers; above that the registers do not hold it (64 columns: 512 and
+// spills) and 256 threads work in the LDS, one barrier a step.  128 grains of
+// 128 x 32: 17 us (25 in the LDS; the library's Cholesky and triangular solve
+// took 40 us in five launches, 74 with the gaps between them).
+// A row of M that cancels to nothing or below (rank loss within the rounding)
+// counts with 2^-52 of its diagonal: the next orthogonalisation mends the column.
+template <int NB>
+__global__ __launch_bounds__(256) void chol_solve_kernel(const double* __restrict__ M, int b, double* __restrict__ Y,
+                                                         int d) {
+  __shared__ double A[NB][NB + 2];  // upper triangle: row k ends as the unscaled row k of the factor
+  __shared__ double diag[NB], pinv[NB], dinv[NB];
+  const double* Mg = M + (size_t)blockIdx.y * b * b;
+  double* Yg = Y + (size_t)blockIdx.y * d * b;
+  const int row = blockIdx.x * 256 + threadIdx.x;
+  double y[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) y[j] = (row < d && j < b) ? Yg[(size_t)j * d + row] : 0.0;
+  for (int e = threadIdx.x; e < NB * NB; e += 256) {
+    const int i = e / NB, j = e % NB;
+    const double v = (i < b && j < b) ? Mg[(size_t)j * b + i] : (i == j ? 1.0 : 0.0);
+    A[i][j] = v;
+    if (i == j) diag[i] = v;
+  }
+  __syncthreads();
+  if constexpr (NB <= 32) {
+    // one wave, column j of the triangle in lane j's registers
+    if (threadIdx.x < 64) {
+      const int j = threadIdx.x < NB ? threadIdx.x : NB - 1;
+      double c[NB];
+#pragma unroll
+      for (int k = 0; k < NB; ++k) c[k] = A[k][j];
+      const double dj = diag[j];
+      double pis = 1.0;
+#pragma unroll
+      for (int k = 0; k < NB; ++k) {  // rows from b on are the identity's
+        double p = from_lane(c[k], k);
+        if (p <= 0.0) p = 0x1p-52 * from_lane(dj, k);
+        const double pi = 1.0 / p;
+        if (j == k) pis = pi;
+        const double t = c[k] * pi;
+#pragma unroll
+        for (int i = k + 1; i < NB; ++i) c[i] = fma(-from_lane(c[k], i), t, c[i]);
+      }
+      if (threadIdx.x < NB) {
+#pragma unroll
+        for (int k = 0; k < NB; ++k) A[k][j] = c[k];  // (below the diagonal: never read)
+        pinv[j] = pis;
+        dinv[j] = sqrt(pis);
+      }
+    }
+    __syncthreads();
+  } else {
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+    for (int k = 0; k < b; ++k) {
+      double p = A[k][k];
+      if (p <= 0.0) p = 0x1p-52 * diag[k];
+      const double pi = 1.0 / p;
+      if (threadIdx.x == 0) {
+        pinv[k] = pi;
+        dinv[k] = sqrt(pi);
+      }
+      for (int i = k + 1 + ty; i < b; i += 16) {
+        const double f = A[k][i] * pi;
+        for (int j = i - ((i - k - 1 - tx) & 15) + 16 * (((i - k - 1 - tx) & 15) != 0); j < b; j += 16)
+          A[i][j] = fma(-f, A[k][j], A[i][j]);
+      }
+      __syncthreads();
+    }
+  }
+  if (row >= d) return;
+#pragma unroll
+  for (int k = 0; k < NB; ++k) {
+    if (k < b) {
+      const double t = y[k] * pinv[k];
+#pragma unroll
+      for (int j = k + 1; j < NB; ++j) y[j] = fma(-t, A[k][j], y[j]);
+      Yg[(size_t)k * d + row] = y[k] * dinv[k];
+    }
+  }
+}
+
 // Top-r Ritz vectors (columns b-1, b-2, ... of Wf, column-major d x b) ->
 // sign-fixed FP64 rows Wd[slot][j][:] and FP32 basis rows of grain gmap[slot].
 // grid (r, chunk).
@@ -679,10 +766,16 @@ void pca_encode_grains(Index* ix, const int64_t* d_off, const std::vector<int32_
         rb(rocblas_dgemm_strided_batched(blas.h, rocblas_operation_transpose, rocblas_operation_none, bsz, bsz, (int)d,
                                          &one, Yp, (int)d, sV, Yp, (int)d, sV, &zero, M, bsz, sM, gc),
            "dgemm Y^T*Y");
-        rb(rocsolver_dpotrf_strided_batched(blas.h, rocblas_fill_upper, bsz, M, bsz, sM, info, gc), "dpotrf");
-        rb(rocblas_dtrsm_strided_batched(blas.h, rocblas_side_right, rocblas_fill_upper, rocblas_operation_none,
-                                         rocblas_diagonal_non_unit, (int)d, bsz, &one, M, bsz, sM, Yp, (int)d, sV, gc),
-           "dtrsm");
+        const dim3 grid((d + 255) / 256, gc);
+        if (bsz <= 32)
+          hipLaunchKernelGGL(chol_solve_kernel<32>, grid, dim3(256), 0, s, M, bsz, Yp, (int)d);
+        else if (bsz <= 64)
+          hipLaunchKernelGGL(chol_solve_kernel<64>, grid, dim3(256), 0, s, M, bsz, Yp, (int)d);
+        else if (bsz <= 96)
+          hipLaunchKernelGGL(chol_solve_kernel<96>, grid, dim3(256), 0, s, M, bsz, Yp, (int)d);
+        else
+          hipLaunchKernelGGL(chol_solve_kernel<2 * HNTL_MAX_R>, grid, dim3(256), 0, s, M, bsz, Yp, (int)d);
+        HIP_TRY(hipGetLastError());
       }
     };
     cholqr(V);

@@ -54,7 +54,6 @@ __device__ __forceinline__ float gelu_grad(float x) {
 }
 
 // ------------------------------------------------------------------ GEMM
-constexpr int GM = 128, GN = 128, GK = 64, GLD = GK + 8;  // LDS rows padded by 8 bf16
 
 enum { EPI_F32 = 0, EPI_BIAS_GELU = 1, EPI_GELU_GRAD = 2, EPI_BIAS_F32 = 3, EPI_DIST = 4 };
 struct Epi {
@@ -124,241 +123,130 @@ __device__ __forceinline__ void epi_store_t(const Epi& e, int row, int col, floa
   }
 }
 
-// One thread's share of a 128 x 64 tile of X(r, k) (rows r0.., depths k0..):
-// 32 bf16 in four 16-byte words.  XT = false: X(r, k) = X[r * ld + k], the
-// thread holds row t / 2, depths 32 (t % 2) .. + 31; XT = true:
-// X(r, k) = X[k * ld + r], the thread holds depth t / 4, rows 32 (t % 4) .. + 31.
-struct Frag {
-  uint4 v[4];
+// ----------------------------------------------- small-tile GEMM, any orientation
+// C(m, n) = sum_k A(m, k) B(n, k), where XT = false: X(r, k) = X[r * ld + k] (K % 8
+// == 0) and XT = true: X(r, k) = X[k * ld + r] (rows % 8 == 0); ld % 8 == 0 and
+// 16-byte aligned operands in both.  One workgroup of 4 waves per 64 x 64 tile of
+// C, wave w owns a 32 x 32 quarter as 2 x 2 MFMA 16x16x32 tiles: lane (i = lane %
+// 16, kq = lane / 16) feeds depths 8 kq .. 8 kq + 7 of row / column i and holds
+// C[4 kq + j][i] of each.  Bound by latency at the sizes it is for (products that
+// leave 256 x 128 tiles to a fraction of the CUs): four depth tiles of 64 are in
+// flight in registers, two LDS buffers, one barrier per depth tile.  A tile row
+// is 8 vectors of 8 depths; vector c of row r sits at c ^ ((r ^ r / 8) % 8), so
+// neither the 16 rows of an operand read nor the writes of a transposed operand
+// (8 rows apart) share banks.  A transposed operand comes in as 8 rows of two
+// neighbouring depths a thread, which leave as eight 4-byte pairs.
+// Training steps of 512 rows over 768-1024-1024-1024: weight gradients 15 us each,
+// input gradients 17, forward products 11 (49 and 59 on 128 x 128 tiles that stored
+// transposed operands element by element, 36 on 256 x 128 tiles); 256 x 8,192 x 768:
+// 15 us (33 on 256 x 128 tiles).  Tiles are handed to the XCDs in contiguous runs.
+constexpr int SM = 64, SK = 64, SPD = 4;
+
+struct SFrag {
+  uint4 v[2];
 };
 
+// Buffer loads of a depth tile, so that rows and depths past the end (an offset
+// past the record count: zeros) need no branch and tiles in flight can be counted.
 template <bool XT>
-__device__ __forceinline__ void gemm_fetch(Frag& f, const uint16_t* __restrict__ X, int ld, int R, int K, int r0,
-                                           int k0) {
+__device__ __forceinline__ void sfetch(SFrag& f, const uint16_t* __restrict__ X, int ld, int R, int K, int r0, int k0) {
   const int t = threadIdx.x;
-  const int a = XT ? (t >> 2) : (t >> 1);       // depth (XT) or row
-  const int b0 = XT ? (t & 3) * 32 : (t & 1) * 32;  // first row (XT) or depth of the run
+  const uint16_t* base = X + (XT ? (size_t)k0 * ld + r0 : (size_t)r0 * ld + k0);
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base), 0, 0x7FFFFFF0, 0x00027000);
 #pragma unroll
-  for (int h = 0; h < 4; ++h) {
-    const int gr = XT ? r0 + b0 + 8 * h : r0 + a;  // row of element 0 of this word
-    const int gk = XT ? k0 + a : k0 + b0 + 8 * h;  // depth of element 0
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (!XT) {
-      if (gr < R && gk + 8 <= K) {
-        v = *reinterpret_cast<const uint4*>(X + (size_t)gr * ld + gk);
-      } else if (gr < R) {
-        uint16_t e[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) e[u] = gk + u < K ? X[(size_t)gr * ld + gk + u] : 0;
-        memcpy(&v, e, 16);
-      }
-    } else {
-      if (gk < K && gr + 8 <= R) {
-        v = *reinterpret_cast<const uint4*>(X + (size_t)gk * ld + gr);
-      } else if (gk < K) {
-        uint16_t e[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) e[u] = gr + u < R ? X[(size_t)gk * ld + gr + u] : 0;
-        memcpy(&v, e, 16);
-      }
-    }
-    f.v[h] = v;
+  for (int h = 0; h < 2; ++h) {
+    const int r = XT ? 8 * (t & 7) : t >> 2;
+    const int k = XT ? 2 * (t >> 3) + h : 16 * (t & 3) + 8 * h;
+    const uint32_t off = 2u * (XT ? (uint32_t)k * ld + r : (uint32_t)r * ld + k);
+    const auto v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (r0 + r < R && k0 + k < K) ? off : 0xFFFFFFF0u, 0, 0);
+    f.v[h] = make_uint4(v[0], v[1], v[2], v[3]);
   }
 }
 
+__device__ __forceinline__ int svec(int r, int c) { return c ^ ((r ^ (r >> 3)) & 7); }
+
 template <bool XT>
-__device__ __forceinline__ void gemm_store(uint16_t (*S)[GLD], const Frag& f) {
+__device__ __forceinline__ void sstore(uint16_t (*S)[SK], const SFrag& f) {
   const int t = threadIdx.x;
-  if (!XT) {
-    const int r = t >> 1, kk = (t & 1) * 32;
+  if constexpr (!XT) {
+    const int r = t >> 2;
 #pragma unroll
-    for (int h = 0; h < 4; ++h) *reinterpret_cast<uint4*>(&S[r][kk + 8 * h]) = f.v[h];
+    for (int h = 0; h < 2; ++h) *reinterpret_cast<uint4*>(&S[r][8 * svec(r, 2 * (t & 3) + h)]) = f.v[h];
   } else {
-    const int k = t >> 2, rr = (t & 3) * 32;
+    const int kp = t >> 3;
+    const uint32_t lo[4] = {f.v[0].x, f.v[0].y, f.v[0].z, f.v[0].w};
+    const uint32_t hi[4] = {f.v[1].x, f.v[1].y, f.v[1].z, f.v[1].w};
 #pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      uint16_t e[8];
-      memcpy(e, &f.v[h], 16);
-#pragma unroll
-      for (int u = 0; u < 8; ++u) S[rr + 8 * h + u][k] = e[u];
+    for (int u = 0; u < 8; ++u) {
+      const int r = 8 * (t & 7) + u;
+      // depth 2 kp in the low half, 2 kp + 1 in the high half
+      const uint32_t w = u & 1 ? (lo[u / 2] >> 16) | (hi[u / 2] & 0xFFFF0000u) : (lo[u / 2] & 0xFFFFu) | (hi[u / 2] << 16);
+      *reinterpret_cast<uint32_t*>(&S[r][8 * svec(r, kp >> 2) + 2 * (kp & 3)]) = w;
     }
   }
 }
 
-// One workgroup (4 waves) per 128 x 128 tile of C; wave w owns a 64 x 64
-// quarter as 4 x 4 MFMA 16x16 tiles.  Lane (i = lane % 16, kq = lane / 16)
-// feeds depths 8 kq .. 8 kq + 7 of row / column i to each MFMA and holds
-// C[4 kq + j][i] of each 16 x 16 output.  The next depth tile is fetched into
-// registers while the MFMAs of the current one run.  Rows from *mlim on are
-// skipped.
 template <bool AT, bool BT, int EPI>
-__global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint16_t* __restrict__ A, int lda,
-                                                        const uint16_t* __restrict__ B, int ldb, int M, int N, int K,
-                                                        Epi e, const int32_t* __restrict__ mlim) {
-  __shared__ __attribute__((aligned(16))) uint16_t As[GM][GLD];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[GN][GLD];
-  const int lane = lane_id(), wave = threadIdx.x >> 6;
-  const int m0 = blockIdx.y * GM, n0 = blockIdx.x * GN;
-  if (mlim) {
-    const int lim = (int)(*mlim - e.row_base);
-    if (m0 >= lim) return;
-    if (lim < M) M = lim;
-  }
-  const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
-  const int i = lane & 15, kq = lane >> 4;
-  floatx4 acc[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
-  Frag fa, fb;
-  gemm_fetch<AT>(fa, A, lda, M, K, m0, 0);
-  gemm_fetch<BT>(fb, B, ldb, N, K, n0, 0);
-  for (int k0 = 0; k0 < K; k0 += GK) {
-    gemm_store<AT>(As, fa);
-    gemm_store<BT>(Bs, fb);
-    __syncthreads();
-    if (k0 + GK < K) {
-      gemm_fetch<AT>(fa, A, lda, M, K, m0, k0 + GK);
-      gemm_fetch<BT>(fb, B, ldb, N, K, n0, k0 + GK);
-    }
-#pragma unroll
-    for (int ks = 0; ks < GK; ks += 32) {
-      bf16x8 af[4], bfv[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        af[t] = *reinterpret_cast<const bf16x8*>(&As[wm + 16 * t + i][ks + 8 * kq]);
-        bfv[t] = *reinterpret_cast<const bf16x8*>(&Bs[wn + 16 * t + i][ks + 8 * kq]);
-      }
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a], bfv[b], acc[a][b], 0, 0, 0);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int row = m0 + wm + 16 * a + 4 * kq + j;
-        const int col = n0 + wn + 16 * b + i;
-        if (row >= M || col >= N) continue;
-        epi_store<EPI>(e, row, col, acc[a][b][j]);
-      }
-}
-
-// ---------------------------------------------- large-tile GEMM, both k-contiguous
-// C = A B^T with A (M x K) and B (N x K) both row-major (k contiguous, K % 8
-// == 0), the shape of every forward product.  One workgroup of 8 waves per
-// 256 x 128 tile of C; wave w owns rows 64 (w / 2) .. + 63 and columns
-// 64 (w % 2) .. + 63 as 4 x 4 MFMA 16x16x32 tiles.  Depth tiles of 64 go
-// global -> registers -> LDS into two LDS buffers: tile k + 1 loads while
-// tile k feeds the MFMAs, one barrier per depth tile.  Tiles are handed to the
-// 8 XCDs in contiguous runs (workgroup ids go round-robin over the XCDs), so
-// the workgroups of one XCD share A row blocks in their L2.
-constexpr int NM = 256, NN = 128, NK = 64, NLD = NK + 8;
-
-struct NFrag {
-  uint4 a[4];  // A: row t / 2, depths 32 (t % 2) + 8 h
-  uint4 b[2];  // B: row t / 4, depths 16 (t % 4) + 8 h
-};
-
-// 8 consecutive bf16 of row r from depth k (K % 8 == 0: a run is wholly in or out).
-__device__ __forceinline__ uint4 load8(const uint16_t* __restrict__ X, int ld, int R, int K, int r, int k) {
-  uint4 v = make_uint4(0u, 0u, 0u, 0u);
-  if (r < R && k < K) v = *reinterpret_cast<const uint4*>(X + (size_t)r * ld + k);
-  return v;
-}
-
-__device__ __forceinline__ void nfetch(NFrag& f, const uint16_t* __restrict__ A, int lda, int M,
-                                       const uint16_t* __restrict__ B, int ldb, int N, int K, int m0, int n0, int k0) {
-  const int t = threadIdx.x;
-#pragma unroll
-  for (int h = 0; h < 4; ++h) f.a[h] = load8(A, lda, M, K, m0 + (t >> 1), k0 + (t & 1) * 32 + 8 * h);
-#pragma unroll
-  for (int h = 0; h < 2; ++h) f.b[h] = load8(B, ldb, N, K, n0 + (t >> 2), k0 + (t & 3) * 16 + 8 * h);
-}
-
-__device__ __forceinline__ void nstore(uint16_t (*As)[NLD], uint16_t (*Bs)[NLD], const NFrag& f) {
-  const int t = threadIdx.x;
-#pragma unroll
-  for (int h = 0; h < 4; ++h) *reinterpret_cast<uint4*>(&As[t >> 1][(t & 1) * 32 + 8 * h]) = f.a[h];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) *reinterpret_cast<uint4*>(&Bs[t >> 2][(t & 3) * 16 + 8 * h]) = f.b[h];
-}
-
-template <int EPI>
-__global__ __launch_bounds__(512) void gemm_nn_kernel(const uint16_t* __restrict__ A, int lda,
-                                                      const uint16_t* __restrict__ B, int ldb, int M, int N, int K,
-                                                      Epi e, const int32_t* __restrict__ mlim, int tiles_n,
-                                                      int ntiles) {
-  extern __shared__ __attribute__((aligned(16))) uint16_t nsm[];
-  uint16_t(*As0)[NLD] = reinterpret_cast<uint16_t(*)[NLD]>(nsm);
-  uint16_t(*Bs0)[NLD] = reinterpret_cast<uint16_t(*)[NLD]>(nsm + NM * NLD);
-  uint16_t(*As1)[NLD] = reinterpret_cast<uint16_t(*)[NLD]>(nsm + (NM + NN) * NLD);
-  uint16_t(*Bs1)[NLD] = reinterpret_cast<uint16_t(*)[NLD]>(nsm + (2 * NM + NN) * NLD);
-  // XCD-contiguous tile order: workgroup b runs on XCD b % 8
-  const int nb = (int)gridDim.x, per = nb / 8;
-  const int bid = (int)blockIdx.x;
-  const int tile = (nb % 8 == 0) ? (bid % 8) * per + bid / 8 : bid;
+__global__ __launch_bounds__(256) void gemm_small_kernel(const uint16_t* __restrict__ A, int lda,
+                                                         const uint16_t* __restrict__ B, int ldb, int M, int N, int K,
+                                                         Epi e, const int32_t* __restrict__ mlim, int tiles_n,
+                                                         int ntiles) {
+  __shared__ __attribute__((aligned(16))) uint16_t As[2][SM][SK];
+  __shared__ __attribute__((aligned(16))) uint16_t Bs[2][SM][SK];
+  const int tile = (int)(blockIdx.x % 8) * ((int)gridDim.x / 8) + (int)blockIdx.x / 8;  // the grid is a multiple of 8
   if (tile >= ntiles) return;
-  const int m0 = (tile / tiles_n) * NM, n0 = (tile % tiles_n) * NN;
+  const int m0 = (tile / tiles_n) * SM, n0 = (tile % tiles_n) * SM;
   if (mlim) {
     const int lim = (int)(*mlim - e.row_base);
     if (m0 >= lim) return;
     if (lim < M) M = lim;
   }
   const int lane = lane_id(), wave = threadIdx.x >> 6;
-  const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
   const int i = lane & 15, kq = lane >> 4;
-  floatx4 acc[4][4];
+  floatx4 acc[2][2];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const int nk = (K + NK - 1) / NK;
-  auto mma = [&](uint16_t (*As)[NLD], uint16_t (*Bs)[NLD]) {
+    for (int b = 0; b < 2; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+  SFrag fa[SPD], fb[SPD];
 #pragma unroll
-    for (int ks = 0; ks < NK; ks += 32) {
-      bf16x8 af[4], bfv[4];
+  for (int p = 0; p < SPD; ++p) {  // (tiles past K load nothing)
+    sfetch<AT>(fa[p], A, lda, M, K, m0, p * SK);
+    sfetch<BT>(fb[p], B, ldb, N, K, n0, p * SK);
+    __builtin_amdgcn_sched_barrier(0);  // requested in the order of use
+  }
+  for (int k0 = 0; k0 < K; k0 += SPD * SK) {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        af[t] = *reinterpret_cast<const bf16x8*>(&As[wm + 16 * t + i][ks + 8 * kq]);
-        bfv[t] = *reinterpret_cast<const bf16x8*>(&Bs[wn + 16 * t + i][ks + 8 * kq]);
+    for (int p = 0; p < SPD; ++p) {
+      if (k0 + p * SK >= K) break;
+      // the buffer written here was last read two depth tiles ago, which the barrier between closed
+      sstore<AT>(As[p & 1], fa[p]);
+      sstore<BT>(Bs[p & 1], fb[p]);
+      __syncthreads();
+      sfetch<AT>(fa[p], A, lda, M, K, m0, k0 + (p + SPD) * SK);
+      sfetch<BT>(fb[p], B, ldb, N, K, n0, k0 + (p + SPD) * SK);
+#pragma unroll
+      for (int ks = 0; ks < SK; ks += 32) {
+        bf16x8 af[2], bfv[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const int ra = wm + 16 * t + i, rb = wn + 16 * t + i;
+          af[t] = *reinterpret_cast<const bf16x8*>(&As[p & 1][ra][8 * svec(ra, ks / 8 + kq)]);
+          bfv[t] = *reinterpret_cast<const bf16x8*>(&Bs[p & 1][rb][8 * svec(rb, ks / 8 + kq)]);
+        }
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int b = 0; b < 2; ++b)
+            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a], bfv[b], acc[a][b], 0, 0, 0);
       }
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a], bfv[b], acc[a][b], 0, 0, 0);
     }
-  };
-  NFrag f;
-  nfetch(f, A, lda, M, B, ldb, N, K, m0, n0, 0);
-  nstore(As0, Bs0, f);
-  __syncthreads();
-  // LDS buffer k % 2 holds depth tile k while tile k + 1 loads into registers;
-  // the buffer written in a step was last read in the step before, which the
-  // barrier closed
-  for (int k = 0; k < nk; k += 2) {
-    if (k + 1 < nk) nfetch(f, A, lda, M, B, ldb, N, K, m0, n0, (k + 1) * NK);
-    mma(As0, Bs0);
-    if (k + 1 < nk) nstore(As1, Bs1, f);
-    __syncthreads();
-    if (k + 1 >= nk) break;
-    if (k + 2 < nk) nfetch(f, A, lda, M, B, ldb, N, K, m0, n0, (k + 2) * NK);
-    mma(As1, Bs1);
-    if (k + 2 < nk) nstore(As0, Bs0, f);
-    __syncthreads();
   }
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int row = m0 + wm + 16 * a + 4 * kq + j;
@@ -366,10 +254,9 @@ __global__ __launch_bounds__(512) void gemm_nn_kernel(const uint16_t* __restrict
         if (row < M && col < N) epi_store<EPI>(e, row, col, acc[a][b][j]);
       }
 }
-constexpr size_t NN_LDS = (size_t)2 * (NM + NN) * NLD * sizeof(uint16_t);
 
 // ------------------------------- 256 x 256 tiles, LDS filled by direct loads
-// The same product as gemm_nn_kernel (both operands k-contiguous) for large
+// The same product as gemm_small_kernel<false, false> for large
 // shapes with K % 64 == 0.  One workgroup of 8 waves (two per SIMD) per
 // 256 x 256 tile of C; wave w owns rows 128 (w / 4) .. + 127 and columns
 // 64 (w % 4) .. + 63 as 8 x 4 MFMA 16x16x32 tiles.  Depth tiles of 64 go from
@@ -381,11 +268,11 @@ constexpr size_t NN_LDS = (size_t)2 * (NM + NN) * NLD * sizeof(uint16_t);
 // position c ^ (r % 8) of the row (an XOR swizzle), so the 16 rows read by
 // one ds_read_b128 of an MFMA fragment spread over the LDS banks.  Rows past M
 // or N load a valid clamped row (their results are never stored).  Every
-// output element is accumulated in the same order as in gemm_nn_kernel (depth
+// output element is accumulated in the same order as in gemm_small_kernel (depth
 // tiles of 64, MFMA steps of 32), so the kernels give identical results.
 constexpr int BM = 256, BN = 256;
 constexpr int BIG_GROUP = 4;  // row blocks per tile group
-constexpr size_t DL_STAGE = (size_t)(BM + BN) * NK * sizeof(uint16_t);  // 64 KiB
+constexpr size_t DL_STAGE = (size_t)(BM + BN) * SK * sizeof(uint16_t);  // 64 KiB
 constexpr size_t BIG_LDS = 2 * DL_STAGE;
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
@@ -442,23 +329,23 @@ __global__ __launch_bounds__(512) void gemm_big_kernel(const uint16_t* __restric
   for (int a = 0; a < 8; ++a)
 #pragma unroll
     for (int b = 0; b < 4; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const int nk = K / NK;
+  const int nk = K / SK;
   uint16_t* const st0 = dsm;
   uint16_t* const st1 = dsm + DL_STAGE / sizeof(uint16_t);
   dl_fetch(st0, A, lda, M, m0, 0);
-  dl_fetch(st0 + BM * NK, B, ldb, N, n0, 0);
+  dl_fetch(st0 + BM * SK, B, ldb, N, n0, 0);
   for (int k = 0; k < nk; ++k) {
     __builtin_amdgcn_s_waitcnt(0);  // this wave's requests for tile k have landed
     __syncthreads();                // every wave's have, and every wave is done with tile k - 1
     if (k + 1 < nk) {               // the other buffer (last read for tile k - 1) takes tile k + 1
       uint16_t* nx = (k & 1) ? st0 : st1;
-      dl_fetch(nx, A, lda, M, m0, (k + 1) * NK);
-      dl_fetch(nx + BM * NK, B, ldb, N, n0, (k + 1) * NK);
+      dl_fetch(nx, A, lda, M, m0, (k + 1) * SK);
+      dl_fetch(nx + BM * SK, B, ldb, N, n0, (k + 1) * SK);
     }
     const uint16_t* As = (k & 1) ? st1 : st0;
-    const uint16_t* Bs = As + BM * NK;
+    const uint16_t* Bs = As + BM * SK;
 #pragma unroll
-    for (int ks = 0; ks < NK; ks += 32) {
+    for (int ks = 0; ks < SK; ks += 32) {
       const int kc = (ks >> 3) + kq;
       bf16x8 bfv[4];
 #pragma unroll
@@ -490,49 +377,43 @@ __global__ __launch_bounds__(512) void gemm_big_kernel(const uint16_t* __restric
       }
     }
 }
-constexpr int BIG_MIN_ROWS = 512;  // fewer rows: the 256 x 128 tiles keep more workgroups busy
-constexpr int64_t BIG_MIN_TILES = 256;  // fewer 256 x 256 tiles than CUs: the 256 x 128 tiles
+// 256 x 256 tiles once every CU gets one.  Three products of n rows over
+// 768-1024-1024-8192: n = 16,384 524 us against 887 on 64 x 64 tiles, 8,192 328
+// against 487 (the first two products on 64 x 64 in both); over 768-1024-1024-1024:
+// n = 16,384 (256 tiles each) 239 against 258.  Below, 256 x 128 tiles (double
+// buffered through registers) lost to 64 x 64 at every size: 10,000 rows 262 against
+// 171 us, 8,192 x 8,192 412 against 333, 256 x 8,192 33 against 15.
+constexpr int64_t BIG_MIN_TILES = 256;
 
 template <bool AT, bool BT, int EPI>
 void gemm(const uint16_t* A, int lda, const uint16_t* B, int ldb, int M, int N, int K, const Epi& e, hipStream_t s,
           const int32_t* mlim = nullptr) {
   if (M <= 0 || N <= 0) return;
+  // rows of whole 16-byte words (the widths of a router and of split-BF16 routing are multiples of 8)
+  if ((lda % 8) != 0 || (ldb % 8) != 0 || lda >= (1 << 23) || ldb >= (1 << 23) || ((uintptr_t)A % 16) != 0 ||
+      ((uintptr_t)B % 16) != 0 || ((AT ? M : K) % 8) != 0 || ((BT ? N : K) % 8) != 0)
+    throw ArgError{HNTL_EUNSUPPORTED, "BF16 products need 16-byte aligned rows"};
+  auto tiles = [&](int tm, int tn) { return (int64_t)((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
+  auto lds = [](const void* kernel, size_t bytes, bool& set) {  // more than 64 KiB of dynamic LDS
+    if (set) return;
+    HIP_TRY(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+    set = true;
+  };
+  // grids are multiples of 8 for the XCD-contiguous order
   if constexpr (!AT && !BT) {
-    if ((K % 8) == 0 && (lda % 8) == 0 && (ldb % 8) == 0 && ((uintptr_t)A % 16) == 0 && ((uintptr_t)B % 16) == 0 &&
-        M >= BIG_MIN_ROWS && N >= BN && (K % NK) == 0 &&
-        (int64_t)((M + BM - 1) / BM) * ((N + BN - 1) / BN) >= BIG_MIN_TILES) {
-      const int tn = (N + BN - 1) / BN, tm = (M + BM - 1) / BM;
-      const int nt = tn * tm;
-      const int grid = (nt + 7) / 8 * 8;  // a multiple of 8 for the XCD-contiguous order
-      static bool lds_set = false;        // more than 64 KiB of dynamic LDS
-      if (!lds_set) {
-        HIP_TRY(hipFuncSetAttribute((const void*)gemm_big_kernel<EPI>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)BIG_LDS));
-        lds_set = true;
-      }
-      hipLaunchKernelGGL((gemm_big_kernel<EPI>), dim3((unsigned)grid), dim3(512), BIG_LDS, s, A, lda, B, ldb, M, N, K,
-                         e, mlim, tn, nt);
-      HIP_TRY(hipGetLastError());
-      return;
-    }
-    if ((K % 8) == 0 && (lda % 8) == 0 && (ldb % 8) == 0 && ((uintptr_t)A % 16) == 0 && ((uintptr_t)B % 16) == 0) {
-      const int tn = (N + NN - 1) / NN, tm = (M + NM - 1) / NM;
-      const int nt = tn * tm;
-      const int grid = (nt + 7) / 8 * 8;  // a multiple of 8 for the XCD-contiguous order
-      static bool lds_set = false;        // more than 64 KiB of dynamic LDS
-      if (!lds_set) {
-        HIP_TRY(hipFuncSetAttribute((const void*)gemm_nn_kernel<EPI>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)NN_LDS));
-        lds_set = true;
-      }
-      hipLaunchKernelGGL((gemm_nn_kernel<EPI>), dim3((unsigned)grid), dim3(512), NN_LDS, s, A, lda, B, ldb, M, N, K, e,
-                         mlim, tn, nt);
+    if ((K % SK) == 0 && tiles(BM, BN) >= BIG_MIN_TILES) {
+      static bool set = false;
+      lds((const void*)gemm_big_kernel<EPI>, BIG_LDS, set);
+      const int nt = (int)tiles(BM, BN);
+      hipLaunchKernelGGL((gemm_big_kernel<EPI>), dim3((unsigned)((nt + 7) / 8 * 8)), dim3(512), BIG_LDS, s, A, lda, B,
+                         ldb, M, N, K, e, mlim, (N + BN - 1) / BN, nt);
       HIP_TRY(hipGetLastError());
       return;
     }
   }
-  const dim3 grid((unsigned)((N + GN - 1) / GN), (unsigned)((M + GM - 1) / GM));
-  hipLaunchKernelGGL((gemm_bf16_kernel<AT, BT, EPI>), grid, dim3(256), 0, s, A, lda, B, ldb, M, N, K, e, mlim);
+  const int nt = (int)tiles(SM, SM);
+  hipLaunchKernelGGL((gemm_small_kernel<AT, BT, EPI>), dim3((unsigned)((nt + 7) / 8 * 8)), dim3(256), 0, s, A, lda, B,
+                     ldb, M, N, K, e, mlim, (N + SM - 1) / SM, nt);
   HIP_TRY(hipGetLastError());
 }
 

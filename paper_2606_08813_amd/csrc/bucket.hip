@@ -342,12 +342,6 @@ __global__ void fill_i32_kernel(int32_t* __restrict__ p, int64_t n, int32_t v) {
   if (i < n) p[i] = v;
 }
 
-__global__ void fill_multi_kernel(FillList L) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  for (int k = 0; k < L.n; ++k)
-    if (i < L.seg[k].n) L.seg[k].p[i] = L.seg[k].v;
-}
-
 }  // namespace
 
 // Fill with a kernel rather than hipMemsetAsync, so that captured graphs hold
@@ -355,14 +349,6 @@ __global__ void fill_multi_kernel(FillList L) {
 void launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s) {
   if (n <= 0) return;
   hipLaunchKernelGGL(fill_i32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n, v);
-  HIP_TRY(hipGetLastError());
-}
-
-void launch_fill_multi(const FillList& L, hipStream_t s) {
-  int64_t n = 0;
-  for (int k = 0; k < L.n; ++k) n = std::max<int64_t>(n, L.seg[k].n);
-  if (n <= 0) return;
-  hipLaunchKernelGGL(fill_multi_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, L);
   HIP_TRY(hipGetLastError());
 }
 

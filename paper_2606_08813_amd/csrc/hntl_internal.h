@@ -157,6 +157,7 @@ void launch_row_norms(const float* A, int64_t rows, int d, float* out, hipStream
 // <a, mu> from BF16 MFMA over [a_hi | a_hi | a_lo] . [mu_hi | mu_lo | mu_hi]; As is
 // scratch of rows x 3d bf16.  ensure_centroid_split makes the index's centroid split once.
 // launch_dist_bf16: the same with <a, mu> = bf16(a) . bf16(mu) (As: rows x d bf16).
+// A == null: As holds the rows' operands already.
 void ensure_centroid_split(Index& ix, hipStream_t s);
 void launch_dist_bf16x3(const Index& ix, const float* A, const float* an, int64_t rows, uint16_t* As, float* D,
                         hipStream_t s, const int32_t* nlim = nullptr, int64_t row_base = 0);
@@ -178,6 +179,12 @@ void launch_topk_rows(const float* D, int64_t rows, int cols, int P, int32_t* id
                       const float* bn = nullptr, const float* bmax = nullptr, int d = 0, float err = 0.f, const int32_t* nlim = nullptr,
                       int64_t row_base = 0, unsigned int* overflow = nullptr, float2* znorm = nullptr);
 
+// The caller's result buffers of a plan's run (null: none), kept on the device.
+struct PlanOut {
+  int32_t* ids;
+  float* dist;
+};
+
 // Centroid routing (Section 2.1 step 1): the P nearest centroids of every row
 // of Q by FP32 direct differences, from a shortlist of expansion distances
 // whose products run on MFMA in one of three forms.
@@ -194,9 +201,10 @@ float route_err(int form);
 inline int route_form(uint32_t flags) {
   return (flags & HNTL_FLAG_ROUTE_BF16X3) ? ROUTE_BF16X3 : (flags & HNTL_FLAG_ROUTE_BF16) ? ROUTE_BF16 : ROUTE_F32;
 }
+// prepared: what of Q's norms and BF16 operands is in w already (PREP_*; -1: nothing)
 void launch_route_centroid(const Index& ix, const float* Q, int64_t nq, int P, const RouteScratch& w,
                            int32_t* probes, float* pdist, hipStream_t s, const int32_t* nlim = nullptr,
-                           unsigned int* overflow = nullptr);
+                           unsigned int* overflow = nullptr, int prepared = -1);
 
 // exact k nearest rows of B (cols x d) for every row of A (rows x d), k <= 16:
 // MFMA expansion shortlist of 32 per row, re-scored by direct differences
@@ -265,7 +273,7 @@ inline int64_t bucket_counters(int64_t G) { return (2 * G + 3) / 4 * 4; }
 // counts_zeroed: b.cnt holds zeros (larger batches fill it first otherwise).
 void launch_bucket(const int32_t* probes, int64_t nq, int P, const Buckets& b, hipStream_t s,
                    bool counts_zeroed = false);
-// up to 8 fills in one launch (graph-friendly resets)
+// up to 8 fills, done by the kernel that begins a plan's run
 struct FillSeg {
   int32_t* p;
   int64_t n;
@@ -275,7 +283,25 @@ struct FillList {
   FillSeg seg[8];
   int n;
 };
-void launch_fill_multi(const FillList& L, hipStream_t s);
+// Start of a plan's run, one pass over its nq queries: copies them from src to Q
+// (not if they are the same), forms what routing reads of them, resets counters
+// and stores the batch size and the caller's result buffers (null: none).
+enum { PREP_NORMS = 0, PREP_BF16 = 1, PREP_BF16X3 = 2, PREP_STANDARDIZE = 3 };
+struct PlanBegin {
+  const float* src;
+  float* Q;
+  int64_t nq;
+  int d;
+  int prep;          // norms (PREP_NORMS, PREP_BF16*) in qn, BF16 operands in out
+  float* qn;
+  uint16_t* out;
+  const float *mean, *stdv;
+  FillList fill;
+  int32_t* nq_dev;
+  PlanOut* out_dev;
+  PlanOut results;
+};
+void launch_plan_begin(const PlanBegin& b, hipStream_t s);
 void launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
 
 constexpr int PROJECT_TILE = 64;  // pairs per workgroup of the shared-basis projection kernel
@@ -333,7 +359,7 @@ void launch_merge_rerank(const Index& ix, const float* Q, int64_t nq, int P, int
                          float* pool_D_out, int32_t* ids, float* dist, hipStream_t s,
                          const int32_t* lbase = nullptr, const int32_t* nsplit = nullptr,
                          const float* eps_id = nullptr,
-                         const int32_t* nlim = nullptr);  // rows from *nlim on: -1 / +inf only
+                         const int32_t* nlim = nullptr, const PlanOut* out_dev = nullptr);  // rows from *nlim on: -1 / +inf only
 
 // Persistent fused project-scan-select kernel (the batching form).  Its
 // waves take work items from one device ticket counter, in three runs:
@@ -387,7 +413,7 @@ struct FusedArgs {
 // which the cumulative softmax probability reaches mass (later slots: -1).
 void launch_route_learned(const Index& ix, const float* Q, int64_t nq, int P, float tau, int32_t* probes,
                           float* pdist, const RouterScratch& w, hipStream_t s, const int32_t* nlim = nullptr,
-                          float mass = 0.f);
+                          float mass = 0.f, bool prepared = false);
 
 // build helpers
 void launch_pack_codes(const Index& ix, const float* codes_go, const float* eps_go, hipStream_t s);

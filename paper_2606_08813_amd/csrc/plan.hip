@@ -48,10 +48,6 @@ int fused_resident_ct3(int, int, int, int);
 
 namespace {
 
-__global__ void set_count_kernel(int32_t* __restrict__ p, int32_t v) {
-  if (threadIdx.x == 0) *p = v;
-}
-
 bool fused_launch(int codes, const FusedArgs* a, int rp, int C, int qt, int nw, int grid, hipStream_t s) {
   switch (codes) {
     case HNTL_CODES_FP32: return launch_fused_ct0(a, rp, C, qt, nw, grid, s);
@@ -154,6 +150,7 @@ struct Plan {
   int32_t* ids = nullptr;
   float* dist = nullptr;
   int32_t* nq_dev = nullptr;
+  PlanOut* out_dev = nullptr;       // the running call's result buffers
   // routing
   int32_t* probes = nullptr;
   RouteScratch route;
@@ -207,6 +204,7 @@ struct Plan {
     ids = L.take<int32_t>((size_t)max_nq * sp.k);
     dist = L.take<float>((size_t)max_nq * sp.k);
     nq_dev = L.take<int32_t>(1);
+    out_dev = L.take<PlanOut>(1);
     probes = L.take<int32_t>(np);
     if (sp.route != HNTL_ROUTE_LEARNED) {
       const int form = route_form(sp.flags);
@@ -307,27 +305,53 @@ struct Plan {
     return a;
   }
 
-  // The launch sequence of one run (batch size already in nq_dev).  With
-  // `ev` (6 events) the stage boundaries are recorded: route, bucketing,
+  // What routing reads of the queries beside the rows themselves, formed at the start of a run.
+  int prep() const {
+    if (sp.route == HNTL_ROUTE_LEARNED) return PREP_STANDARDIZE;
+    // BF16 operands where one block of distances takes them all (up to 16 rows are
+    // routed by direct differences)
+    if (route.form == ROUTE_F32 || max_nq <= 16 || route.chunk < (int64_t)max_nq) return PREP_NORMS;
+    return route.form == ROUTE_BF16X3 ? PREP_BF16X3 : PREP_BF16;
+  }
+
+  // Start of a run over the nq rows at src (Q: in place), results also to `results`.
+  // Outside the graph: its grid and pointers are the call's.
+  void begin(const float* src, uint32_t nq, const PlanOut& results, hipStream_t s) {
+    PlanBegin g{};
+    g.src = src;
+    g.Q = Q;
+    g.nq = nq;
+    g.d = (int)ix->d;
+    g.prep = prep();
+    const bool learned = sp.route == HNTL_ROUTE_LEARNED;
+    g.qn = learned ? nullptr : route.qn;
+    g.out = learned ? rs.xh : route.As;
+    g.mean = learned ? ix->router->mean : nullptr;
+    g.stdv = learned ? ix->router->stdv : nullptr;
+    g.fill.seg[0] = FillSeg{ticket, 2 * TICKET_INTS, 0};
+    g.fill.seg[1] = FillSeg{reinterpret_cast<int32_t*>(scored), 2, 0};
+    g.fill.seg[2] = FillSeg{proj_done, proj_items, 0};
+    g.fill.seg[3] = FillSeg{reinterpret_cast<int32_t*>(qbound), (int64_t)max_nq, -1};
+    g.fill.seg[4] = FillSeg{b.cnt, 2 * bucket_counters(ix->G), 0};
+    g.fill.n = 5;
+    g.nq_dev = nq_dev;
+    g.out_dev = out_dev;
+    g.results = results;
+    launch_plan_begin(g, s);
+  }
+
+  // The launch sequence of one run after begin().  With `ev` (6 events, the first
+  // recorded before begin()) the stage boundaries are recorded: route, bucketing,
   // separate projection launch (empty with proj = 0), fused kernel, merge +
   // rerank.
   void enqueue(hipStream_t s, hipEvent_t* ev = nullptr) {
     const Index& x = *ix;
     const int P = (int)sp.P;
-    if (ev) HIP_TRY(hipEventRecord(ev[0], s));
-    FillList f{};
-    f.seg[0] = FillSeg{ticket, 2 * TICKET_INTS, 0};
-    f.seg[1] = FillSeg{reinterpret_cast<int32_t*>(scored), 2, 0};
-    f.seg[2] = FillSeg{proj_done, proj_items, 0};
-    f.seg[3] = FillSeg{reinterpret_cast<int32_t*>(qbound), (int64_t)max_nq, -1};
-    f.seg[4] = FillSeg{b.cnt, 2 * bucket_counters(x.G), 0};
-    f.n = 5;
-    launch_fill_multi(f, s);
     // routing reads the batch size from nq_dev: rows past it get probes -1
     if (sp.route == HNTL_ROUTE_LEARNED)
-      launch_route_learned(x, Q, max_nq, P, sp.tau, probes, nullptr, rs, s, nq_dev, sp.mass);
+      launch_route_learned(x, Q, max_nq, P, sp.tau, probes, nullptr, rs, s, nq_dev, sp.mass, true);
     else
-      launch_route_centroid(x, Q, max_nq, P, route, probes, pdist, s, nq_dev);
+      launch_route_centroid(x, Q, max_nq, P, route, probes, pdist, s, nq_dev, nullptr, prep());
     if (ev) HIP_TRY(hipEventRecord(ev[1], s));
     const bool bf16 = (sp.flags & HNTL_FLAG_PROJECT_BF16) != 0;
     auto fused = [&](int args) {
@@ -355,7 +379,7 @@ struct Plan {
     if (ev) HIP_TRY(hipEventRecord(ev[3], s));
     if (prune) {
       fused(0);
-      launch_prune_pairs(x, (int)sp.codes, Q, 
+      launch_prune_pairs(x, (int)sp.codes, Q,
                          PruneArgs{probes, kept, (int64_t)max_nq, P, (int)sp.C, pdist, qbound, nullptr, need}, s);
       pass.pick = PICK_LATER;
       pass.lists_to = nullptr;
@@ -369,13 +393,12 @@ struct Plan {
     }
     if (ev) HIP_TRY(hipEventRecord(ev[4], s));
     launch_merge_rerank(x, Q, max_nq, P, (int)sp.C, (int)sp.k, kept, part, nullptr, nullptr, nullptr, ids, dist, s,
-                        b.lbase, nsplit, (sp.flags & HNTL_FLAG_MODE_A) ? x.eps_id : nullptr, nq_dev);
+                        b.lbase, nsplit, (sp.flags & HNTL_FLAG_MODE_A) ? x.eps_id : nullptr, nq_dev, out_dev);
     if (ev) HIP_TRY(hipEventRecord(ev[5], s));
   }
 
-  void run(uint32_t nq, hipStream_t s) {
-    hipLaunchKernelGGL(set_count_kernel, dim3(1), dim3(64), 0, s, nq_dev, (int32_t)nq);
-    HIP_TRY(hipGetLastError());
+  void run(const float* src, uint32_t nq, const PlanOut& results, hipStream_t s) {
+    begin(src, nq, results, s);
     if (!execs.empty())
       HIP_TRY(hipGraphLaunch(execs[0], s));
     else
@@ -618,7 +641,7 @@ hntl_status hntl_plan_run(hntl_plan* plan, uint32_t nq, void* stream) {
   return guarded_call([&] {
     HIP_TRY(hipSetDevice(pl.device));
     hipStream_t s = (hipStream_t)stream;
-    pl.run(nq, s);
+    pl.run(pl.Q, nq, PlanOut{nullptr, nullptr}, s);
     if (pl.sp.flags & HNTL_FLAG_SYNC) {
       HIP_TRY(hipStreamSynchronize(s));
       HIP_TRY(hipGetLastError());
@@ -639,14 +662,7 @@ hntl_status hntl_plan_search(hntl_plan* plan, const float* Q, uint32_t nq, int32
   return guarded_call([&] {
     HIP_TRY(hipSetDevice(pl.device));
     hipStream_t s = (hipStream_t)stream;
-    const Index& ix = *pl.ix;
-    if (Q != pl.Q)
-      HIP_TRY(hipMemcpyAsync(pl.Q, Q, sizeof(float) * (size_t)nq * ix.d, hipMemcpyDeviceToDevice, s));
-    pl.run(nq, s);
-    if (ids != pl.ids)
-      HIP_TRY(hipMemcpyAsync(ids, pl.ids, sizeof(int32_t) * (size_t)nq * pl.sp.k, hipMemcpyDeviceToDevice, s));
-    if (dist != pl.dist)
-      HIP_TRY(hipMemcpyAsync(dist, pl.dist, sizeof(float) * (size_t)nq * pl.sp.k, hipMemcpyDeviceToDevice, s));
+    pl.run(Q, nq, PlanOut{ids != pl.ids ? ids : nullptr, dist != pl.dist ? dist : nullptr}, s);
     if (pl.sp.flags & HNTL_FLAG_SYNC) {
       HIP_TRY(hipStreamSynchronize(s));
       HIP_TRY(hipGetLastError());
@@ -689,7 +705,8 @@ hntl_status hntl_plan_profile(hntl_plan* plan, uint32_t nq, uint32_t reps, doubl
     unsigned long long sc = 0;
     try {
       for (uint32_t rep = 0; rep < reps; ++rep) {
-        hipLaunchKernelGGL(set_count_kernel, dim3(1), dim3(64), 0, s, pl.nq_dev, (int32_t)nq);
+        HIP_TRY(hipEventRecord(ev[0], s));
+        pl.begin(pl.Q, nq, PlanOut{nullptr, nullptr}, s);
         pl.enqueue(s, ev);
         HIP_TRY(hipEventSynchronize(ev[PLAN_STAGES]));
         for (int i = 0; i < PLAN_STAGES; ++i) {
@@ -754,12 +771,11 @@ hntl_status hntl_tune(hntl_index* index, const hntl_search_params* sp, const flo
             }
             throw;
           }
-          HIP_TRY(hipMemcpyAsync(pl->Q, Q, sizeof(float) * (size_t)nq * ix.d, hipMemcpyDeviceToDevice, s));
-          pl->run(nq, s);  // warm-up
+          pl->run(Q, nq, PlanOut{nullptr, nullptr}, s);  // warm-up
           std::vector<float> t;
           for (int rep = 0; rep < 5; ++rep) {
             HIP_TRY(hipEventRecord(e0, s));
-            pl->run(nq, s);
+            pl->run(pl->Q, nq, PlanOut{nullptr, nullptr}, s);
             HIP_TRY(hipEventRecord(e1, s));
             HIP_TRY(hipEventSynchronize(e1));
             float ms = 0.f;

@@ -29,7 +29,8 @@ __global__ __launch_bounds__(256) void merge_rerank_kernel(const float* __restri
                                                            const int32_t* __restrict__ lbase,
                                                            const int32_t* __restrict__ nsplit,
                                                            const float* __restrict__ eps_id, int64_t nrows,
-                                                           const int32_t* __restrict__ nlim) {
+                                                           const int32_t* __restrict__ nlim,
+                                                           const PlanOut* __restrict__ out_dev) {
   __shared__ uint64_t lst[2 * CAP];
   __shared__ int32_t pool[CAP];
   __shared__ float delta[CAP];
@@ -182,6 +183,16 @@ __global__ __launch_bounds__(256) void merge_rerank_kernel(const float* __restri
   }
   __syncthreads();
 
+  // results go to the call's buffers and, in a plan's run, to those the caller named
+  const PlanOut user = out_dev ? *out_dev : PlanOut{nullptr, nullptr};
+  auto store = [&](int j, uint64_t key) {
+    const int32_t id = key == KEY_NONE ? -1 : (int32_t)key_id(key);
+    const float dd = key == KEY_NONE ? __builtin_inff() : key_dist(key);
+    ids[q * k + j] = id;
+    dist[q * k + j] = dd;
+    if (user.ids) user.ids[q * k + j] = id;
+    if (user.dist) user.dist[q * k + j] = dd;
+  };
   if constexpr (CAP == 64) {
     if (wave == 0) {
       // top k of at most 64 exact distances: one bitonic sort across the lanes
@@ -189,8 +200,7 @@ __global__ __launch_bounds__(256) void merge_rerank_kernel(const float* __restri
       uint64_t key = ok ? make_key(delta[lane], (uint32_t)pool[lane]) : KEY_NONE;
       key = wave_sort64(key);
       if (lane < k) {
-        ids[q * k + lane] = key == KEY_NONE ? -1 : (int32_t)key_id(key);
-        dist[q * k + lane] = key == KEY_NONE ? __builtin_inff() : key_dist(key);
+        store(lane, key);
       }
     }
   } else if (wave == 0) {
@@ -208,8 +218,7 @@ __global__ __launch_bounds__(256) void merge_rerank_kernel(const float* __restri
       const int j = rr * 64 + lane;
       if (j >= k) continue;
       const uint64_t key = L.best[rr];
-      ids[q * k + j] = key == KEY_NONE ? -1 : (int32_t)key_id(key);
-      dist[q * k + j] = key == KEY_NONE ? __builtin_inff() : key_dist(key);
+      store(j, key);
     }
   }
 }
@@ -239,7 +248,7 @@ void launch_merge_rerank(const Index& ix, const float* Q, int64_t nq, int P, int
                          const uint64_t* part,
                          const int32_t* pool_in, int32_t* pool_out, float* pool_D_out, int32_t* ids, float* dist,
                          hipStream_t s, const int32_t* lbase, const int32_t* nsplit, const float* eps_id,
-                         const int32_t* nlim) {
+                         const int32_t* nlim, const PlanOut* out_dev) {
   if (nq <= 0) return;
   if (eps_id && pool_in) throw ArgError{HNTL_EUNSUPPORTED, "Mode A answers need the merged pool, not an injected one"};
   if (!eps_id && !ix.X) throw ArgError{HNTL_ESTATE, "this index holds no raw vectors: only Mode A searches"};
@@ -251,7 +260,7 @@ void launch_merge_rerank(const Index& ix, const float* Q, int64_t nq, int P, int
 #define HNTL_MR(CAPV, RRV, JUV)                                                                                  \
   hipLaunchKernelGGL((merge_rerank_kernel<CAPV, RRV, JUV, true>), grid, dim3(256), 0, s, Q, (int)ix.d, P, C, k,      \
                      (int)ix.G, (int64_t)ix.N, probes, part, pool_in, ix.X, pool_out, pool_D_out, ids, dist, vec4,   \
-                     lbase, nsplit, eps_id, nq, nlim)
+                     lbase, nsplit, eps_id, nq, nlim, out_dev)
   const bool narrow = ix.d <= 4 * HNTL_WAVE;
   if (cap == 64) {
     if (narrow)

@@ -768,8 +768,78 @@ __global__ void split3_kernel(const float* __restrict__ X, int64_t rows, int d, 
   o[d + k] = corder ? l : h;
   o[2 * d + k] = corder ? h : l;
 }
+
+// One wave per query row (d % 4 == 0), up to 1024 values of it in flight.  Bound by
+// memory: the row is read once and its copy and operands written.  16,384 x 768
+// with BF16 operands 26 us; copy, norms, conversion, batch size and counters in
+// a launch each took 62.
+__global__ __launch_bounds__(256) void plan_begin_kernel(PlanBegin b, bool vec4) {
+  const int lane = lane_id();
+  const int64_t tid = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (tid == 0) {
+    *b.nq_dev = (int32_t)b.nq;
+    *b.out_dev = b.results;
+  }
+  for (int k = 0; k < b.fill.n; ++k)
+    for (int64_t i = tid; i < b.fill.seg[k].n; i += (int64_t)gridDim.x * 256) b.fill.seg[k].p[i] = b.fill.seg[k].v;
+  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= b.nq) return;
+  const int d = b.d, w = b.prep == PREP_BF16X3 ? 3 : 1;
+  const float* src = b.src + row * d;
+  float* dst = b.Q + row * d;
+  uint16_t* o = b.out + (size_t)row * w * d;
+  float acc = 0.f;
+  constexpr int U = 4;
+  for (int j0 = 4 * lane; j0 < d; j0 += U * 256) {
+    float4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = j0 + 256 * u;
+      v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (j < d)
+        v[u] = vec4 ? *reinterpret_cast<const float4*>(src + j)
+                    : make_float4(src[j], src[j + 1], src[j + 2], src[j + 3]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = j0 + 256 * u;
+      if (j >= d) continue;
+      if (src != dst) *reinterpret_cast<float4*>(dst + j) = v[u];
+      float x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc = fmaf(x[c], x[c], acc);
+      if (b.prep == PREP_NORMS) continue;
+      ushort4 h, l;
+      if (b.prep == PREP_STANDARDIZE) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) x[c] = (x[c] - b.mean[j + c]) / b.stdv[j + c];
+      }
+      h = make_ushort4(to_bf16(x[0]), to_bf16(x[1]), to_bf16(x[2]), to_bf16(x[3]));
+      *reinterpret_cast<ushort4*>(o + j) = h;
+      if (b.prep != PREP_BF16X3) continue;
+      auto low = [](float y, uint16_t hi) { return to_bf16(y - __uint_as_float((uint32_t)hi << 16)); };
+      l = make_ushort4(low(x[0], h.x), low(x[1], h.y), low(x[2], h.z), low(x[3], h.w));
+      *reinterpret_cast<ushort4*>(o + d + j) = h;
+      *reinterpret_cast<ushort4*>(o + 2 * d + j) = l;
+    }
+  }
+  if (b.prep != PREP_STANDARDIZE) {
+    acc = wave_sum(acc);
+    if (lane == 0) b.qn[row] = acc;
+  }
+}
 std::mutex g_split_mu;
 }  // namespace
+
+void launch_plan_begin(const PlanBegin& b, hipStream_t s) {
+  if (b.d % 4 != 0) throw ArgError{HNTL_EUNSUPPORTED, "plans need d % 4 == 0"};
+  int64_t fill = 0;
+  for (int k = 0; k < b.fill.n; ++k) fill = std::max<int64_t>(fill, b.fill.seg[k].n);
+  // a workgroup per four rows, or for each 1,024 counters of a small batch
+  const int64_t grid = std::max<int64_t>(std::max<int64_t>((b.nq + 3) / 4, (fill + 1023) / 1024), 1);
+  hipLaunchKernelGGL(plan_begin_kernel, dim3((unsigned)grid), dim3(256), 0, s, b, (uintptr_t)b.src % 16 == 0);
+  HIP_TRY(hipGetLastError());
+}
 
 void ensure_centroid_split(Index& ix, hipStream_t s) {
   std::lock_guard<std::mutex> lk(g_split_mu);
@@ -787,9 +857,11 @@ void launch_dist_bf16x3(const Index& ix, const float* A, const float* an, int64_
                         hipStream_t s, const int32_t* nlim, int64_t row_base) {
   if (rows <= 0) return;
   if (!ix.cent_split) throw ArgError{HNTL_ESTATE, "split-BF16 routing: centroid split not built"};
-  const int64_t n = rows * ix.d;
-  hipLaunchKernelGGL(split3_kernel, dim3(blocks(n)), dim3(256), 0, s, A, rows, (int)ix.d, 0, As);
-  HIP_TRY(hipGetLastError());
+  if (A) {
+    const int64_t n = rows * ix.d;
+    hipLaunchKernelGGL(split3_kernel, dim3(blocks(n)), dim3(256), 0, s, A, rows, (int)ix.d, 0, As);
+    HIP_TRY(hipGetLastError());
+  }
   Epi e{};
   e.C = D;
   e.ldc = (int)ix.G;
@@ -806,9 +878,11 @@ void launch_dist_bf16(const Index& ix, const float* A, const float* an, int64_t 
                       hipStream_t s, const int32_t* nlim, int64_t row_base) {
   if (rows <= 0) return;
   if (!ix.cent_split) throw ArgError{HNTL_ESTATE, "BF16 routing: centroid split not built"};
-  const int64_t n = rows * ix.d;
-  hipLaunchKernelGGL(to_bf16_kernel, dim3(blocks(n)), dim3(256), 0, s, A, n, As);
-  HIP_TRY(hipGetLastError());
+  if (A) {
+    const int64_t n = rows * ix.d;
+    hipLaunchKernelGGL(to_bf16_kernel, dim3(blocks(n)), dim3(256), 0, s, A, n, As);
+    HIP_TRY(hipGetLastError());
+  }
   Epi e{};
   e.C = D;
   e.ldc = (int)ix.G;
@@ -850,31 +924,35 @@ float route_err(int form) {
 
 void launch_route_centroid(const Index& ix, const float* Q, int64_t nq, int P, const RouteScratch& w,
                            int32_t* probes, float* pdist, hipStream_t s, const int32_t* nlim,
-                           unsigned int* overflow) {
+                           unsigned int* overflow, int prepared) {
   if (nq <= 0) return;
   if (w.form != ROUTE_F32 && !ix.cent_split) throw ArgError{HNTL_ESTATE, "BF16 routing: centroid split not built"};
   const int G = (int)ix.G, d = (int)ix.d;
-  launch_row_norms(Q, nq, d, w.qn, s);
+  if (prepared < 0) launch_row_norms(Q, nq, d, w.qn, s);
+  const bool operands = prepared == PREP_BF16 || prepared == PREP_BF16X3;
   for (int64_t q0 = 0; q0 < nq; q0 += w.chunk) {
     const int64_t rows = std::min<int64_t>(w.chunk, nq - q0);
     const float* Qc = Q + q0 * d;
     if (rows <= 16 || w.form == ROUTE_F32)  // a few rows: exact direct differences (FP32 MFMA expansion otherwise)
       launch_dist_matrix(Qc, w.qn + q0, rows, ix.centroids, ix.cnorm, G, d, w.D, s, nlim, q0);
     else if (w.form == ROUTE_BF16X3)
-      launch_dist_bf16x3(ix, Qc, w.qn + q0, rows, w.As, w.D, s, nlim, q0);
+      launch_dist_bf16x3(ix, operands ? nullptr : Qc, w.qn + q0, rows, w.As, w.D, s, nlim, q0);
     else
-      launch_dist_bf16(ix, Qc, w.qn + q0, rows, w.As, w.D, s, nlim, q0);
+      launch_dist_bf16(ix, operands ? nullptr : Qc, w.qn + q0, rows, w.As, w.D, s, nlim, q0);
     launch_topk_rows(w.D, rows, G, P, probes + q0 * P, pdist ? pdist + q0 * P : nullptr, s, Qc, w.qn + q0,
                      ix.centroids, ix.cnorm, ix.cnmax, d, route_err(w.form), nlim, q0, overflow);
   }
 }
 
 void launch_route_learned(const Index& ix, const float* Q, int64_t nq, int P, float tau, int32_t* probes,
-                          float* pdist, const RouterScratch& w, hipStream_t s, const int32_t* nlim, float mass) {
+                          float* pdist, const RouterScratch& w, hipStream_t s, const int32_t* nlim, float mass,
+                          bool prepared) {
   const Router& rt = *ix.router;
-  hipLaunchKernelGGL(standardize_kernel, dim3(blocks(nq * rt.d)), dim3(256), 0, s, Q, nullptr, nq, rt.d, rt.mean,
-                     rt.stdv, w.xh, nlim);
-  HIP_TRY(hipGetLastError());
+  if (!prepared) {
+    hipLaunchKernelGGL(standardize_kernel, dim3(blocks(nq * rt.d)), dim3(256), 0, s, Q, nullptr, nq, rt.d, rt.mean,
+                       rt.stdv, w.xh, nlim);
+    HIP_TRY(hipGetLastError());
+  }
   Epi e{};
   e.bias = rt.b[0];
   e.H = w.h1;

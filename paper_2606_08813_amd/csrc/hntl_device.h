@@ -430,18 +430,21 @@ struct WaveTopR {
 // ------------------------------------------------------------- work items
 // Grain of work item `item` of a list whose items per grain have the exclusive
 // prefix ioff[0..G] (the largest g with ioff[g] <= item); false past the end.
+// Called by whole waves with one item each: 64 places are looked at together, so
+// 8,192 grains take three dependent loads instead of thirteen.
 __device__ __forceinline__ bool item_grain(const int32_t* __restrict__ ioff, int G, int item, int& g) {
-  if (item >= ioff[G]) return false;
-  int lo = 0, hi = G;
+  const int lane = lane_id();
+  const int end = ioff[G];
+  int lo = 0, hi = G;  // ioff[lo] <= item < ioff[hi]
   while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (ioff[mid] <= item)
-      lo = mid;
-    else
-      hi = mid;
+    const int step = (hi - lo + 63) >> 6, at = lo + step * lane;
+    // ascending, and true for lane 0: the last place it holds for
+    const uint64_t m = __ballot(at < hi && ioff[at < hi ? at : lo] <= item);
+    lo += step * (m ? 63 - __clzll(m) : 0);
+    hi = min(hi, lo + step);
   }
   g = lo;
-  return true;
+  return item < end;
 }
 
 // Whether the nearest probed grain of query q (probes: P per query) has fewer

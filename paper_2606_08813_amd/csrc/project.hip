@@ -65,13 +65,13 @@ __device__ __forceinline__ int xcd_item(int b) {
 // chunk k0 .. k0 + GK - 1: every thread loads its share of the 16 NCT basis rows
 // (zero rows from r on, zeros from d on) and of the centroid into registers,
 // then LDS; each wave reads its 16 query rows' slices straight from memory into
-// registers (the next chunk's while this chunk's MFMAs run) and forms
+// registers (PD chunks are in flight while one is multiplied) and forms
 // q' = q - mu in FP32.  Two LDS buffers, one barrier per chunk.  Lane (i, kq)
 // feeds depth 32 h + 8 kq + e of row / basis row i of chunk half h, as in
 // project_wave (FP32: 8 steps of 16x16x4, e = step) and project_wave_bf16
 // (one 16x16x32 BF16 step, e = 0..7).  Needs d % 4 == 0 (FP32) or d % 8 == 0
 // (BF16) and 16-byte aligned rows.
-template <bool BF16, int NCT, int NW>
+template <bool BF16, int NCT, int NW, int PD>
 __global__ __launch_bounds__(64 * NW) void project_lds_kernel(
     const float* __restrict__ Q, int d, int P, const float* __restrict__ centroids, const float* __restrict__ basis,
     const uint16_t* __restrict__ basis16, int r, ListRef list, int G, const int32_t* __restrict__ gorder,
@@ -84,6 +84,7 @@ __global__ __launch_bounds__(64 * NW) void project_lds_kernel(
   constexpr int NB = ROWS * VPR;              // basis vectors per chunk
   constexpr int NV = NB + GK / 4;             // + centroid vectors (FP32)
   constexpr int NT = 64 * NW;
+  static_assert(NB % 64 == 0, "a wave stages basis or centroid vectors");
   constexpr int PER = (NV + NT - 1) / NT;     // vectors staged per thread and chunk
   __shared__ __align__(16) E wsh[2][ROWS * RS];
   __shared__ __align__(16) float msh[2][GK];
@@ -103,38 +104,43 @@ __global__ __launch_bounds__(64 * NW) void project_lds_kernel(
   const E* Wg = BF16 ? (const E*)(basis16 + (size_t)g * r * d) : (const E*)(basis + (size_t)g * r * d);
 
   using u32x4 = unsigned int __attribute__((ext_vector_type(4)));
-  u32x4 st[PER];
-  auto stage_load = [&](int k0) {
+  u32x4 st[PD][PER];
+  float qv[PD][16];
+  // Requests chunk k0 into register set p: the thread's share of the basis and
+  // centroid (bounds-checked buffer loads: zeros past the rank and past d), the
+  // lane's query slices (halves h = 0, 1, 8 floats each; depths past d repeat the
+  // row's last, which meet zero basis rows and are zeroed at their use).  No
+  // branches, so that the sets in flight can be counted.
+  const int swave = __builtin_amdgcn_readfirstlane(wave);
+  auto request = [&](int p, int k0) {
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
       const int v = u * NT + (int)threadIdx.x;
-      u32x4 x = {0u, 0u, 0u, 0u};
-      if (v < NB) {
-        const int row = v / VPR, k = k0 + (v % VPR) * EPV;
-        if (row < r && k < d) x = ldg(reinterpret_cast<const u32x4*>(Wg + (size_t)row * d + k));
-      } else if (v < NV) {
-        const int k = k0 + (v - NB) * 4;
-        if (k < d) x = ldg(reinterpret_cast<const u32x4*>(mu + k));
-      }
-      st[u] = x;
+      const bool basis_part = u * NT + 64 * swave < NB;  // NB is a multiple of 64: the same for the wave
+      const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
+          basis_part ? (void*)const_cast<E*>(Wg) : (void*)const_cast<float*>(mu), 0,
+          basis_part ? r * d * (int)sizeof(E) : 4 * d, 0x00027000);
+      const int row = v / VPR, k = k0 + (v % VPR) * EPV;
+      const int at = basis_part ? (row < r && k < d ? (int)sizeof(E) * (row * d + k) : -16)
+                                : (v < NV ? 4 * (k0 + (v - NB) * 4) : -16);
+      st[p][u] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, 0, 0);
     }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int e = 0; e < 8; e += 4) {
+        const int k = min(k0 + 32 * h + 8 * kq + e, d - 4);
+        *reinterpret_cast<floatx4*>(&qv[p][8 * h + e]) = ldg(reinterpret_cast<const floatx4*>(qp + k));
+      }
   };
-  auto stage_store = [&](int buf) {
+  auto stage_store = [&](int p, int buf) {
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
       const int v = u * NT + (int)threadIdx.x;
       if (v < NB)
-        *reinterpret_cast<u32x4*>(&wsh[buf][(v / VPR) * RS + (v % VPR) * EPV]) = st[u];
+        *reinterpret_cast<u32x4*>(&wsh[buf][(v / VPR) * RS + (v % VPR) * EPV]) = st[p][u];
       else if (v < NV)
-        *reinterpret_cast<u32x4*>(&msh[buf][(v - NB) * 4]) = st[u];
-    }
-  };
-  // the lane's query slices of one chunk: halves h = 0, 1, 8 floats each
-  auto q_load = [&](float (&qv)[16], int k0) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int kb = k0 + 32 * h + 8 * kq;
-      load_ks<true>(*reinterpret_cast<float(*)[8]>(&qv[8 * h]), qp + kb, qrow >= 0 ? d - kb : 0);
+        *reinterpret_cast<u32x4*>(&msh[buf][(v - NB) * 4]) = st[p][u];
     }
   };
 
@@ -187,27 +193,26 @@ __global__ __launch_bounds__(64 * NW) void project_lds_kernel(
     }
   };
 
-  const int nch = (d + GK - 1) / GK;
-  float q0[16], q1[16];
-  stage_load(0);
-  q_load(q0, 0);
-  stage_store(0);
-  __syncthreads();
-  // one chunk: prefetch chunk ch + 1 (LDS share into registers, query slices
-  // into `nxt`), multiply chunk ch, publish chunk ch + 1 into the other buffer
-  auto step = [&](int ch, const float (&cur)[16], float (&nxt)[16]) {
-    const bool more = ch + 1 < nch;
-    if (more) {
-      stage_load((ch + 1) * GK);
-      q_load(nxt, (ch + 1) * GK);
+#pragma unroll
+  for (int p = 0; p < PD; ++p) {
+    request(p, p * GK);
+    __builtin_amdgcn_sched_barrier(0);  // requested in the order of use
+  }
+  for (int k0 = 0; k0 < d; k0 += PD * GK) {
+#pragma unroll
+    for (int p = 0; p < PD; ++p) {
+      const int kc = k0 + p * GK;
+      if (kc >= d) break;
+      // the buffer written here was last read two chunks ago, which the barrier between closed
+      const int buf = (kc / GK) & 1;
+      stage_store(p, buf);
+      float cur[16];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) cur[e] = kc + 32 * (e / 8) + 8 * kq + (e & 4) < d ? qv[p][e] : 0.f;
+      __syncthreads();
+      request(p, kc + PD * GK);
+      if (cnt > 0) compute(buf, cur, kc);
     }
-    if (cnt > 0) compute(ch & 1, cur, ch * GK);
-    if (more) stage_store((ch + 1) & 1);
-    __syncthreads();
-  };
-  for (int ch = 0; ch < nch; ch += 2) {
-    step(ch, q0, q1);
-    if (ch + 1 < nch) step(ch + 1, q1, q0);
   }
   if (cnt > 0) project_store<NCT>(acc, sq, r, pairs, cnt, T, epsq);
 }
@@ -222,8 +227,18 @@ void launch_project_k(const Index& ix, const float* Q, int P, const Buckets& b, 
   if (tile == PROJECT_TILE && VEC) {
     constexpr int NW = PROJECT_TILE / PT, M = 8 * XRUN;
     const dim3 grid((unsigned)((b.max_items[LIST_ALL] + M - 1) / M * M)), block(64 * NW);
-    hipLaunchKernelGGL((project_lds_kernel<BF16, NCT, NW>), grid, block, 0, s, Q, (int)ix.d, P, ix.centroids,
-                       ix.basis, ix.basis_bf16, (int)ix.r, list, (int)ix.G, b.gorder, b.order, T, epsq);
+#define HNTL_PROJ(PD)                                                                                              \
+  hipLaunchKernelGGL((project_lds_kernel<BF16, NCT, NW, PD>), grid, block, 0, s, Q, (int)ix.d, P, ix.centroids,   \
+                     ix.basis, ix.basis_bf16, (int)ix.r, list, (int)ix.G, b.gorder, b.order, T, epsq)
+    // Two chunks ahead where the rows are long enough for it and the registers leave
+    // four waves a SIMD (BF16, or up to 32 basis rows): 3,001 queries over 1,024 grains
+    // at rank 32 58 -> 51 us, BF16 at rank 48 158 -> 150; FP32 at rank 48 222 -> 237,
+    // rows of 128 26 -> 32.  Four ahead lost everywhere (62, 168, 282, 44).
+    if ((BF16 || NCT <= 2) && ix.d >= 4 * GK)
+      HNTL_PROJ(2);
+    else
+      HNTL_PROJ(1);
+#undef HNTL_PROJ
     return;
   }
   if (tile != PT) throw ArgError{HNTL_EDEVICE, "projection item size must be 16 pairs (or PROJECT_TILE, vector form)"};

@@ -617,8 +617,8 @@ __device__ __forceinline__ int row_window(const float* __restrict__ drow, int co
 
 // Bound by memory (the row is read once: 135 us of 16,384 x 8,192 at 4 TB/s, then
 // 3 KB a re-scored entry from cache) with one row per wave and its whole row in
-// flight.  At 16,384 x 8,192: scores 144 us, distances with 27 re-scored entries
-// a row 217 us; a streamed list (16 chunks a segment, about ten flushes a row)
+// flight.  At 16,384 x 8,192: scores 123 us, distances with 27 re-scored entries
+// a row 210 us; a streamed list (16 chunks a segment, about ten flushes a row)
 // took 185 and 273.  256 such rows 29 us (49), 10,000 x 1,024 30 us (49), one row
 // of 1,024 5.8 us (10.8).
 // bmax: the largest bn (device).

@@ -123,6 +123,76 @@ __device__ __forceinline__ void epi_store_t(const Epi& e, int row, int col, floa
   }
 }
 
+// CT consecutive output columns of one row, with 4-byte alignment (a row of an odd
+// number of columns moves the next one's).
+template <class T, int CT>
+struct Run {
+  typedef T type __attribute__((ext_vector_type(CT), aligned(sizeof(T))));
+};
+
+// Stores a wave's RT tiles of 16 rows and its 16 CT columns from (row0, col0), lane i
+// of a row holding columns CT i .. CT i + CT - 1 (B's rows go into the MFMAs in that
+// order): a store instruction covers whole stretches of 64 CT bytes of four rows.
+// With column 16 b + i in tile b every store touched 64 bytes of a row at a time, and
+// 16,384 x 8,192 outputs took 227 us to leave (2.4 TB/s); the distances of 16,384 x
+// 8,192 x 768 take 268 us (339 before), the scores over 1,024 320 (367).  The row
+// and column terms are loaded before the first store: a load after a store would
+// wait for it.  NT: FP32 outputs of 64 MB and more, larger than what the caches
+// keep for their reader, bypass them (selection after them 227 -> 210 us, 150 ->
+// 123 without distances).
+template <int EPI, int RT, int CT, bool NT>
+__device__ __forceinline__ void tile_store(const Epi& e, const floatx4 (&acc)[RT][CT], int row0, int col0, int M, int N) {
+  const int lane = lane_id();
+  const int i = lane & 15, kq = lane >> 4;
+  const int col = col0 + CT * i;
+  float ct[CT], rt[RT][4];
+#pragma unroll
+  for (int b = 0; b < CT; ++b) ct[b] = epi_col_term<EPI>(e, min(col + b, N - 1));
+#pragma unroll
+  for (int a = 0; a < RT; ++a)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) rt[a][j] = epi_row_term<EPI>(e, min(row0 + 16 * a + 4 * kq + j, M - 1));
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int a = 0; a < RT; ++a)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int row = row0 + 16 * a + 4 * kq + j;
+      if (row >= M) continue;
+      if (EPI != EPI_GELU_GRAD && col + CT <= N) {
+        typename Run<float, CT>::type v;
+        typename Run<uint16_t, CT>::type h;
+#pragma unroll
+        for (int b = 0; b < CT; ++b) {
+          const float x = acc[a][b][j];
+          if constexpr (EPI == EPI_F32)
+            v[b] = x;
+          else if constexpr (EPI == EPI_BIAS_F32)
+            v[b] = e.scale * (x + ct[b]);
+          else if constexpr (EPI == EPI_DIST)
+            v[b] = fmaxf(rt[a][j] + ct[b] - 2.f * x, 0.f);
+          else {
+            v[b] = x + ct[b];
+            h[b] = to_bf16(gelu(v[b]));
+          }
+        }
+        if (EPI != EPI_BIAS_GELU || e.C) {
+          auto* out = reinterpret_cast<typename Run<float, CT>::type*>(e.C + (size_t)row * e.ldc + col);
+          if constexpr (NT)
+            __builtin_nontemporal_store(v, out);
+          else
+            *out = v;
+        }
+        if constexpr (EPI == EPI_BIAS_GELU)
+          *reinterpret_cast<typename Run<uint16_t, CT>::type*>(e.H + (size_t)row * e.ldh + col) = h;
+      } else {
+#pragma unroll
+        for (int b = 0; b < CT; ++b)
+          if (col + b < N) epi_store_t<EPI>(e, row, col + b, acc[a][b][j], rt[a][j], ct[b]);
+      }
+    }
+}
+
 // ----------------------------------------------- small-tile GEMM, any orientation
 // C(m, n) = sum_k A(m, k) B(n, k), where XT = false: X(r, k) = X[r * ld + k] (K % 8
 // == 0) and XT = true: X(r, k) = X[k * ld + r] (rows % 8 == 0); ld % 8 == 0 and
@@ -137,9 +207,9 @@ __device__ __forceinline__ void epi_store_t(const Epi& e, int row, int col, floa
 // (8 rows apart) share banks.  A transposed operand comes in as 8 rows of two
 // neighbouring depths a thread, which leave as eight 4-byte pairs.
 // Training steps of 512 rows over 768-1024-1024-1024: weight gradients 15 us each,
-// input gradients 17, forward products 11 (49 and 59 on 128 x 128 tiles that stored
+// input gradients 17, forward products 9 (49 and 59 on 128 x 128 tiles that stored
 // transposed operands element by element, 36 on 256 x 128 tiles); 256 x 8,192 x 768:
-// 15 us (33 on 256 x 128 tiles).  Tiles are handed to the XCDs in contiguous runs.
+// 13 us (33 on 256 x 128 tiles).  Tiles are handed to the XCDs in contiguous runs.
 constexpr int SM = 64, SK = 64, SPD = 4;
 
 struct SFrag {
@@ -231,7 +301,7 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const uint16_t* __restr
         bf16x8 af[2], bfv[2];
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-          const int ra = wm + 16 * t + i, rb = wn + 16 * t + i;
+          const int ra = wm + 16 * t + i, rb = wn + 2 * i + t;
           af[t] = *reinterpret_cast<const bf16x8*>(&As[p & 1][ra][8 * svec(ra, ks / 8 + kq)]);
           bfv[t] = *reinterpret_cast<const bf16x8*>(&Bs[p & 1][rb][8 * svec(rb, ks / 8 + kq)]);
         }
@@ -243,16 +313,7 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const uint16_t* __restr
       }
     }
   }
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int row = m0 + wm + 16 * a + 4 * kq + j;
-        const int col = n0 + wn + 16 * b + i;
-        if (row < M && col < N) epi_store<EPI>(e, row, col, acc[a][b][j]);
-      }
+  tile_store<EPI, 2, 2, false>(e, acc, m0 + wm, n0 + wn, M, N);
 }
 
 // ------------------------------- 256 x 256 tiles, LDS filled by direct loads
@@ -264,9 +325,8 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const uint16_t* __restr
 // wave instruction writes 16 bytes at the instruction's LDS base + 16 l), into
 // two buffers: tile k + 1 is requested before tile k is multiplied, so its
 // latency hides behind a whole tile of MFMAs, with no registers holding it.
-// A row of a depth tile is 8 chunks of 16 bytes; chunk c of row r sits at
-// position c ^ (r % 8) of the row (an XOR swizzle), so the 16 rows read by
-// one ds_read_b128 of an MFMA fragment spread over the LDS banks.  Rows past M
+// A row of a depth tile is 8 chunks of 16 bytes, swizzled so that the rows of one
+// fragment read spread over the LDS banks (dl_pos). Rows past M
 // or N load a valid clamped row (their results are never stored).  Every
 // output element is accumulated in the same order as in gemm_small_kernel (depth
 // tiles of 64, MFMA steps of 32), so the kernels give identical results.
@@ -277,17 +337,37 @@ constexpr size_t BIG_LDS = 2 * DL_STAGE;
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
+// Position of depth chunk c of row r of a 256 x 64 tile, and what sits at a
+// position.  A's fragments read 16 neighbouring rows: chunk c at c ^ (r % 8) of its
+// row.  B's read every fourth row: the 16 chunks of a pair of rows are permuted by
+// XOR with (r / 4) % 16, so those rows too spread over the banks.
+template <bool FOURTH>
+__device__ __forceinline__ int dl_pos(int r, int c) {
+  return FOURTH ? (r >> 1) * 16 + (((r & 1) * 8 + c) ^ ((r >> 2) & 15)) : r * 8 + (c ^ (r & 7));
+}
+template <bool FOURTH>
+__device__ __forceinline__ void dl_at(int pos, int& r, int& c) {
+  if constexpr (FOURTH) {
+    const int x = (pos & 15) ^ ((pos >> 5) & 15);
+    r = (pos >> 4) * 2 + (x >> 3);
+    c = x & 7;
+  } else {
+    r = pos >> 3;
+    c = (pos & 7) ^ (r & 7);
+  }
+}
+
 // Requests one operand's 256 x 64 depth tile (rows r0.., depths k0..) into
 // the LDS at `dst`: 2048 chunks, 4 wave instructions of 64 chunks per wave.
+template <bool FOURTH>
 __device__ __forceinline__ void dl_fetch(uint16_t* dst, const uint16_t* __restrict__ X, int ld, int R, int r0,
                                          int k0) {
   const int lane = lane_id(), wave = threadIdx.x >> 6;
 #pragma unroll
   for (int h = 0; h < 4; ++h) {
-    const int u = h * 8 + wave;         // instruction index: LDS bytes 1024 u .. + 1023
-    const int c = u * 64 + lane;        // chunk of the tile in LDS order
-    const int row = c >> 3, pos = c & 7;
-    const int kc = pos ^ (row & 7);     // the depth chunk stored at that position
+    const int u = h * 8 + wave;  // instruction index: LDS bytes 1024 u .. + 1023
+    int row, kc;
+    dl_at<FOURTH>(u * 64 + lane, row, kc);
     const int gr = min(r0 + row, R - 1);
     __builtin_amdgcn_global_load_lds((const void*)(X + (size_t)gr * ld + k0 + kc * 8),
                                      (lds_ptr_t)(dst + (size_t)u * 512), 16, 0, 0);
@@ -295,8 +375,9 @@ __device__ __forceinline__ void dl_fetch(uint16_t* dst, const uint16_t* __restri
 }
 
 // 8 bf16 of row r, depths 8 kc .. 8 kc + 7, of a swizzled depth tile.
+template <bool FOURTH>
 __device__ __forceinline__ bf16x8 dl_frag(const uint16_t* S, int r, int kc) {
-  return *reinterpret_cast<const bf16x8*>(S + ((size_t)r * 8 + (kc ^ (r & 7))) * 8);
+  return *reinterpret_cast<const bf16x8*>(S + (size_t)dl_pos<FOURTH>(r, kc) * 8);
 }
 
 template <int EPI>
@@ -332,15 +413,15 @@ __global__ __launch_bounds__(512) void gemm_big_kernel(const uint16_t* __restric
   const int nk = K / SK;
   uint16_t* const st0 = dsm;
   uint16_t* const st1 = dsm + DL_STAGE / sizeof(uint16_t);
-  dl_fetch(st0, A, lda, M, m0, 0);
-  dl_fetch(st0 + BM * SK, B, ldb, N, n0, 0);
+  dl_fetch<false>(st0, A, lda, M, m0, 0);
+  dl_fetch<true>(st0 + BM * SK, B, ldb, N, n0, 0);
   for (int k = 0; k < nk; ++k) {
     __builtin_amdgcn_s_waitcnt(0);  // this wave's requests for tile k have landed
     __syncthreads();                // every wave's have, and every wave is done with tile k - 1
     if (k + 1 < nk) {               // the other buffer (last read for tile k - 1) takes tile k + 1
       uint16_t* nx = (k & 1) ? st0 : st1;
-      dl_fetch(nx, A, lda, M, m0, (k + 1) * SK);
-      dl_fetch(nx + BM * SK, B, ldb, N, n0, (k + 1) * SK);
+      dl_fetch<false>(nx, A, lda, M, m0, (k + 1) * SK);
+      dl_fetch<true>(nx + BM * SK, B, ldb, N, n0, (k + 1) * SK);
     }
     const uint16_t* As = (k & 1) ? st1 : st0;
     const uint16_t* Bs = As + BM * SK;
@@ -349,33 +430,16 @@ __global__ __launch_bounds__(512) void gemm_big_kernel(const uint16_t* __restric
       const int kc = (ks >> 3) + kq;
       bf16x8 bfv[4];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) bfv[t] = dl_frag(Bs, wn + 16 * t + i, kc);
+      for (int t = 0; t < 4; ++t) bfv[t] = dl_frag<true>(Bs, wn + 4 * i + t, kc);
 #pragma unroll
       for (int a = 0; a < 8; ++a) {
-        const bf16x8 af = dl_frag(As, wm + 16 * a + i, kc);
+        const bf16x8 af = dl_frag<false>(As, wm + 16 * a + i, kc);
 #pragma unroll
         for (int b = 0; b < 4; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bfv[b], acc[a][b], 0, 0, 0);
       }
     }
   }
-  float ct[4];
-#pragma unroll
-  for (int b = 0; b < 4; ++b) {
-    const int col = n0 + wn + 16 * b + i;
-    ct[b] = col < N ? epi_col_term<EPI>(e, col) : 0.f;
-  }
-#pragma unroll
-  for (int a = 0; a < 8; ++a)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int row = m0 + wm + 16 * a + 4 * kq + j;
-      const float rt = row < M ? epi_row_term<EPI>(e, row) : 0.f;
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const int col = n0 + wn + 16 * b + i;
-        if (row < M && col < N) epi_store_t<EPI>(e, row, col, acc[a][b][j], rt, ct[b]);
-      }
-    }
+  tile_store<EPI, 8, 4, true>(e, acc, m0 + wm, n0 + wn, M, N);
 }
 // 256 x 256 tiles once every CU gets one.  Three products of n rows over
 // 768-1024-1024-8192: n = 16,384 524 us against 887 on 64 x 64 tiles, 8,192 328

@@ -6,6 +6,7 @@ import pytest
 from oracle import router as orr
 from tests.gpu_common import announce, require_gpu, to_dev
 from tests.test_gpu_router_sizes import small_index
+from tests.test_gpu_tiles import plain_index
 from workloads import patch_mixture as pm
 
 pytestmark = pytest.mark.gpu
@@ -36,3 +37,21 @@ def test_scores_and_gradients(n, d, h1, h2, G):
     for k in ref:
         err = np.linalg.norm(g[k].astype(np.float64) - ref[k]) / max(np.linalg.norm(ref[k]), 1e-300)
         assert err < 1e-3, (k, err)  # the bound of the wide-layer test
+
+
+@pytest.mark.parametrize("nq,G", [(4160, 4101), (4100, 4099), (5000, 4225)])
+@pytest.mark.parametrize("flag", ["HNTL_FLAG_ROUTE_BF16", "HNTL_FLAG_ROUTE_BF16X3"])
+def test_large_tiles_at_odd_column_counts(nq, G, flag):
+    """256 x 256 tiles whose rows of results start at any 4-byte address and whose last columns are no whole run."""
+    torch = require_gpu()
+    from paper_2606_08813_amd import hntl
+    announce(f"{flag}: {nq} x {G}")
+    d, P = 64, 4
+    cent = pm.uniform_rows(G, d, 94)
+    Q = pm.uniform_rows(nq, d, 95)
+    ix = plain_index(hntl, cent, cent, r=8)
+    o = hntl.hntl_search_stages(ix, to_dev(Q), P, 8, 1, flags=hntl.HNTL_FLAG_SYNC | getattr(hntl, flag))
+    full = hntl.hntl_search_stages(ix, to_dev(Q), P, 8, 1)
+    # the re-scored nearest grains do not depend on the form of the product
+    assert torch.equal(o["probes"], full["probes"])
+    assert torch.equal(o["pdist"], full["pdist"])

@@ -563,10 +563,11 @@ __global__ void col_combine_kernel(const double* __restrict__ part, int64_t n, i
 }
 
 // Softmax cross-entropy of one row of scores against the target distribution
-// of `kt` grain ids (each weighing 1 / kt): ds = (p - y) / B in FP32 and BF16,
-// and the row's loss.  One workgroup of 256 per row.
+// of `kt` grain ids (each weighing 1 / kt; row rows[r] of tgt, or r itself):
+// ds = (p - y) / B in FP32 and BF16, and the row's loss.  One workgroup of 256 per row.
 __global__ __launch_bounds__(256) void softmax_ce_kernel(const float* __restrict__ S, int G,
-                                                         const int32_t* __restrict__ tgt, int kt, float invB,
+                                                         const int32_t* __restrict__ tgt,
+                                                         const int32_t* __restrict__ rows, int kt, float invB,
                                                          float* __restrict__ ds, uint16_t* __restrict__ dsb,
                                                          float* __restrict__ loss) {
   __shared__ float red[256];
@@ -592,7 +593,7 @@ __global__ __launch_bounds__(256) void softmax_ce_kernel(const float* __restrict
   }
   z = red[0];
   const float logz = logf(z);
-  const int32_t* t = tgt + r * kt;
+  const int32_t* t = tgt + (rows ? (int64_t)rows[r] : r) * kt;
   const float w = 1.f / (float)kt;
   for (int g = threadIdx.x; g < G; g += 256) {
     float y = 0.f;
@@ -763,14 +764,21 @@ __global__ void map_ids_kernel(const int32_t* __restrict__ ids, int64_t n, const
 
 inline unsigned blocks(int64_t n, int t = 256) { return (unsigned)((n + t - 1) / t); }
 
-uint64_t splitmix(uint64_t x) {
+__host__ __device__ inline uint64_t splitmix(uint64_t x) {
   x += 0x9E3779B97F4A7C15ull;
   x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
   x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
   return x ^ (x >> 31);
 }
-double uni(uint64_t seed, uint64_t stream, uint64_t i) {
+__host__ __device__ inline double uni(uint64_t seed, uint64_t stream, uint64_t i) {
   return (double)(splitmix(splitmix(seed ^ (stream * 0xD1B54A32D192ED03ull)) + i) >> 11) * (1.0 / 9007199254740992.0);
+}
+
+// Uniform weights in [-bound, bound) from the counter-based generator.  3.8 million of
+// them on the host and their copy kept a training run of 16,384 rows waiting 1.7 ms.
+__global__ void init_weights_kernel(float* __restrict__ w, int64_t n, uint64_t seed, uint64_t stream, double bound) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) w[i] = (float)((2.0 * uni(seed, stream, (uint64_t)i) - 1.0) * bound);
 }
 
 }  // namespace
@@ -1150,7 +1158,8 @@ struct Trainer {
   }
 
   // Loss and gradients of the batch X[rows[0..B)] against targets tg (B x kt).
-  void grad(const float* X, const int32_t* d_rows, const int32_t* tg, int kt) {
+  // trows: the targets' rows (null: tg holds the batch's own); the loss is added to *lossp
+  void grad(const float* X, const int32_t* d_rows, const int32_t* tg, const int32_t* trows, int kt, float* lossp) {
     const int d = rt.d, H1 = rt.h1, H2 = rt.h2, G = rt.G;
     hipLaunchKernelGGL(standardize_kernel, dim3(blocks((int64_t)B * d)), dim3(256), 0, s, X, d_rows, (int64_t)B, d,
                        rt.mean, rt.stdv, xh, nullptr);
@@ -1173,8 +1182,7 @@ struct Trainer {
     o.bias = rt.b[2];
     o.scale = 1.f;
     gemm<false, false, EPI_BIAS_F32>(h2, H2, rt.Wb[2], H2, B, G, H2, o, s);
-    HIP_TRY(hipMemsetAsync(loss, 0, sizeof(float), s));
-    hipLaunchKernelGGL(softmax_ce_kernel, dim3(B), dim3(256), 0, s, S, G, tg, kt, 1.f / (float)B, ds, dsb, loss);
+    hipLaunchKernelGGL(softmax_ce_kernel, dim3(B), dim3(256), 0, s, S, G, tg, trows, kt, 1.f / (float)B, ds, dsb, lossp);
     HIP_TRY(hipGetLastError());
     // layer 3: gW3[g][k] = sum_b ds[b][g] h2[b][k]; dh2 = ds W3, times gelu'(a2)
     Epi w{};
@@ -1318,7 +1326,8 @@ hntl_status hntl_router_grad(hntl_index* index, const float* X, uint32_t n, cons
     std::vector<int32_t> idx(n);
     std::iota(idx.begin(), idx.end(), 0);
     HIP_TRY(hipMemcpyAsync(tr.rows, idx.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, s));
-    tr.grad(X, tr.rows, targets, (int)kt);
+    HIP_TRY(hipMemsetAsync(tr.loss, 0, sizeof(float), s));
+    tr.grad(X, tr.rows, targets, nullptr, (int)kt, tr.loss);
     float* outs[6] = {gW1, gb1, gW2, gb2, gW3, gb3};
     for (int l = 0; l < 3; ++l) {
       if (outs[2 * l]) HIP_TRY(hipMemcpyAsync(outs[2 * l], tr.g[2 * l], sizeof(float) * rt.wsize(l), hipMemcpyDefault, s));
@@ -1397,10 +1406,9 @@ hntl_status hntl_router_train(hntl_index* index, const float* Qtrain, uint32_t n
       for (int l = 0; l < 3; ++l) {
         const int fan_in = l == 0 ? rt.d : l == 1 ? rt.h1 : rt.h2;
         const double bound = std::sqrt((l < 2 ? 6.0 : 3.0) / fan_in);
-        std::vector<float> w(rt.wsize(l));
-        for (size_t i = 0; i < w.size(); ++i) w[i] = (float)((2.0 * uni(rp->seed, 10 + l, i) - 1.0) * bound);
-        HIP_TRY(hipMemcpy(rt.W[l], w.data(), sizeof(float) * w.size(), hipMemcpyHostToDevice));
-        HIP_TRY(hipMemset(rt.b[l], 0, sizeof(float) * rt.bsize(l)));
+        hipLaunchKernelGGL(init_weights_kernel, dim3(blocks(rt.wsize(l))), dim3(256), 0, s, rt.W[l], rt.wsize(l),
+                           rp->seed, (uint64_t)(10 + l), bound);
+        HIP_TRY(hipMemsetAsync(rt.b[l], 0, sizeof(float) * rt.bsize(l), s));
       }
       Scratch sc(s);
       double* part = sc.get<double>((size_t)STAT_SPLITS * ix.d);
@@ -1444,16 +1452,16 @@ hntl_status hntl_router_train(hntl_index* index, const float* Qtrain, uint32_t n
     const uint32_t epochs = rp->epochs ? rp->epochs : 1;
     std::vector<int32_t> order(n);
     std::iota(order.begin(), order.end(), 0);
+    // Batches are not waited for: the order of the rows, the targets and the batches'
+    // losses stay on the device for an epoch (a wait, a gather of targets on the host
+    // and a copy per batch left the GPU idle for 2.6 ms of a 32-batch epoch).
     int32_t* d_order = nullptr;
-    int32_t* tgb = nullptr;
+    float* d_loss = nullptr;
     HIP_TRY(hipMalloc((void**)&d_order, sizeof(int32_t) * n));
-    HIP_TRY(hipMalloc((void**)&tgb, sizeof(int32_t) * (size_t)B * kt));
     std::unique_ptr<int32_t, void (*)(int32_t*)> o1(d_order, [](int32_t* p) { (void)hipFree(p); });
-    std::unique_ptr<int32_t, void (*)(int32_t*)> o2(tgb, [](int32_t* p) { (void)hipFree(p); });
-    std::vector<int32_t> tg_h((size_t)n * kt);
-    HIP_TRY(hipMemcpyAsync(tg_h.data(), tg, sizeof(int32_t) * tg_h.size(), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    std::vector<int32_t> tgb_h((size_t)B * kt);
+    HIP_TRY(hipMalloc((void**)&d_loss, sizeof(float) * nb));
+    std::unique_ptr<float, void (*)(float*)> o2(d_loss, [](float* p) { (void)hipFree(p); });
+    std::vector<float> loss_h(nb);
     for (uint32_t ep = 0; ep < epochs; ++ep) {
       if (!(rp->flags & HNTL_ROUTER_NO_SHUFFLE))  // Fisher-Yates from the counter-based generator
         for (uint32_t i = n - 1; i > 0; --i) {
@@ -1461,18 +1469,16 @@ hntl_status hntl_router_train(hntl_index* index, const float* Qtrain, uint32_t n
           std::swap(order[i], order[std::min(j, i)]);
         }
       HIP_TRY(hipMemcpyAsync(d_order, order.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, s));
-      double eloss = 0.0;
+      HIP_TRY(hipMemsetAsync(d_loss, 0, sizeof(float) * nb, s));
       for (uint32_t bi = 0; bi < nb; ++bi) {
-        for (uint32_t r = 0; r < B; ++r)
-          std::memcpy(&tgb_h[(size_t)r * kt], &tg_h[(size_t)order[bi * B + r] * kt], sizeof(int32_t) * kt);
-        HIP_TRY(hipMemcpyAsync(tgb, tgb_h.data(), sizeof(int32_t) * tgb_h.size(), hipMemcpyHostToDevice, s));
-        tr.grad(Qtrain, d_order + (size_t)bi * B, tgb, (int)kt);
+        const int32_t* rows = d_order + (size_t)bi * B;
+        tr.grad(Qtrain, rows, tg, rows, (int)kt, d_loss + bi);
         tr.adam(rp->lr > 0 ? rp->lr : 1e-3f);
-        float l = 0.f;
-        HIP_TRY(hipMemcpyAsync(&l, tr.loss, sizeof(float), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));  // also keeps tgb_h from being overwritten early
-        eloss += l;
       }
+      HIP_TRY(hipMemcpyAsync(loss_h.data(), d_loss, sizeof(float) * nb, hipMemcpyDeviceToHost, s));
+      HIP_TRY(hipStreamSynchronize(s));  // also keeps the row order from being overwritten early
+      double eloss = 0.0;
+      for (float l : loss_h) eloss += l;
       if (epoch_loss) epoch_loss[ep] = (float)(eloss / nb);
     }
     rt.trained = true;

@@ -211,6 +211,38 @@ __device__ __forceinline__ void chunk_step(floatx4 (&acc)[MT][NT], HalfFrag<MT, 
   f1.mma(acc);
 }
 
+// Stores a wave's MT x NT MFMA tiles of distances from (row0, col0).  The norms
+// are loaded before the first store: a load after a store would wait for it.
+template <int MT, int NT>
+__device__ __forceinline__ void store_dist(const floatx4 (&acc)[MT][NT], const float* __restrict__ an, int64_t row0,
+                                           int64_t rows, const float* __restrict__ bn, int col0, int cols,
+                                           float* __restrict__ D) {
+  const int lane = lane_id();
+  float ar[MT][4], br[NT];
+#pragma unroll
+  for (int n = 0; n < NT; ++n) br[n] = bn[min(col0 + n * 16 + (lane & 15), cols - 1)];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t row = row0 + m * 16 + 4 * (lane >> 4) + i;
+      ar[m][i] = an[row < rows ? row : rows - 1];
+    }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t row = row0 + m * 16 + 4 * (lane >> 4) + i;
+      if (row >= rows) continue;
+#pragma unroll
+      for (int n = 0; n < NT; ++n) {
+        const int col = col0 + n * 16 + (lane & 15);
+        if (col < cols) D[row * cols + col] = fmaxf(ar[m][i] + br[n] - 2.f * acc[m][n][i], 0.f);
+      }
+    }
+}
+
 // Distances on the tiles above: 10,000 x 1,024 x 768 in 155 us (101 TFLOP/s; 158 on
 // tile_dot), 300 x 2,048 x 768 in 22 us (31 on tile_dot), 16,384 x 8,192 x 768 in
 // 1.77 ms (117 TFLOP/s; 1.88).  Without the requests the loop runs at 137 to 143
@@ -260,19 +292,7 @@ __global__ __launch_bounds__(64 * WR * WC) void dist_tile_kernel(const float* __
     chunk_step(acc, f0, buf1, buf1 + RT * FK, buf0, buf0 + RT * FK, wr, wc, d - (k + 1) * FK, k + 2 < nk,
                d - (k + 2) * FK, [&]() { fetch(buf1, k + 3); }, none);
   }
-#pragma unroll
-  for (int m = 0; m < MT; ++m)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t row = row0 + wr + m * 16 + 4 * (lane >> 4) + i;
-      if (row >= rows) continue;
-      const float ar = an[row];
-#pragma unroll
-      for (int n = 0; n < NT; ++n) {
-        const int col = col0 + wc + n * 16 + (lane & 15);
-        if (col < cols) D[row * cols + col] = fmaxf(ar + bn[col] - 2.f * acc[m][n][i], 0.f);
-      }
-    }
+  store_dist<MT, NT>(acc, an, row0 + wr, rows, bn, col0 + wc, cols, D);
 }
 
 // The same distances on tile_dot: short rows and rows that allow no 16-byte
@@ -295,19 +315,7 @@ __global__ __launch_bounds__(256) void dist_matrix_kernel(const float* __restric
   floatx4 acc[2][2];
   tile_dot(acc, As, Bs, A, rows, Bm, cols, d, row0, col0, vec4);
   const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
-#pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-    for (int ct = 0; ct < 2; ++ct)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int64_t row = row0 + wr + rt * 16 + 4 * (lane >> 4) + i;
-        const int col = col0 + wc + ct * 16 + (lane & 15);
-        if (row < rows && col < cols) {
-          const float v = an[row] + bn[col] - 2.f * acc[rt][ct][i];
-          D[row * cols + col] = fmaxf(v, 0.f);
-        }
-      }
+  store_dist<2, 2>(acc, an, row0 + wr, rows, bn, col0 + wc, cols, D);
 }
 
 // Small batches (<= 16 rows): exact distances by direct differences, one

@@ -419,7 +419,7 @@ __global__ __launch_bounds__(512) void fused_kernel(const FusedArgs* __restrict_
       if (a.proj_bf16)
         project_wave_bf16<NCT>(a.Q, a.d, a.P, a.centroids, a.basis16, a.r, g, pairs, cnt, a.T, a.epsq);
       else
-        project_wave<true, NCT>(a.Q, a.d, a.P, a.centroids, a.basis, a.r, g, pairs, cnt, a.T, a.epsq);
+        project_wave<true, NCT, QT == 1>(a.Q, a.d, a.P, a.centroids, a.basis, a.r, g, pairs, cnt, a.T, a.epsq);
       // release: the tangents of this item are visible before its flag is
       __hip_atomic_store((gptr)(a.proj_done + it), 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
     }

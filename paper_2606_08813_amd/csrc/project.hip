@@ -29,7 +29,7 @@ __global__ __launch_bounds__(64) void project_kernel(
   const int first = (blockIdx.x - list.ioff[rank]) * PT;  // within the grain's pairs
   const int cnt = min(PT, list.count(rank) - first);
   if (cnt <= 0) return;
-  project_wave<VEC, NCT>(Q, d, P, centroids, basis, r, g, order + list.start(rank) + first, cnt, T, epsq);
+  project_wave<VEC, NCT, true>(Q, d, P, centroids, basis, r, g, order + list.start(rank) + first, cnt, T, epsq);
 }
 
 template <int NCT>

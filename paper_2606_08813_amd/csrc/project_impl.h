@@ -87,7 +87,7 @@ __device__ __forceinline__ void project_store(const floatx4 (&acc)[NCT], float s
 // per operand and chunk straight from global memory.  NCT = ceil(r / 16)
 // column tiles.
 // Projects the cnt (<= 16) pairs pairs[0..cnt) of grain g with one wave.
-template <bool VEC, int NCT>
+template <bool VEC, int NCT, bool STREAM>
 __device__ __forceinline__ void project_wave(const float* __restrict__ Q, int d, int P,
                                              const float* __restrict__ centroids, const float* __restrict__ basis,
                                              int r, int g, const int32_t* __restrict__ pairs, int cnt,
@@ -104,22 +104,45 @@ __device__ __forceinline__ void project_wave(const float* __restrict__ Q, int d,
   for (int c = 0; c < NCT; ++c) acc[c] = floatx4{0.f, 0.f, 0.f, 0.f};
   float sq = 0.f;
 
-  // two register sets: the next depth chunk loads while this one multiplies
+  // Two register sets: the next depth chunk loads while this one multiplies.  STREAM
+  // (16-byte loads only): nothing is skipped past d (the row's last four values come
+  // instead, and the query's are zeroed when they are used), since a load behind a
+  // branch makes every wait a full one.  It takes more registers: for kernels whose
+  // item is a projection, or that have them (the fused kernel's single pairs; with
+  // 2 and 4 pairs its occupancy would fall).  One query over 8 grains of rank 32, d =
+  // 768: the fused kernel 27 us (29).
+  constexpr bool S = VEC && STREAM;
   auto load = [&](float (&a)[KS], float (&m)[KS], float (&b)[NCT][KS], int k0) {
     const int kb = k0 + KS * kq;
     const int lim = d - kb;  // valid floats from kb (may be <= 0: zeros)
-    load_ks<VEC>(m, mu + kb, lim);
-    load_ks<VEC>(a, qp + kb, qrow >= 0 ? lim : 0);
+    if constexpr (S) {
 #pragma unroll
-    for (int c = 0; c < NCT; ++c) {
-      const int j = c * 16 + i;
-      load_ks<VEC>(b[c], Wg + (size_t)(j < r ? j : 0) * d + kb, j < r ? lim : 0);
+      for (int e = 0; e < KS; e += 4) {
+        const int k = min(kb + e, d - 4);
+        *reinterpret_cast<floatx4*>(&m[e]) = ldg(reinterpret_cast<const floatx4*>(mu + k));
+        *reinterpret_cast<floatx4*>(&a[e]) = ldg(reinterpret_cast<const floatx4*>(qp + k));
+#pragma unroll
+        for (int c = 0; c < NCT; ++c) {
+          const int j = c * 16 + i;
+          *reinterpret_cast<floatx4*>(&b[c][e]) =
+              ldg(reinterpret_cast<const floatx4*>(Wg + (size_t)(j < r ? j : 0) * d + k));
+        }
+      }
+    } else {
+      load_ks<VEC>(m, mu + kb, lim);
+      load_ks<VEC>(a, qp + kb, qrow >= 0 ? lim : 0);
+#pragma unroll
+      for (int c = 0; c < NCT; ++c) {
+        const int j = c * 16 + i;
+        load_ks<VEC>(b[c], Wg + (size_t)(j < r ? j : 0) * d + kb, j < r ? lim : 0);
+      }
     }
   };
-  auto mult = [&](float (&a)[KS], const float (&m)[KS], const float (&b)[NCT][KS]) {
+  auto mult = [&](float (&a)[KS], const float (&m)[KS], const float (&b)[NCT][KS], int k0) {
+    const int kb = k0 + KS * kq;
 #pragma unroll
     for (int e = 0; e < KS; ++e) {
-      a[e] = qrow >= 0 ? a[e] - m[e] : 0.f;
+      a[e] = qrow >= 0 && (!S || kb + (e & ~3) < d) ? a[e] - m[e] : 0.f;
       sq = fmaf(a[e], a[e], sq);
     }
 #pragma unroll
@@ -127,15 +150,25 @@ __device__ __forceinline__ void project_wave(const float* __restrict__ Q, int d,
 #pragma unroll
       for (int c = 0; c < NCT; ++c) acc[c] = mfma16x16x4(a[e], b[c][e], acc[c]);
   };
-  float a0[KS], m0[KS], b0[NCT][KS], a1[KS], m1[KS], b1[NCT][KS];
+  alignas(16) float a0[KS], m0[KS], b0[NCT][KS], a1[KS], m1[KS], b1[NCT][KS];
   load(a0, m0, b0, 0);
   for (int k0 = 0; k0 < d; k0 += 2 * KC) {
-    const bool second = k0 + KC < d;
-    if (second) load(a1, m1, b1, k0 + KC);
-    mult(a0, m0, b0);
-    if (second) {
-      if (k0 + 2 * KC < d) load(a0, m0, b0, k0 + 2 * KC);
-      mult(a1, m1, b1);
+    if constexpr (S) {
+      load(a1, m1, b1, k0 + KC);
+      __builtin_amdgcn_sched_barrier(0);
+      mult(a0, m0, b0, k0);
+      if (k0 + KC >= d) break;
+      load(a0, m0, b0, k0 + 2 * KC);
+      __builtin_amdgcn_sched_barrier(0);
+      mult(a1, m1, b1, k0 + KC);
+    } else {
+      const bool second = k0 + KC < d;
+      if (second) load(a1, m1, b1, k0 + KC);
+      mult(a0, m0, b0, k0);
+      if (second) {
+        if (k0 + 2 * KC < d) load(a0, m0, b0, k0 + 2 * KC);
+        mult(a1, m1, b1, k0 + KC);
+      }
     }
   }
 

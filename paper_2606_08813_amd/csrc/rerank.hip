@@ -18,8 +18,8 @@ namespace hntl {
 
 namespace {
 
-template <int CAP, int RR, int JU, bool NT>
-__global__ __launch_bounds__(256) void merge_rerank_kernel(const float* __restrict__ Q, int d, int P, int C, int k,
+template <int CAP, int RR, int JU, bool NT, int NW>
+__global__ __launch_bounds__(64 * NW) void merge_rerank_kernel(const float* __restrict__ Q, int d, int P, int C, int k,
                                                            int G, int64_t N, const int32_t* __restrict__ probes,
                                                            const uint64_t* __restrict__ part,
                                                            const int32_t* __restrict__ pool_in,
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(256) void merge_rerank_kernel(const float* __restri
   // loads of JU float4 column groups of all RR rows before using any of them,
   // so every wave keeps RR x JU x 1 KB of row data in flight
   const float* qv = Q + (size_t)q * d;
-  for (int c0 = wave * RR; c0 < C && !eps_id; c0 += 4 * RR) {
+  for (int c0 = wave * RR; c0 < C && !eps_id; c0 += NW * RR) {
     int32_t id[RR];
     const float* x[RR];
     float acc[RR];
@@ -244,6 +244,11 @@ void ensure_eps_by_id(Index& ix, hipStream_t s) {
   ix.eps_id = p;
 }
 
+// Up to two rows a CU, 16 waves share a row's pool instead of 4, so a pool of 64 rows is
+// one round of loads and not four: one row 12.3 -> 9.3 us, 256 rows with pools of 128
+// 33 -> 25; from 700 rows on there are waves enough and it gains nothing.
+constexpr int64_t MR_WIDE_ROWS = 512;
+
 void launch_merge_rerank(const Index& ix, const float* Q, int64_t nq, int P, int C, int k, const int32_t* probes,
                          const uint64_t* part,
                          const int32_t* pool_in, int32_t* pool_out, float* pool_D_out, int32_t* ids, float* dist,
@@ -257,10 +262,17 @@ void launch_merge_rerank(const Index& ix, const float* Q, int64_t nq, int P, int
   dim3 grid((unsigned)nq);
   // rows of up to 256 floats: one column group per lane and 8 rows per wave (few
   // registers, many waves); longer rows: 3 column groups x 4 rows
-#define HNTL_MR(CAPV, RRV, JUV)                                                                                  \
-  hipLaunchKernelGGL((merge_rerank_kernel<CAPV, RRV, JUV, true>), grid, dim3(256), 0, s, Q, (int)ix.d, P, C, k,      \
-                     (int)ix.G, (int64_t)ix.N, probes, part, pool_in, ix.X, pool_out, pool_D_out, ids, dist, vec4,   \
-                     lbase, nsplit, eps_id, nq, nlim, out_dev)
+#define HNTL_MR_W(CAPV, RRV, JUV, NWV)                                                                               \
+  hipLaunchKernelGGL((merge_rerank_kernel<CAPV, RRV, JUV, true, NWV>), grid, dim3(64 * NWV), 0, s, Q, (int)ix.d, P,  \
+                     C, k, (int)ix.G, (int64_t)ix.N, probes, part, pool_in, ix.X, pool_out, pool_D_out, ids, dist,   \
+                     vec4, lbase, nsplit, eps_id, nq, nlim, out_dev)
+#define HNTL_MR(CAPV, RRV, JUV)       \
+  do {                                \
+    if (nq <= MR_WIDE_ROWS)           \
+      HNTL_MR_W(CAPV, RRV, JUV, 16);  \
+    else                              \
+      HNTL_MR_W(CAPV, RRV, JUV, 4);   \
+  } while (0)
   const bool narrow = ix.d <= 4 * HNTL_WAVE;
   if (cap == 64) {
     if (narrow)
@@ -279,6 +291,7 @@ void launch_merge_rerank(const Index& ix, const float* Q, int64_t nq, int P, int
       HNTL_MR(256, 4, 3);
   }
 #undef HNTL_MR
+#undef HNTL_MR_W
   HIP_TRY(hipGetLastError());
 }
 

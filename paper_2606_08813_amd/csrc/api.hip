@@ -289,6 +289,13 @@ struct StagedScratch {
   }
 };
 
+// One scan of every pair instead of slot 0, its reset and the others: 8 pairs over
+// grains of 105 rows scan in 6 us instead of 15 (a search of one query 62 -> 56 us).
+// A pair is one wave's work, so its grain must be short enough to scan in the time
+// of the two launches saved (32 blocks, 9 us), and the pairs few enough that
+// leaving any of them out would save nothing.
+constexpr uint32_t ONE_SCAN_PAIRS = 16, ONE_SCAN_ROWS = 2048;
+
 // The staged search's launch sequence on scratch w (laid out for this call).
 void run_staged(const Index& ix, const float* Q, uint32_t nq, const hntl_search_params& sp, const StagedIO& io,
                 StagedScratch& w, hipStream_t s) {
@@ -338,7 +345,11 @@ void run_staged(const Index& ix, const float* Q, uint32_t nq, const hntl_search_
       launch_fill_i32(b.cnt, 2 * bucket_counters(ix.G), 0, s);
       b.max_items[LIST_ALL] = (int)(nq / b.lists.tile[LIST_ALL] + std::min<int64_t>(ix.G, nq) + 1);
     }
-    launch_bucket(probes, nq, (int)P, b, s, w.prune);
+    // a few pairs over short grains: all of them in one scan (as if each were its
+    // query's nearest)
+    const bool one_scan = P > 1 && !w.prune && nq * P <= ONE_SCAN_PAIRS && ix.max_grain <= ONE_SCAN_ROWS;
+    if (one_scan) b.max_items[LIST_SLOT0] = (int)(nq * P);
+    launch_bucket(probes, one_scan ? nq * P : nq, one_scan ? 1 : (int)P, b, s, w.prune);
     // 3. projection
     const float* T = io.tangent_in;
     const float* eq = io.epsq_in;
@@ -353,7 +364,7 @@ void run_staged(const Index& ix, const float* Q, uint32_t nq, const hntl_search_
     // 4. scan + per-pair top-C: slot 0 unbounded, then the other slots
     //    bounded by it (and pruned by the exact lower bound unless disabled)
     clk.at(HNTL_STAGE_SCAN);
-    if (P > 1) launch_reset_slot0_tail(pt, nq, (int)P, (int)C, s);
+    if (P > 1 && !one_scan) launch_reset_slot0_tail(pt, nq, (int)P, (int)C, s);
     launch_scan(ix, (int)sp.codes, T, eq, (int)P, (int)C, b, LIST_SLOT0, pt, nullptr, false, true, scored, s);
     if (w.prune) {
       // the other slots' pairs that slot 0's C-th key leaves: bucketed, projected
@@ -367,7 +378,7 @@ void run_staged(const Index& ix, const float* Q, uint32_t nq, const hntl_search_
       launch_bucket(probes, nq, (int)P, b, s, true);
       launch_project(ix, Q, (int)P, b, To, eo, bf16, s);
     }
-    if (P > 1)
+    if (P > 1 && !one_scan)
       launch_scan(ix, (int)sp.codes, T, eq, (int)P, (int)C, b, LIST_REST, pt, bounded ? pt : nullptr, bounded,
                   !bounded || w.prune, scored, s);
     part = pt;

@@ -66,16 +66,16 @@ _SCAN_SRC = ("paper_2606_08813_amd/csrc/fused_impl.h", "paper_2606_08813_amd/csr
              "paper_2606_08813_amd/csrc/hntl_device.h", "paper_2606_08813_amd/csrc/plan.hip",
              "paper_2606_08813_amd/csrc/bucket.hip")
 _SHA = {
-    "paper_2606_08813_amd/csrc/fused_impl.h": "077cb0221488c77b89f0cfbb719688a9350e9d16",
-    "paper_2606_08813_amd/csrc/scan_impl.h": "08b1aa9c637b5afc8f01025d863320b4b9fa4998",
-    "paper_2606_08813_amd/csrc/hntl_device.h": "8042d049177634c7c50bf9f741925e63359e7b21",
-    "paper_2606_08813_amd/csrc/plan.hip": "7a6f9b44aa5f8ef18a7c9574b2ad2af57c79e889",
-    "paper_2606_08813_amd/csrc/bucket.hip": "dc32fc07f95bbf8d60d3997767278e18c59cc518",
+    "paper_2606_08813_amd/csrc/fused_impl.h": "cc7a956096383def329df3be57d11c244709ce7e",
+    "paper_2606_08813_amd/csrc/scan_impl.h": "f97cb34bb38e6e3d726945d518f0bb2de9662595",
+    "paper_2606_08813_amd/csrc/hntl_device.h": "9a2e28e36e0c5eee990e345deb0cfa9c90cbcacf",
+    "paper_2606_08813_amd/csrc/plan.hip": "97700475f79fe8d48a31c364c82e80bfffbafd6f",
+    "paper_2606_08813_amd/csrc/bucket.hip": "693c51d4f08a5a1fc8bbc29376367b50a50acbee",
     "paper_2606_08813_amd/csrc/fused_ct0.hip": "dce4677b8d7025d96f78ce59f33911b619912e08",
     "paper_2606_08813_amd/csrc/fused_ct1.hip": "a15377c01ab0b4b06e0a90b3788ed3259d5aad97",
-    "paper_2606_08813_amd/csrc/rerank.hip": "10c86c447d3bd19bc14c2dbd764d3fc5305ff15d",
-    "paper_2606_08813_amd/csrc/project.hip": "ac70a7ba410f94fcf3a0388a38a0e5c439942fd7",
-    "paper_2606_08813_amd/csrc/project_impl.h": "b7f2c4adb2e898712edc62fc094072e5ff0dab9b",
+    "paper_2606_08813_amd/csrc/rerank.hip": "338d97f9620a179a9f154fe6ffeefb846f1f0619",
+    "paper_2606_08813_amd/csrc/project.hip": "bc860e87b2adacb42b2f4074fd1032024c05cf7e",
+    "paper_2606_08813_amd/csrc/project_impl.h": "408003a14713ce40c6d01a28b372975de874d0d2",
 }
 
 
@@ -85,32 +85,35 @@ def _traffic(kernel, codes, batch, fetch_kib, write_kib, sources, profile, sched
             "write_scale": 1.0, "sources": {f: _SHA[f] for f in sources}, "profile": profile, "sched": sched}
 
 
-# the fused scan's traffic depends on its tiles, ranges and passes (not on the
-# waves per workgroup)
-_WIDE = {"qt": 8, "range": 32, "passes": 1}
-_NARROW = {"qt": 1, "range": 32, "passes": 2}
+# the fused scan's traffic depends on its tiles and ranges (not on the waves per
+# workgroup, nor on the passes: these plans prune pairs before their projection and
+# scan probe slot 0 first under either setting)
+_WIDE = {"qt": 8, "range": 32}
+_NARROW = {"qt": 1, "range": 32}
 
 
-# per plan run: the fused scan launch(es), the separate projection launch, the
-# merge + rerank launch (KiB per dispatch; the two-pass 256-query plan's two
-# scan launches summed)
+# per plan run: the fused scan launches, the separate projection launches, the
+# merge + rerank launch (KiB per dispatch; probe slot 0's scan and projection and
+# those of the other slots' pairs summed)
 TRAFFIC = [
-    _traffic("scan", "fp32", 16384, 2.196e6, 8.634e4, _SCAN_SRC + ("paper_2606_08813_amd/csrc/fused_ct0.hip",),
+    _traffic("scan", "fp32", 16384, 1.330e6 + 7.361e5, 4.109e4 + 3.392e4,
+             _SCAN_SRC + ("paper_2606_08813_amd/csrc/fused_ct0.hip",),
              "profiles/fused_scan_zipf10M_d768_G8192_r48_dram_counters.md", _WIDE),
-    _traffic("scan", "fp32", 256, 7.962e4 + 1.121e5, 710.0 + 891.8,
+    _traffic("scan", "fp32", 256, 1.123e5 + 7.991e4, 713.0 + 769.0,
              _SCAN_SRC + ("paper_2606_08813_amd/csrc/fused_ct0.hip",),
              "profiles/fused_scan_zipf10M_d768_G8192_r48_dram_counters.md", _NARROW),
-    _traffic("scan", "bf16", 16384, 1.120e6, 8.752e4, _SCAN_SRC + ("paper_2606_08813_amd/csrc/fused_ct1.hip",),
+    _traffic("scan", "bf16", 16384, 6.830e5 + 3.605e5, 4.105e4 + 3.434e4,
+             _SCAN_SRC + ("paper_2606_08813_amd/csrc/fused_ct1.hip",),
              "profiles/fused_scan_zipf10M_d768_G8192_r48_dram_counters.md", _WIDE),
-    _traffic("scan", "bf16", 256, 4.122e4 + 5.823e4, 709.9 + 891.6,
+    _traffic("scan", "bf16", 256, 5.823e4 + 4.098e4, 712.0 + 776.0,
              _SCAN_SRC + ("paper_2606_08813_amd/csrc/fused_ct1.hip",),
              "profiles/fused_scan_zipf10M_d768_G8192_r48_dram_counters.md", _NARROW),
-    _traffic("rerank", "fp32", 16384, 2.666e6, 3712.0, ("paper_2606_08813_amd/csrc/rerank.hip",),
+    _traffic("rerank", "fp32", 16384, 2.638e6, 3072.0, ("paper_2606_08813_amd/csrc/rerank.hip",),
              "profiles/merge_rerank_zipf10M_d768_G8192_r48_dram_counters.md"),
-    _traffic("project", "fp32", 16384, 7.475e5, 5.759e4,
+    _traffic("project", "fp32", 16384, 3.693e5 + 2.861e5, 3588.0 + 3.581e4,
              ("paper_2606_08813_amd/csrc/project.hip", "paper_2606_08813_amd/csrc/project_impl.h"),
              "profiles/projection_zipf10M_d768_G8192_r48_counters.md"),
-    _traffic("project", "bf16", 16384, 5.59e5, 5.745e4,
+    _traffic("project", "bf16", 16384, 2.007e5 + 2.660e5, 3587.0 + 3.676e4,
              ("paper_2606_08813_amd/csrc/project.hip", "paper_2606_08813_amd/csrc/project_impl.h"),
              "profiles/projection_zipf10M_d768_G8192_r48_counters.md"),
 ]
@@ -569,6 +572,8 @@ def main():
                       "frac": round(achieved / s["peak"], 4), "ms": round(stage_avg[name], 4)}
         tr = measured_traffic(name, W.name, args.form, args.codes if name != "project" else
                               ("bf16" if bf16_project else "fp32"), P, args.mode, W.nq, sched)
+        if name == "project" and args.form == "plan" and not args.no_prune:
+            roof[name]["work_counts"] = "every (query, probe) pair, also those pruned before their projection"
         if tr:  # the stage's DRAM bytes from counters on this kernel source
             roof[name]["traffic"] = tr
             roof[name]["dram_GBps"] = round(tr / t / 1e9, 1)

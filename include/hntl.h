@@ -385,10 +385,11 @@ typedef struct hntl_schedule {
   uint32_t grid;   /* workgroups of the persistent launch (0 = as many as are resident at once) */
   uint32_t passes; /* 1: every item in one launch; 2: projection and probe-slot-0 items in a first launch,
                       the other slots in a second one, which then start from each query's slot-0 bound
-                      (0 = 1) */
+                      (0 = 1; with proj = 1, batches that prune pairs before their projection always
+                      run probe slot 0 first) */
   uint32_t proj;   /* 0: projection items run inside the fused kernel; 1: a grain-major projection
-                      launch (16 pairs of one grain per single-wave workgroup) runs before it and
-                      the fused kernel only scans and selects */
+                      launch (64 pairs of one grain per workgroup) runs before it and the fused
+                      kernel only scans and selects */
 } hntl_schedule;
 
 #define HNTL_PLAN_GRAPH 1u /* capture a HIP graph at creation; runs replay it */
@@ -446,10 +447,11 @@ hntl_status hntl_plan_info_get(hntl_plan* plan, hntl_plan_info* out);
 /*
  * hntl_plan_profile - run the plan reps times without its graph, with HIP events
  * between its stages on `stream`, and return the mean device milliseconds per stage
- * in stage_ms[0..5): routing, bucketing (with the resets), the separate projection
- * launch (schedule proj = 1; 0 otherwise), the fused project-scan-select kernel,
- * merge + rerank.  *scored (may be NULL) receives the
- * eq. 6 scores the last run computed.  The queries are the first nq rows of the
+ * in stage_ms[0..5): routing (with the start of the run), bucketing, the separate
+ * projection (schedule proj = 1; 0 otherwise), the fused project-scan-select kernel,
+ * merge + rerank.  Where pairs are pruned before their projection, bucketing (with the
+ * pruning), projection and scan are the sums of their two launches.  *scored (may be
+ * NULL) receives the eq. 6 scores the last run computed.  The queries are the first nq rows of the
  * plan's Q buffer.  Synchronous.
  */
 hntl_status hntl_plan_profile(hntl_plan* plan, uint32_t nq, uint32_t reps, double* stage_ms, uint64_t* scored,

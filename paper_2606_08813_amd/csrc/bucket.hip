@@ -9,7 +9,7 @@
 // results bound the other slots.  Three work-item lists are cut from the ranges
 // without materialising them: the exclusive prefix ioff[L][rank] of
 // ceil(pairs / tile_L) numbers list L's items, and a kernel finds the grain of
-// item i by binary search in ioff (or from the decoded item table).
+// item i by a search of ioff (or from the decoded item table).
 //
 // Three kernels: bucket_count_kernel takes every pair's place among its
 // grain's pairs of the same kind from the counter itself (a returning atomic),

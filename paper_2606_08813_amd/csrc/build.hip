@@ -21,8 +21,8 @@
 // (delta_g = 1e-6 trace(S_g) keeps every iterate full rank without moving
 // eigenvectors) with Cholesky-QR2 re-orthonormalisation, and a final
 // Rayleigh-Ritz step (Jacobi eigensolver on the small projected matrix).  The
-// batched FP64 GEMM/TRSM are library calls (rocBLAS), as are the batched
-// Cholesky and the small Jacobi eigensolver (rocSOLVER).
+// batched FP64 GEMMs are library calls (rocBLAS), as is the small Jacobi
+// eigensolver (rocSOLVER); Cholesky factor and triangular solve are one kernel.
 #include <rocblas/rocblas.h>
 #include <rocsolver/rocsolver.h>
 

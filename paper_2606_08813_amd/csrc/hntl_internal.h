@@ -63,7 +63,7 @@ struct Index {
 
   float* centroids = nullptr;  // G x d
   float* cnorm = nullptr;      // G, ||mu_g||^2
-  float* cnmax = nullptr;      // 1: the largest of them
+  float* cnmax = nullptr;      // 1: the largest of them (behind rmax)
   float* basis = nullptr;      // G x r x d
   int32_t* goff = nullptr;     // G + 1 grain-order offsets
   int32_t* boff = nullptr;     // G + 1 block offsets

@@ -5,10 +5,11 @@
 // search needs for batches of up to max_nq queries, so a run allocates
 // nothing and its launch sequence can be captured once into a HIP graph:
 //
-//   reset (fill kernels: ticket, per-grain projection counters, per-query
-//          bounds; graphs hold kernel nodes only)
-//   routing          row norms, centroid distances (own MFMA GEMMs with a
-//                    distance epilogue), top-P + exact re-score
+//   begin            outside the graph, one kernel: queries copied in with their
+//                    norms and routing operands, tickets, counters and per-query
+//                    bounds reset, batch size and the caller's result buffers stored
+//   routing          centroid distances (own MFMA GEMMs with a distance epilogue),
+//                    top-P + exact re-score
 //   bucketing        pairs grouped by grain, items numbered largest grain first,
 //                    per-pair list slots when grains are split into ranges
 //   projection       with the schedule option proj = 1
@@ -16,10 +17,10 @@
 //                    with proj = 1 and batches where it pays, bucketing to scan
 //                    run for probe slot 0 first, and again for the other slots'
 //                    pairs that the exact pruning keeps
-//   merge + rerank   pool = exact top C over the query's lists, FP32 rerank
+//   merge + rerank   pool = exact top C over the query's lists, FP32 rerank; results
+//                    into the plan's buffers and the caller's
 //
-// The batch size lives in device memory (written by a one-thread kernel
-// before each run) and every kernel, the routing GEMMs included, skips rows
+// The batch size lives in device memory and every kernel, the routing GEMMs included, skips rows
 // past it, so one captured graph serves every batch size up to max_nq.
 #include <algorithm>
 #include <cmath>
@@ -79,6 +80,9 @@ constexpr int TICKET_INTS = 9 * 64;
 constexpr int MIN_GRID = 8;  // every class of scan counters needs a workgroup
 // search flags a plan honours (beyond HNTL_FLAG_SYNC)
 constexpr int PLAN_STAGES = 5;  // route, bucket, projection launch, fused kernel, merge + rerank
+// boundaries of the stages, and of what lies between two scans of a pruned plan
+// (prune + bucketing, projection)
+constexpr int PLAN_EVENTS = PLAN_STAGES + 1 + 3;
 constexpr uint32_t PLAN_FLAGS =
     HNTL_FLAG_PROJECT_BF16 | HNTL_FLAG_NO_PRUNE | HNTL_FLAG_ROUTE_BF16X3 | HNTL_FLAG_ROUTE_BF16 | HNTL_FLAG_MODE_A;
 constexpr uint64_t MAX_LIST_BYTES = 4ull << 30;  // candidate-list storage of one plan
@@ -340,10 +344,10 @@ struct Plan {
     launch_plan_begin(g, s);
   }
 
-  // The launch sequence of one run after begin().  With `ev` (6 events, the first
-  // recorded before begin()) the stage boundaries are recorded: route, bucketing,
-  // separate projection launch (empty with proj = 0), fused kernel, merge +
-  // rerank.
+  // The launch sequence of one run after begin().  With `ev` (PLAN_EVENTS events, the
+  // first recorded before begin()) the stage boundaries are recorded: route,
+  // bucketing, separate projection launch (empty with proj = 0), fused kernel, merge +
+  // rerank; with pairs pruned between two scans, that part's boundaries follow them.
   void enqueue(hipStream_t s, hipEvent_t* ev = nullptr) {
     const Index& x = *ix;
     const int P = (int)sp.P;
@@ -364,9 +368,10 @@ struct Plan {
     // another slot goes on only if its lower bound (from the routing distance, no
     // projection) does not exceed the bound that slot 0 left for its query.
     // Queries whose nearest grain cannot overfill a list (C members or fewer: such
-    // lists are written unsorted) get no bound from it: all their pairs go first, beside the long items of slot 0
-    // (alone in the second pass their short items left the GPU to a few waves:
-    // 250 us of 750 at 16,384 queries over Zipf-sized grains).
+    // lists are written unsorted) get no bound from it: all their pairs go first,
+    // beside the long items of slot 0 (alone in the second pass their short items
+    // left the GPU to a few waves: 250 us of 750 at 16,384 queries over Zipf-sized
+    // grains).
     const int need = sch.range && sch.range * B <= sp.C ? INT32_MAX : (int)sp.C + 1;
     Buckets pass = b;
     pass.pick = prune ? PICK_FIRST : PICK_ALL;
@@ -379,6 +384,7 @@ struct Plan {
     if (ev) HIP_TRY(hipEventRecord(ev[3], s));
     if (prune) {
       fused(0);
+      if (ev) HIP_TRY(hipEventRecord(ev[6], s));
       launch_prune_pairs(x, (int)sp.codes, Q,
                          PruneArgs{probes, kept, (int64_t)max_nq, P, (int)sp.C, pdist, qbound, nullptr, need}, s);
       pass.pick = PICK_LATER;
@@ -386,7 +392,9 @@ struct Plan {
       pass.cnt = b.cnt + bucket_counters(x.G);
       pass.lists_from = lists_end;
       launch_bucket(kept, max_nq, P, pass, s, true);
+      if (ev) HIP_TRY(hipEventRecord(ev[7], s));
       launch_project(x, Q, P, pass, T, epsq, bf16, s);
+      if (ev) HIP_TRY(hipEventRecord(ev[8], s));
       fused(3);
     } else {
       for (int ph = sch.passes == 2 ? 1 : 0; ph <= (sch.passes == 2 ? 2 : 0); ++ph) fused(ph);
@@ -699,7 +707,7 @@ hntl_status hntl_plan_profile(hntl_plan* plan, uint32_t nq, uint32_t reps, doubl
   return guarded_call([&] {
     HIP_TRY(hipSetDevice(pl.device));
     hipStream_t s = (hipStream_t)stream;
-    hipEvent_t ev[PLAN_STAGES + 1];
+    hipEvent_t ev[PLAN_EVENTS];
     for (auto& e : ev) HIP_TRY(hipEventCreate(&e));
     std::vector<double> acc(PLAN_STAGES, 0.0);
     unsigned long long sc = 0;
@@ -713,6 +721,14 @@ hntl_status hntl_plan_profile(hntl_plan* plan, uint32_t nq, uint32_t reps, doubl
           float t = 0.f;
           HIP_TRY(hipEventElapsedTime(&t, ev[i], ev[i + 1]));
           acc[i] += t;
+        }
+        if (pl.prune) {  // the second bucketing and projection lie between the two scans
+          float tb = 0.f, tp = 0.f;
+          HIP_TRY(hipEventElapsedTime(&tb, ev[6], ev[7]));
+          HIP_TRY(hipEventElapsedTime(&tp, ev[7], ev[8]));
+          acc[1] += tb;
+          acc[2] += tp;
+          acc[3] -= tb + tp;
         }
         HIP_TRY(hipMemcpy(&sc, pl.scored, sizeof(sc), hipMemcpyDeviceToHost));
       }

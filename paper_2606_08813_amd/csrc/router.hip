@@ -206,7 +206,7 @@ __device__ __forceinline__ void tile_store(const Epi& e, const floatx4 (&acc)[RT
 // neither the 16 rows of an operand read nor the writes of a transposed operand
 // (8 rows apart) share banks.  A transposed operand comes in as 8 rows of two
 // neighbouring depths a thread, which leave as eight 4-byte pairs.
-// Training steps of 512 rows over 768-1024-1024-1024: weight gradients 15 us each,
+// Training steps of 1,024 rows over 768-512-512-1024: weight gradients 15 us each,
 // input gradients 17, forward products 9 (49 and 59 on 128 x 128 tiles that stored
 // transposed operands element by element, 36 on 256 x 128 tiles); 256 x 8,192 x 768:
 // 13 us (33 on 256 x 128 tiles).  Tiles are handed to the XCDs in contiguous runs.
@@ -774,8 +774,8 @@ __host__ __device__ inline double uni(uint64_t seed, uint64_t stream, uint64_t i
   return (double)(splitmix(splitmix(seed ^ (stream * 0xD1B54A32D192ED03ull)) + i) >> 11) * (1.0 / 9007199254740992.0);
 }
 
-// Uniform weights in [-bound, bound) from the counter-based generator.  3.8 million of
-// them on the host and their copy kept a training run of 16,384 rows waiting 1.7 ms.
+// Uniform weights in [-bound, bound) from the counter-based generator.  1.2 million of
+// them on the host and their copy kept a training run waiting 1.7 ms.
 __global__ void init_weights_kernel(float* __restrict__ w, int64_t n, uint64_t seed, uint64_t stream, double bound) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) w[i] = (float)((2.0 * uni(seed, stream, (uint64_t)i) - 1.0) * bound);

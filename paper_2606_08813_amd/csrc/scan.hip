@@ -212,15 +212,21 @@ void launch_grain_bounds(Index& ix, hipStream_t s) {
   if (!ix.blo) ix.blo = dev_alloc<float>(&ix, (size_t)ix.G * ix.rp);
   if (!ix.bhi) ix.bhi = dev_alloc<float>(&ix, (size_t)ix.G * ix.rp);
   if (!ix.emin) ix.emin = dev_alloc<float>(&ix, ix.G);
-  if (!ix.rmax) ix.rmax = dev_alloc<float>(&ix, ix.G);
-  if (!ix.cnmax) ix.cnmax = dev_alloc<float>(&ix, 1);
+  if (!ix.rmax) {
+    ix.rmax = dev_alloc<float>(&ix, (size_t)ix.G + 1);
+    ix.cnmax = ix.rmax + ix.G;
+  }
   launch_norm_max(ix.cnorm, (int)ix.G, ix.cnmax, s);
+  int64_t upto[9] = {};  // members of grains of 2^(k-1) + 1 .. 2^k
+  for (uint32_t g = 0; g < ix.G; ++g) {
+    const int64_t ng = ix.offsets_h[g + 1] - ix.offsets_h[g];
+    int k = 0;
+    while (k <= 8 && ng > (1 << k)) ++k;
+    if (k <= 8) upto[k] += ng;
+  }
+  int64_t n = 0;
   for (int k = 0; k <= 8; ++k) {
-    int64_t n = 0;
-    for (uint32_t g = 0; g < ix.G; ++g) {
-      const int64_t ng = ix.offsets_h[g + 1] - ix.offsets_h[g];
-      if (ng <= (1 << k)) n += ng;
-    }
+    n += upto[k];
     ix.small_share[k] = (float)((double)n / (double)std::max<uint64_t>(ix.N, 1));
   }
   hipLaunchKernelGGL(grain_bounds_kernel, dim3(ix.G), dim3(256), 0, s, ix.codes, ix.eps, (int)ix.rp, (int)ix.r,

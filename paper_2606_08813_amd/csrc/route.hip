@@ -706,7 +706,8 @@ __global__ __launch_bounds__(TOPK_ROWS * 64, NCH > 64 ? 3 : 4) void topk_rows_ke
 #pragma unroll
       for (int u = 0; u < RB; ++u) {
         const int j = j0 + u < Mr ? j0 + u : j0;
-        cs[u] = (int)min(key_id(shfl_u64(mine, j)), (uint32_t)cols - 1);  // (NaN rows have no entries)
+        // (a place without an entry reads some column, and its result is dropped below)
+        cs[u] = (int)min(key_id(shfl_u64(mine, j)), (uint32_t)cols - 1);
         bp[u] = Bm + (size_t)cs[u] * d;
         acc[u] = 0.f;
       }
@@ -751,14 +752,17 @@ __global__ __launch_bounds__(TOPK_ROWS * 64, NCH > 64 ? 3 : 4) void topk_rows_ke
 #pragma unroll
       for (int u = 0; u < RB; ++u) {
         const float tot = wave_sum(acc[u]);
-        if (lane == j0 + u && lane < Mr) ex = make_key(tot, (uint32_t)cs[u]);
+        if (lane == j0 + u && lane < Mr && mine != KEY_NONE) ex = make_key(tot, (uint32_t)cs[u]);
       }
     }
     ex = wave_sort64(ex);
   }
+  // A row with fewer than P entries (its distances are NaN: a query or centroids that are not
+  // finite) has fewer probes.  Never the same column twice: plans size their lists for P
+  // different grains.
   if (lane < P) {
-    idx[row * P + lane] = (int32_t)key_id(ex);
-    if (val) val[row * P + lane] = key_dist(ex);
+    idx[row * P + lane] = ex == KEY_NONE ? -1 : (int32_t)key_id(ex);
+    if (val) val[row * P + lane] = ex == KEY_NONE ? __builtin_inff() : key_dist(ex);
   }
 }
 

@@ -10,6 +10,7 @@
 // that the bound leaves in reach of the P-th by direct differences before it
 // picks the P probes.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "hntl_device.h"
@@ -799,8 +800,8 @@ __global__ __launch_bounds__(1024) void max_kernel(const float* __restrict__ a, 
 // of their own over B (3.1 GB at 1M x 768) cost 0.87 ms.  Bound by the FP32 MFMA
 // units at 64 and 128 rows, by reading B once at 16.  Whole call over
 // 1,000,000 x 768, before (64 x 64 tiles of tile_dot whose every value went
-// through the LDS to a list, 128 ranges a row) and now: 1 query 2.93 -> 0.83 ms
-// (3.7 TB/s), 16 3.19 -> 0.94, 64 3.33 -> 1.49, 300 6.87 -> 5.24, 1,024
+// through the LDS to a list, 128 ranges a row) and now: 1 query 2.93 -> 0.81 ms
+// (3.8 TB/s), 16 3.19 -> 0.92, 64 3.33 -> 1.42, 300 6.87 -> 5.19, 1,024
 // 17.8 -> 13.9 (113 TFLOP/s).
 constexpr int KNN_SHORT = 32;
 
@@ -997,11 +998,12 @@ __global__ __launch_bounds__(64 * KNN_WAVES, RT == 128 ? 2 : 4) void knn_tile_ke
   }
 }
 
-// Pass 1 for rows that allow no 16-byte loads, grid (row tiles of 64, ranges).
+// Pass 1 on tile_dot, grid (row tiles of 64, ranges): rows that allow no 16-byte loads, and
+// the shapes that knn_rows leaves it.
 __global__ __launch_bounds__(256) void knn_partial_kernel(const float* __restrict__ A, const float* __restrict__ an,
                                                           int64_t rows, const float* __restrict__ Bm,
                                                           const float* __restrict__ bn, int64_t cols, int d,
-                                                          int64_t per_split, uint64_t* __restrict__ part) {
+                                                          int64_t per_split, uint64_t* __restrict__ part, bool vec4) {
   __shared__ float tiles[2 * TM * LDT];  // As and Bs; then the 64 x 64 distance tile
   __shared__ uint64_t stage[4][16][64];
   float(*As)[LDT] = reinterpret_cast<float(*)[LDT]>(tiles);
@@ -1017,7 +1019,7 @@ __global__ __launch_bounds__(256) void knn_partial_kernel(const float* __restric
   for (int r = 0; r < 16; ++r) L[r].init(stage[wave][r], KNN_SHORT);
   for (int64_t col0 = c_begin; col0 < c_end; col0 += TN) {
     floatx4 acc[2][2];
-    tile_dot(acc, As, Bs, A, rows, Bm, (int)(c_end < cols ? c_end : cols), d, row0, (int)col0, false);
+    tile_dot(acc, As, Bs, A, rows, Bm, (int)(c_end < cols ? c_end : cols), d, row0, (int)col0, vec4);
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
@@ -1197,6 +1199,53 @@ int pow2_at_least(int x) {
 
 namespace hntl {
 
+namespace {
+
+// Rows per tile of pass 1, 0: knn_partial_kernel.  Measured over 1 to 30,000 rows, 600 to
+// 300,000 columns and 32 to 1,024 depths:
+//  - 16 rows up to 4e9 products: a tile's first 128 columns all pass the empty lists, and 64
+//    rows take 50 us to sort them in, 16 rows 5 (64 rows over 10,000 x 768: 270 and 185 us;
+//    90 over 1,500 x 768: 130 us, 843 on 64 rows in ranges of eight tiles and more);
+//  - 128 rows run 4% faster than twice 64 at 256 depths or more, where the padding to them
+//    is no more (1,024 rows over 1,000,000 x 768: 13.9 against 14.5 ms; 300 rows 5.9 against 5.2;
+//    at 64 depths the lists bound them: 5,000 over 100,000 x 64 1,465 against 1,331 us);
+//  - from 448 rows of 384 depths on, up to 2,800 of its 64 x 64 tiles, knn_partial_kernel's
+//    smaller workgroups fill the GPU in one round (1,500 over 5,000 x 1,024: 406 against 477 us,
+//    5,000 over 1,000 x 768: 257 against 303).
+int knn_rows(int64_t rows, int64_t cols, int d, bool vec4) {
+  if (!vec4) return 0;
+  auto tiles = [](int64_t n, int64_t t) { return (n + t - 1) / t; };
+  const int64_t t64 = tiles(rows, 64) * tiles(cols, 64);
+  if (d >= 384 && rows >= 448 && t64 >= 256 && t64 <= 2800) return 0;
+  if (rows <= 16 || (double)rows * (double)cols * d <= 4e9) return 16;
+  return d >= 256 && 100 * 128 * tiles(rows, 128) <= 103 * 64 * tiles(rows, 64) ? 128 : 64;
+}
+
+// Column ranges for rt row tiles of RT rows over `tiles` column tiles of nk depth chunks.  Each
+// range starts with empty lists, which costs as much as `lists` chunks and a share of it
+// again with the logarithm of its length (the values that still pass get fewer), and adds a
+// list per row to merge; the rounds of workgroups should be full.  A workgroup alone on
+// its CU takes 0.8 of the time of two that share it.
+int64_t knn_ranges(int RT, int64_t rt, int64_t tiles, int nk) {
+  const int64_t slots = RT == 128 ? 256 : 512;  // workgroups at once
+  const double lists = RT == 16 ? 8.0 : 20.0;
+  int64_t best = 1;
+  double least = 0.0;
+  for (int64_t sp = 1; sp <= tiles && (sp == 1 || rt * sp <= 4 * slots); sp += sp < 16 ? 1 : 8) {
+    const int64_t len = (tiles + sp - 1) / sp;
+    const int64_t wg = rt * (sp < 8 ? sp : (sp + 7) / 8 * 8);  // (from 8 on each XCD takes every eighth range)
+    const double rounds = RT < 128 && wg <= 256 ? 0.8 : (double)((wg + slots - 1) / slots);
+    const double cost = rounds * ((double)len * nk + lists * (1.0 + std::log((double)len))) + 0.1 * (double)sp;
+    if (sp == 1 || cost < least) {
+      least = cost;
+      best = sp;
+    }
+  }
+  return best;
+}
+
+}  // namespace
+
 void launch_knn(const float* A, int64_t rows, const float* Bm, int64_t cols, int d, int k, int32_t* ids, float* dist,
                 hipStream_t s) {
   if (rows <= 0) return;
@@ -1204,32 +1253,15 @@ void launch_knn(const float* A, int64_t rows, const float* Bm, int64_t cols, int
   if (cols >= (1ll << 31)) throw ArgError{HNTL_EUNSUPPORTED, "brute-force kNN needs fewer than 2^31 rows"};
   float *an = nullptr, *bn = nullptr;
   uint64_t* part = nullptr;
-  int64_t splits, per;
+  int64_t per;
   HIP_TRY(hipMallocAsync((void**)&an, sizeof(float) * rows, s));
   launch_row_norms(A, rows, d, an, s);
-  if ((d % 4) == 0 && ((uintptr_t)A % 16) == 0 && ((uintptr_t)Bm % 16) == 0) {
-    // rows per tile: the work is that of the rows padded to the tile, and 128
-    // rows run 4% faster than twice 64 (1,000,000 x 768: 1,024 queries 13.9
-    // against 14.5 ms, 300 queries 5.9 against 5.2)
-    auto padded = [&](int64_t t) { return (rows + t - 1) / t * t; };
-    const int RT = rows <= 16 ? 16 : 100 * padded(128) <= 103 * padded(64) ? 128 : 64;
+  const bool vec4 = (d % 4) == 0 && ((uintptr_t)A % 16) == 0 && ((uintptr_t)Bm % 16) == 0;
+  const int RT = knn_rows(rows, cols, d, vec4);
+  int64_t splits = 1;
+  if (RT) {
     const int64_t rt = (rows + RT - 1) / RT;
-    // column ranges: the fewest (each adds a list per row to merge) that leave
-    // the last round of workgroups at least 95% full, at least 8 tiles a range
-    const int64_t slots = 256 * (RT == 128 ? 1 : 2);
-    const int64_t most = std::max<int64_t>(1, std::min<int64_t>(cols / (8 * KNN_COLS), 4 * slots));
-    double best = 0.0;
-    splits = 1;
-    for (int64_t sp = 1; sp <= most && best < 0.95; ++sp) {
-      if (sp > 8 && sp % 8) continue;  // whole rounds over the XCDs
-      const int64_t wg = rt * sp;
-      const double full = (double)wg / (double)((wg + slots - 1) / slots * slots);
-      if (full > best) {
-        best = full;
-        splits = sp;
-      }
-      if (wg > 8 * slots) break;
-    }
+    splits = knn_ranges(RT, rt, (cols + KNN_COLS - 1) / KNN_COLS, (d + FK - 1) / FK);
     per = ((cols + splits - 1) / splits + KNN_COLS - 1) / KNN_COLS * KNN_COLS;
     splits = (cols + per - 1) / per;
     HIP_TRY(hipMallocAsync((void**)&part, sizeof(uint64_t) * rows * splits * KNN_SHORT, s));
@@ -1253,7 +1285,7 @@ void launch_knn(const float* A, int64_t rows, const float* Bm, int64_t cols, int
     HIP_TRY(hipMallocAsync((void**)&part, sizeof(uint64_t) * rows * splits * KNN_SHORT, s));
     launch_row_norms(Bm, cols, d, bn, s);
     hipLaunchKernelGGL(knn_partial_kernel, dim3((unsigned)rt, (unsigned)splits), dim3(256), 0, s, A, an, rows, Bm, bn,
-                       cols, d, per, part);
+                       cols, d, per, part, vec4);
   }
   HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(knn_merge_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, A, rows, Bm, d,

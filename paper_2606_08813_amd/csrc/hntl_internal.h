@@ -338,8 +338,10 @@ struct PruneArgs {
 };
 void launch_prune_pairs(const Index& ix, int codes, const float* Q, const PruneArgs& a, hipStream_t s);
 // Whether the pruning pays for a batch of nq queries (plan: one whose schedule
-// takes the queries it cannot bound into the first pass).
-bool prune_pays(const Index& ix, const hntl_search_params& sp, int64_t nq, bool plan);
+// takes the queries it cannot bound into the first pass) if it keeps the share `kept`.
+bool prune_pays(const Index& ix, const hntl_search_params& sp, int64_t nq, bool plan, float kept = 0.f);
+// The share it is expected to keep; waits for the stream.
+float expected_kept(const Index& ix, int P, int C, hipStream_t s);
 // Before the slot-0 pass of the staged scan: entry C - 1 of each query's
 // slot-0 list := KEY_NONE (part is nq x P x C keys).
 void launch_reset_slot0_tail(uint64_t* part, int64_t nq, int P, int C, hipStream_t s);

@@ -535,7 +535,8 @@ Plan* make_plan(Index& ix, const hntl_search_params& sp, uint32_t max_nq, const 
   }
   sch.grid = std::max<uint32_t>(sch.grid, MIN_GRID);
   pl->sch = sch;
-  pl->prune = sch.proj && prune_pays(ix, sp, max_nq, true);
+  pl->prune = sch.proj && prune_pays(ix, sp, max_nq, true) &&
+              prune_pays(ix, sp, max_nq, true, expected_kept(ix, (int)sp.P, (int)sp.C, s));
   pl->arena_bytes = pl->layout(nullptr);
   HIP_TRY(hipMalloc((void**)&pl->arena, pl->arena_bytes));
   pl->layout(pl->arena);

@@ -178,6 +178,59 @@ __global__ __launch_bounds__(256) void prune_pairs_dist_kernel(PruneArgs a, int 
   if (lane < a.P) a.kept[q * a.P + lane] = keep;
 }
 
+// What the pruning is likely to keep, from the grains alone (one workgroup per sampled grain
+// g, `near` its P nearest centroids): a query among g's members lies about
+// rho = mean(||z_i||^2 + eps_i) from mu_g, thus sqrt(||mu_g - mu_h||^2 + rho) from mu_h, and its C-th
+// best score is near 1.5 rho.  kept[sample]: the other slots that the pruning's bound
+// would keep then (every one where g has at most C members and leaves no bound).
+constexpr int KEPT_BLOCKS = 64;  // blocks of a grain that rho is taken over
+__global__ __launch_bounds__(256) void expected_kept_kernel(const int32_t* __restrict__ sample,
+                                                            const int32_t* __restrict__ near,
+                                                            const float* __restrict__ near_dist, int P, int C, int G,
+                                                            const float* __restrict__ codes,
+                                                            const float* __restrict__ eps, int rp, int r,
+                                                            const int32_t* __restrict__ goff,
+                                                            const int32_t* __restrict__ boff,
+                                                            const float* __restrict__ rmax,
+                                                            const float* __restrict__ emin, int* __restrict__ kept) {
+  __shared__ float red[256];
+  const int g = sample[blockIdx.x];
+  const int b0 = boff[g], ng = goff[g + 1] - goff[g], nb = min(boff[g + 1] - b0, KEPT_BLOCKS);
+  const int lane = lane_id();
+  float sum = 0.f;
+  for (int b = threadIdx.x >> 6; b < nb; b += 4)
+    if (b * B + lane < ng) {
+      sum += eps[(size_t)(b0 + b) * B + lane];
+      for (int j = 0; j < r; ++j) {
+        const float v = codes[((size_t)(b0 + b) * rp + j) * B + lane];
+        sum = fmaf(v, v, sum);
+      }
+    }
+  red[threadIdx.x] = sum;
+  __syncthreads();
+  for (int o = 128; o > 0; o >>= 1) {
+    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+    __syncthreads();
+  }
+  const float rho = red[0] / (float)max(1, min(ng, KEPT_BLOCKS * B));
+  bool keep = false;
+  if ((int)threadIdx.x >= 1 && (int)threadIdx.x < P) {
+    const int h = near[blockIdx.x * P + threadIdx.x];
+    keep = ng <= C;
+    if (h >= 0 && h < G) {
+      const float a = sqrtf(near_dist[blockIdx.x * P + threadIdx.x] + rho) - rmax[h];
+      keep |= !(a > 0.f && a * a + emin[h] > 1.5f * rho);
+    }
+  }
+  const int n = __popcll(__ballot(keep));  // HNTL_MAX_P < 64: all in the first wave
+  if (threadIdx.x == 0) kept[blockIdx.x] = n;
+}
+
+__global__ void sample_rows_kernel(const float* __restrict__ X, int d, const int32_t* __restrict__ rows,
+                                   float* __restrict__ out) {
+  for (int j = threadIdx.x; j < d; j += blockDim.x) out[(size_t)blockIdx.x * d + j] = X[(size_t)rows[blockIdx.x] * d + j];
+}
+
 // Entry C - 1 of every query's probe-slot-0 list set to KEY_NONE: a list that
 // no scan item writes (its probe is outside 0 .. G-1) then bounds nothing.
 __global__ void reset_slot0_tail_kernel(uint64_t* __restrict__ part, int64_t nq, int P, int C) {
@@ -234,27 +287,72 @@ void launch_grain_bounds(Index& ix, hipStream_t s) {
   HIP_TRY(hipGetLastError());
 }
 
+// Share of the pairs of slots 1 .. P - 1 that the pruning is expected to keep, over grains
+// sampled by their members (0.2 ms).  On fourteen built indexes (patches of several
+// spreads, one to eight grains a patch, a single Gaussian cloud) it was within 0.07 of the share
+// that 2,000 queries kept.
+float expected_kept(const Index& ix, int P, int C, hipStream_t s) {
+  constexpr int S = 64;
+  if (P < 2 || ix.N == 0) return 0.f;
+  std::vector<int32_t> sample(S);
+  for (int i = 0; i < S; ++i) {
+    const int64_t at = (int64_t)((2 * i + 1) * ix.N / (2 * S));
+    sample[i] = (int32_t)(std::upper_bound(ix.offsets_h.begin(), ix.offsets_h.end(), at) - ix.offsets_h.begin()) - 1;
+  }
+  const int G = (int)ix.G, d = (int)ix.d;
+  Scratch sc(s);
+  int32_t* rows = sc.get<int32_t>(S);
+  float* A = sc.get<float>((size_t)S * d);
+  float* an = sc.get<float>(S);
+  float* D = sc.get<float>((size_t)S * G);
+  int32_t* near = sc.get<int32_t>((size_t)S * P);
+  float* near_dist = sc.get<float>((size_t)S * P);
+  int* kept = sc.get<int>(S);
+  HIP_TRY(hipMemcpyAsync(rows, sample.data(), sizeof(int32_t) * S, hipMemcpyHostToDevice, s));
+  hipLaunchKernelGGL(sample_rows_kernel, dim3(S), dim3(256), 0, s, ix.centroids, d, rows, A);
+  HIP_TRY(hipGetLastError());
+  launch_row_norms(A, S, d, an, s);
+  launch_dist_matrix(A, an, S, ix.centroids, ix.cnorm, G, d, D, s);
+  launch_topk_rows(D, S, G, P, near, near_dist, s, A, an, ix.centroids, ix.cnorm, ix.cnmax, d, route_err(ROUTE_F32));
+  hipLaunchKernelGGL(expected_kept_kernel, dim3(S), dim3(256), 0, s, rows, near, near_dist, P, C, G, ix.codes, ix.eps,
+                     (int)ix.rp, (int)ix.r, ix.goff, ix.boff, ix.rmax, ix.emin, kept);
+  HIP_TRY(hipGetLastError());
+  std::vector<int> n(S);
+  HIP_TRY(hipMemcpyAsync(n.data(), kept, sizeof(int) * S, hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipStreamSynchronize(s));
+  int64_t sum = 0;
+  for (int v : n) sum += v;
+  return (float)((double)sum / (double)(S * (P - 1)));
+}
+
 // Scanning slot 0 first, pruning, then bucketing, projecting and scanning what is
 // left takes four more launches (10 us in a plan's graph, less where a stream of
-// single launches waits for the GPU) than one projection of every pair.  Measured
-// with and without on 20 to 10,000 queries over five indexes of 20,000 to 300,000
-// rows, uniform and Zipf sizes:
-//  - plans: even near 64 MB of bases and query rows or 12,000 pairs (100 x 12 over
-//    1,024 x 768: 165 -> 158 us; 3,000 x 8 over 256 x 256: 220 -> 196; 100 x 8 over
-//    256 x 256: 89 -> 98);
+// single launches waits for the GPU) than one projection of every pair, and what is kept
+// pays them again: a second bucketing, bases and codes read twice.  Measured
+// with and without on 20 to 10,000 queries over indexes of 20,000 to 400,000
+// rows, uniform and Zipf sizes, grains apart and overlapping:
+//  - plans, where nothing is kept: even near 64 MB of bases and query rows or 12,000 pairs
+//    (100 x 12 over 1,024 x 768: 165 -> 158 us; 3,000 x 8 over 256 x 256: 220 -> 196; 100 x 8 over
+//    256 x 256: 89 -> 98).  Of 2,000 x 8 pairs over 512 x 768 it gains 10 to 16% with none kept
+//    and loses 8 to 10% with 0.14 kept and up to 31% with all kept (410 -> 538 us); of 10,000 x 8
+//    it gains 10% with none kept, nothing with 0.4 to 0.7, and loses 3 to 14% with all.  So what is
+//    dropped has to make up for the lot and a quarter of what is kept;
 //  - staged searches: even near 700 pairs (100 x 8 over 256 x 768: 130 -> 119 us; 20 x 8:
 //    107 -> 111) where few queries' nearest grain is too small to bound them;
 //    their pairs are all left, and packed 16 or 4 to a wave they run longer
 //    (3,000 x 8 over 1,024 Zipf-sized grains, 5% of the members in grains of at
-//    most C: 457 -> 471), until the projection saved outweighs it.
-bool prune_pays(const Index& ix, const hntl_search_params& sp, int64_t nq, bool plan) {
+//    most C: 457 -> 471), until the projection saved outweighs it.  With all kept the narrow
+//    second scan still makes up for most of it (512 grains of one cloud, 256 and 768 wide: 300
+//    queries 156 -> 144 and 181 -> 182 us, 10,000 468 -> 451 and 736 -> 726).
+bool prune_pays(const Index& ix, const hntl_search_params& sp, int64_t nq, bool plan, float kept) {
   if (sp.P < 2 || (sp.flags & HNTL_FLAG_NO_PRUNE) || sp.codes == HNTL_CODES_INT16) return false;
   // the learned router's probe budget has dropped most of them already
   if (sp.route == HNTL_ROUTE_LEARNED && sp.mass > 0.f && sp.mass < 1.f) return false;
   const int64_t rest = nq * (sp.P - 1);
   const int64_t basis = std::min<int64_t>(ix.G, rest) * ix.r * ((sp.flags & HNTL_FLAG_PROJECT_BF16) ? 2 : 4);
   const int64_t bytes = (basis + rest * 4) * ix.d;
-  if (plan) return bytes >= ((int64_t)64 << 20) || rest >= 12288;
+  const double gain = 1.0 - 1.25 * kept;
+  if (plan) return gain * (double)bytes >= 67108864.0 || gain * (double)rest >= 12288.0;
   int k = 0;
   while (k < 8 && (1u << k) < sp.C) ++k;
   if (ix.small_share[k] <= 0.02f) return rest >= 704;

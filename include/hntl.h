@@ -462,7 +462,8 @@ void hntl_plan_free(hntl_plan* plan);
 /*
  * hntl_tune - the autotuner.  Times every candidate schedule of the fused kernel
  * (proj in {0, 1} x passes in {1, 2} x qt in {1, 2, 4, 8} x nw in {1, 2, 4, 8} x range in
- * {0, 8, 32, 64}, those whose LDS fits) on the nq given queries (device, nq x d) and returns the fastest in *best
+ * {0, 8, 32, 64}, those whose LDS fits; passes = 1 alone where the two are the same
+ * launches) on the nq given queries (device, nq x d) and returns the fastest in *best
  * (*best_ms its median device time of one run).  With db_path != NULL the result is
  * also stored in that text file, one line per (device, index shape, search params,
  * batch size), replacing an older line of the same key; hntl_schedule_lookup reads it.

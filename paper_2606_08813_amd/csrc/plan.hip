@@ -788,6 +788,7 @@ hntl_status hntl_tune(hntl_index* index, const hntl_search_params* sp, const flo
             }
             throw;
           }
+          if (pl->prune && passes == 2) continue;  // the launches of passes = 1
           pl->run(Q, nq, PlanOut{nullptr, nullptr}, s);  // warm-up
           std::vector<float> t;
           for (int rep = 0; rep < 5; ++rep) {

@@ -72,3 +72,13 @@ def test_overlapping_grains_cost_no_second_pass():
     without, b = best(hntl.HNTL_FLAG_NO_PRUNE)
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
     assert with_prune < 1.15 * without, (with_prune, without)  # 1.3 with both passes
+
+
+def test_tuner_times_a_pipeline_once():
+    torch = require_gpu()
+    from paper_2606_08813_amd import hntl
+    announce("tuning where plans prune pairs and passes is not read")
+    ix, X, _ = apart(torch, hntl, 20_000, 50, 32, 16)
+    for nq in (2000, 2100, 2200, 2300, 2400):
+        best, ms = hntl.hntl_tune(ix, X[:nq].contiguous(), P, C, K)
+        assert ms > 0 and not (best["proj"] == 1 and best["passes"] == 2), best

@@ -488,18 +488,6 @@ __global__ void to_bf16_kernel(const float* __restrict__ x, int64_t n, uint16_t*
 }
 
 // xh[r][j] = bf16((X[rows[r]][j] - mean[j]) / std[j]) (rows == null: r itself)
-// h = bf16(gelu(z + bias[col])) over a rows x cols block of FP32 dot products
-__global__ void gelu_bias_bf16_kernel(const float* __restrict__ z, int64_t rows, int cols,
-                                      const float* __restrict__ bias, uint16_t* __restrict__ h) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < rows * cols) h[i] = to_bf16(gelu(z[i] + bias[i % cols]));
-}
-
-__global__ void negate_kernel(const float* __restrict__ a, int64_t n, float* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = -a[i];
-}
-
 __global__ void standardize_kernel(const float* __restrict__ X, const int32_t* __restrict__ rows, int64_t n, int d,
                                    const float* __restrict__ mean, const float* __restrict__ stdv,
                                    uint16_t* __restrict__ xh, const int32_t* __restrict__ nlim) {
@@ -1111,7 +1099,6 @@ struct Trainer {
   uint16_t *xh = nullptr, *h1 = nullptr, *h2 = nullptr, *dsb = nullptr, *da2b = nullptr, *da1b = nullptr;
   float *a1 = nullptr, *a2 = nullptr, *S = nullptr, *ds = nullptr, *da2 = nullptr, *da1 = nullptr, *loss = nullptr;
   int32_t* rows = nullptr;
-  int32_t* tgt = nullptr;
   int step = 0;
 
   template <class T>

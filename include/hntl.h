@@ -412,7 +412,7 @@ hntl_status hntl_plan_create(hntl_index* index, const hntl_search_params* sp, ui
 /*
  * hntl_plan_buffers - the plan's own device buffers: Q (max_nq x d float32),
  * ids (max_nq x k int32), dist (max_nq x k float32).  Writing queries into Q and
- * calling hntl_plan_run avoids the copies of hntl_plan_search.  Any pointer may be NULL.
+ * calling hntl_plan_run avoids hntl_plan_search's copy of them.  Any pointer may be NULL.
  */
 hntl_status hntl_plan_buffers(hntl_plan* plan, float** Q, int32_t** ids, float** dist);
 
@@ -425,9 +425,9 @@ hntl_status hntl_plan_buffers(hntl_plan* plan, float** Q, int32_t** ids, float**
 hntl_status hntl_plan_run(hntl_plan* plan, uint32_t nq, void* stream);
 
 /*
- * hntl_plan_search - copy nq queries (device) into the plan, run it, copy the
- * results out (device ids nq x k, dist nq x k).  Q, ids and dist may also be the
- * plan's own buffers (no copy then).
+ * hntl_plan_search - run the plan on nq queries (device, nq x d; the run copies them
+ * into the plan) with the results in ids and dist (device, nq x k) as well as in
+ * the plan's own buffers.  Q, ids and dist may also be the plan's own buffers.
  */
 hntl_status hntl_plan_search(hntl_plan* plan, const float* Q, uint32_t nq, int32_t* ids, float* dist,
                              void* stream);

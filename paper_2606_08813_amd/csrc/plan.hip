@@ -78,11 +78,11 @@ constexpr size_t LDS_LIMIT = 64 * 1024;
 // one projection counter and 8 scan counters per launch, 256 bytes apart
 constexpr int TICKET_INTS = 9 * 64;
 constexpr int MIN_GRID = 8;  // every class of scan counters needs a workgroup
-// search flags a plan honours (beyond HNTL_FLAG_SYNC)
 constexpr int PLAN_STAGES = 5;  // route, bucket, projection launch, fused kernel, merge + rerank
 // boundaries of the stages, and of what lies between two scans of a pruned plan
 // (prune + bucketing, projection)
 constexpr int PLAN_EVENTS = PLAN_STAGES + 1 + 3;
+// search flags a plan honours (beyond HNTL_FLAG_SYNC)
 constexpr uint32_t PLAN_FLAGS =
     HNTL_FLAG_PROJECT_BF16 | HNTL_FLAG_NO_PRUNE | HNTL_FLAG_ROUTE_BF16X3 | HNTL_FLAG_ROUTE_BF16 | HNTL_FLAG_MODE_A;
 constexpr uint64_t MAX_LIST_BYTES = 4ull << 30;  // candidate-list storage of one plan

@@ -1,13 +1,15 @@
 // Candidate pool and exact rerank (paper Section 2.1 steps 3-4, Mode B).
 //
-// One workgroup (4 waves) per query:
-//   1. wave 0 merges the P per-grain top-C lists into the query's pool: the C
-//      smallest (D, id) over the union of the probed grains.  This is exact
-//      because the global top-C is contained in the union of per-grain top-Cs.
+// One workgroup per query, of 16 waves in batches of up to MR_WIDE_ROWS queries and
+// 4 in larger ones:
+//   1. wave 0 merges the query's top-C lists (one per probed grain, or per block
+//      range of it) into its pool: the C smallest (D, id) over the union of the
+//      probed grains.  This is exact because the global top-C is contained in the
+//      union of the lists.
 //   2. all waves gather the raw float32 rows of the pool (HBM-resident copy of
 //      the corpus) and compute ||q - x||^2 by direct differences in FP32:
-//      16-byte non-temporal loads (each row is used once), two rows per wave
-//      at a time (measured faster than one or four on MI355X).
+//      16-byte non-temporal loads (each row is used once), 8 rows of up to 256
+//      depths or 4 longer ones per wave at a time.
 //   3. wave 0 keeps the k smallest (distance, id).
 #include <mutex>
 

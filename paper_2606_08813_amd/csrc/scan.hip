@@ -93,9 +93,17 @@ __global__ __launch_bounds__(256) void grain_bounds_kernel(const float* __restri
 // the basis and the projection's precision, and needs no projection.  With
 // reduced codes R covers the decoded values (BF16 2^-8 relative; FP8 2^-4
 // relative plus the subnormal quantum per coordinate).  The int16 form clamps
-// z_q after eps_q is taken, so it has no such bound.  Margins: delta = 1e-5 +
-// 1e-8 d on both lengths and 4e-6 p on the square cover the FP32 sums (d terms
-// over 64 lanes), PRUNE_SLACK as in the scan.
+// z_q after eps_q is taken, so it has no such bound.
+//
+// Margins, in roundings of u = 2^-24 (the score's own sums and p sum the same FP32
+// squares (q - mu)_j^2).  The bound holds with p as the projection sums it for eps_q: four
+// chains of d / 4 terms and two additions, at worst 1 - (d / 4 + 2) u of the true sum;
+// the p used here (routing: 64 chains of d / 64 terms, at most four more, and six additions)
+// is at worst 1 + (d / 64 + 10) u of it.  A square root halves both, so the length is at most
+// (0.133 d + 6) u = 8e-9 d + 4e-7 too long, and delta = 1e-5 + 1e-8 d on both lengths covers it
+// for every d (R's sum of up to 64 squares is rounded up where it is made).  ||z_q||^2
+// within eps_q has eight roundings, 5e-7 p of the square at most: 4e-6 p.  The scan's sums
+// over z_q - z_i are off by 70 u of the score: PRUNE_SLACK as there.
 constexpr float PRUNE_SLACK = 1e-4f;
 
 struct PruneForm {

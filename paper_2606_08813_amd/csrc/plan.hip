@@ -461,16 +461,20 @@ bool lists_fit(uint64_t lists, uint32_t C) {
   return lists < (1ull << 31) && lists * C * sizeof(uint64_t) <= MAX_LIST_BYTES;
 }
 
-// Default schedule from the pairs per grain: few of them want short items of
-// one pair spread over many workgroups, many want tiles of four that share the
-// code loads.  The projection runs as its own launch (inside the fused kernel an
-// item is one wave streaming a whole basis) except for a handful of pairs,
-// where the extra launch costs what it saves.  Measured on plans of 1 to 10,000
-// queries over four indexes (30,000 to 1,000,000 rows, 96 to 1,536 grains, uniform
-// and Zipf sizes, FP32, BF16 and FP8 codes), each line within 8% of the best of
-// 42 schedules; against the former defaults (projection inside, 4 x 4 pairs from 8
-// pairs a grain): 1,000,000 x 768, P = 8: 64 queries 293 -> 140 us, 300 372 -> 165,
-// 1,500 445 -> 259, 10,000 1,493 -> 774; one query unchanged.
+// Default schedule: few pairs want short items of one pair spread over many
+// workgroups, many want tiles of four that share the code loads.  Many are 32 pairs a
+// grain, 2,048 queries (each scans its nearest grain without a bound) or, over grains of
+// a block or two, whose items are mostly their overhead, 8,192 pairs.  The projection
+// runs as its own launch (inside the fused kernel an item is one wave streaming a
+// whole basis) except for a handful of pairs, where the extra launch costs what it
+// saves.  Measured on plans of 1 to 16,384 queries over fourteen indexes (30,000 to
+// 1,000,000 rows, 96 to 8,000 grains, uniform and Zipf sizes, FP32, BF16 and FP8 codes): the
+// choice is within 8% of the best of 42 schedules on four of them and within 25% of the
+// best of ten on all, with the single pair up to three times the tiles' time where the line is
+// drawn too late (10,000 x 8 pairs over 3,000 grains of 20 rows: 1,251 us, on tiles 568); against
+// the former defaults (projection inside, 4 x 4 pairs from 8 pairs a grain): 1,000,000 x 768,
+// P = 8: 64 queries 293 -> 140 us, 300 372 -> 165, 1,500 445 -> 259, 10,000 1,493 -> 774; one
+// query unchanged.
 hntl_schedule default_schedule(const Index& ix, const hntl_search_params& sp, uint32_t max_nq) {
   const double per_grain = (double)max_nq * sp.P / std::max<uint32_t>(1, ix.G);
   hntl_schedule s{};
@@ -480,7 +484,8 @@ hntl_schedule default_schedule(const Index& ix, const hntl_search_params& sp, ui
     s.qt = 1;
     s.nw = 1;
     s.range = 8;
-  } else if (per_grain < 32.0) {
+  } else if (per_grain < 32.0 && max_nq < 2048 &&
+             !(ix.N <= 128ull * ix.G && (uint64_t)max_nq * sp.P >= 8192)) {
     s.qt = 1;
     s.nw = 4;
     s.range = 16;

@@ -191,7 +191,7 @@ __global__ __launch_bounds__(256) void prune_pairs_dist_kernel(PruneArgs a, int 
 // rho = mean(||z_i||^2 + eps_i) from mu_g, thus sqrt(||mu_g - mu_h||^2 + rho) from mu_h, and its C-th
 // best score is near 1.5 rho.  kept[sample]: the other slots that the pruning's bound
 // would keep then (every one where g has at most C members and leaves no bound).
-constexpr int KEPT_BLOCKS = 64;  // blocks of a grain that rho is taken over
+constexpr int KEPT_BLOCKS = 16;  // blocks of a grain that rho is taken over (1,024 members; 64: 370 us of launch at r = 48)
 __global__ __launch_bounds__(256) void expected_kept_kernel(const int32_t* __restrict__ sample,
                                                             const int32_t* __restrict__ near,
                                                             const float* __restrict__ near_dist, int P, int C, int G,
@@ -351,7 +351,7 @@ float expected_kept(const Index& ix, int P, int C, hipStream_t s) {
 //    (3,000 x 8 over 1,024 Zipf-sized grains, 5% of the members in grains of at
 //    most C: 457 -> 471), until the projection saved outweighs it.  With all kept the narrow
 //    second scan still makes up for most of it (512 grains of one cloud, 256 and 768 wide: 300
-//    queries 156 -> 144 and 181 -> 182 us, 10,000 468 -> 451 and 736 -> 726).
+//    queries 156 -> 144 and 181 -> 182 us, 10,000 468 -> 451 and 736 -> 726; at worst 148 -> 169).
 bool prune_pays(const Index& ix, const hntl_search_params& sp, int64_t nq, bool plan, float kept) {
   if (sp.P < 2 || (sp.flags & HNTL_FLAG_NO_PRUNE) || sp.codes == HNTL_CODES_INT16) return false;
   // the learned router's probe budget has dropped most of them already

@@ -69,11 +69,11 @@ _SHA = {
     "paper_2606_08813_amd/csrc/fused_impl.h": "cc7a956096383def329df3be57d11c244709ce7e",
     "paper_2606_08813_amd/csrc/scan_impl.h": "f97cb34bb38e6e3d726945d518f0bb2de9662595",
     "paper_2606_08813_amd/csrc/hntl_device.h": "9a2e28e36e0c5eee990e345deb0cfa9c90cbcacf",
-    "paper_2606_08813_amd/csrc/plan.hip": "97700475f79fe8d48a31c364c82e80bfffbafd6f",
+    "paper_2606_08813_amd/csrc/plan.hip": "e9c1dc661e3fb6e2a2c24516c7ecfa60987c8c47",
     "paper_2606_08813_amd/csrc/bucket.hip": "693c51d4f08a5a1fc8bbc29376367b50a50acbee",
     "paper_2606_08813_amd/csrc/fused_ct0.hip": "dce4677b8d7025d96f78ce59f33911b619912e08",
     "paper_2606_08813_amd/csrc/fused_ct1.hip": "a15377c01ab0b4b06e0a90b3788ed3259d5aad97",
-    "paper_2606_08813_amd/csrc/rerank.hip": "338d97f9620a179a9f154fe6ffeefb846f1f0619",
+    "paper_2606_08813_amd/csrc/rerank.hip": "ed63fe9d1dea13d6055df7bad947eaab2d8ea7d8",
     "paper_2606_08813_amd/csrc/project.hip": "bc860e87b2adacb42b2f4074fd1032024c05cf7e",
     "paper_2606_08813_amd/csrc/project_impl.h": "408003a14713ce40c6d01a28b372975de874d0d2",
 }
@@ -96,24 +96,24 @@ _NARROW = {"qt": 1, "range": 32}
 # merge + rerank launch (KiB per dispatch; probe slot 0's scan and projection and
 # those of the other slots' pairs summed)
 TRAFFIC = [
-    _traffic("scan", "fp32", 16384, 1.330e6 + 7.361e5, 4.109e4 + 3.392e4,
+    _traffic("scan", "fp32", 16384, 1.330e6 + 7.380e5, 4.110e4 + 3.392e4,
              _SCAN_SRC + ("paper_2606_08813_amd/csrc/fused_ct0.hip",),
              "profiles/fused_scan_zipf10M_d768_G8192_r48_dram_counters.md", _WIDE),
-    _traffic("scan", "fp32", 256, 1.123e5 + 7.991e4, 713.0 + 769.0,
+    _traffic("scan", "fp32", 256, 1.121e5 + 7.964e4, 712.0 + 892.0,
              _SCAN_SRC + ("paper_2606_08813_amd/csrc/fused_ct0.hip",),
              "profiles/fused_scan_zipf10M_d768_G8192_r48_dram_counters.md", _NARROW),
-    _traffic("scan", "bf16", 16384, 6.830e5 + 3.605e5, 4.105e4 + 3.434e4,
+    _traffic("scan", "bf16", 16384, 6.816e5 + 3.582e5, 4.104e4 + 3.434e4,
              _SCAN_SRC + ("paper_2606_08813_amd/csrc/fused_ct1.hip",),
              "profiles/fused_scan_zipf10M_d768_G8192_r48_dram_counters.md", _WIDE),
-    _traffic("scan", "bf16", 256, 5.823e4 + 4.098e4, 712.0 + 776.0,
+    _traffic("scan", "bf16", 256, 5.822e4 + 4.120e4, 710.0 + 891.0,
              _SCAN_SRC + ("paper_2606_08813_amd/csrc/fused_ct1.hip",),
              "profiles/fused_scan_zipf10M_d768_G8192_r48_dram_counters.md", _NARROW),
     _traffic("rerank", "fp32", 16384, 2.638e6, 3072.0, ("paper_2606_08813_amd/csrc/rerank.hip",),
              "profiles/merge_rerank_zipf10M_d768_G8192_r48_dram_counters.md"),
-    _traffic("project", "fp32", 16384, 3.693e5 + 2.861e5, 3588.0 + 3.581e4,
+    _traffic("project", "fp32", 16384, 3.693e5 + 2.860e5, 3588.0 + 3.580e4,
              ("paper_2606_08813_amd/csrc/project.hip", "paper_2606_08813_amd/csrc/project_impl.h"),
              "profiles/projection_zipf10M_d768_G8192_r48_counters.md"),
-    _traffic("project", "bf16", 16384, 2.007e5 + 2.660e5, 3587.0 + 3.676e4,
+    _traffic("project", "bf16", 16384, 2.007e5 + 2.657e5, 3587.0 + 3.676e4,
              ("paper_2606_08813_amd/csrc/project.hip", "paper_2606_08813_amd/csrc/project_impl.h"),
              "profiles/projection_zipf10M_d768_G8192_r48_counters.md"),
 ]

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <map>
 #include <memory>
 #include <string>
 #include <vector>
@@ -90,6 +91,8 @@ struct Index {
 
   std::vector<int64_t> offsets_h;
   std::vector<int32_t> boff_h;
+  std::vector<int32_t> gorder_h;                   // gorder on the host (made with it)
+  std::map<std::pair<int, int>, float> kept_share;  // expected_kept by P and C (plans; under their lock)
   std::vector<double> captured;  // per grain (build only)
   float small_share[9] = {};     // share of the members in grains of at most 2^k members, k = 0..8
   uint64_t device_bytes = 0;
@@ -340,7 +343,7 @@ void launch_prune_pairs(const Index& ix, int codes, const float* Q, const PruneA
 // Whether the pruning pays for a batch of nq queries (plan: one whose schedule
 // takes the queries it cannot bound into the first pass) if it keeps the share `kept`.
 bool prune_pays(const Index& ix, const hntl_search_params& sp, int64_t nq, bool plan, float kept = 0.f);
-// The share it is expected to keep; waits for the stream.
+// The share it is expected to keep (0.1 ms); waits for the stream.
 float expected_kept(const Index& ix, int P, int C, hipStream_t s);
 // Before the slot-0 pass of the staged scan: entry C - 1 of each query's
 // slot-0 list := KEY_NONE (part is nq x P x C keys).

@@ -116,7 +116,17 @@ void ensure_grain_order(Index& ix) {
   if (!ix.grank) ix.grank = dev_alloc<int32_t>(&ix, ix.G);
   HIP_TRY(hipMemcpy(ix.grank, rank.data(), sizeof(int32_t) * ix.G, hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(d, o.data(), sizeof(int32_t) * ix.G, hipMemcpyHostToDevice));
+  ix.gorder_h = std::move(o);
   ix.gorder = d;
+}
+
+// expected_kept, made once per index, P and C.
+float kept_share(Index& ix, int P, int C, hipStream_t s) {
+  std::lock_guard<std::mutex> lk(g_order_mu);
+  const auto key = std::make_pair(P, C);
+  const auto it = ix.kept_share.find(key);
+  if (it != ix.kept_share.end()) return it->second;
+  return ix.kept_share[key] = expected_kept(ix, P, C, s);
 }
 
 std::string device_key(int dev) {
@@ -140,6 +150,9 @@ std::string tune_key(const Index& ix, const hntl_search_params& sp, uint32_t nq)
 }  // namespace
 
 // ------------------------------------------------------------------ plan
+// Where the split counts by rank follow those by grain (16-byte aligned).
+size_t split_stride(const Index& ix) { return ((size_t)ix.G + 3) / 4 * 4; }
+
 struct Plan {
   Index* ix = nullptr;
   hntl_search_params sp{};
@@ -233,8 +246,8 @@ struct Plan {
     kept = prune ? L.take<int32_t>(np) : probes;
     pdist = prune && sp.route != HNTL_ROUTE_LEARNED ? L.take<float>(np) : nullptr;
     lists_end = L.take<int32_t>(1);
-    nsplit = L.take<int32_t>(x.G);
-    nsplit_rank = L.take<int32_t>(x.G);
+    nsplit = L.take<int32_t>(split_stride(x) + x.G);
+    nsplit_rank = nsplit ? nsplit + split_stride(x) : nullptr;
     b.nsplit_rank = sch.range ? nsplit_rank : nullptr;
     int32_t* lb = L.take<int32_t>(np);
     b.lbase = sch.range ? lb : nullptr;
@@ -541,17 +554,16 @@ Plan* make_plan(Index& ix, const hntl_search_params& sp, uint32_t max_nq, const 
   sch.grid = std::max<uint32_t>(sch.grid, MIN_GRID);
   pl->sch = sch;
   pl->prune = sch.proj && prune_pays(ix, sp, max_nq, true) &&
-              prune_pays(ix, sp, max_nq, true, expected_kept(ix, (int)sp.P, (int)sp.C, s));
+              prune_pays(ix, sp, max_nq, true, kept_share(ix, (int)sp.P, (int)sp.C, s));
   pl->arena_bytes = pl->layout(nullptr);
   HIP_TRY(hipMalloc((void**)&pl->arena, pl->arena_bytes));
   pl->layout(pl->arena);
   HIP_TRY(hipMemsetAsync(pl->Q, 0, sizeof(float) * (size_t)max_nq * ix.d, s));
   HIP_TRY(hipMemsetAsync(pl->err, 0, sizeof(int32_t), s));
-  HIP_TRY(hipMemcpyAsync(pl->nsplit, ns.data(), sizeof(int32_t) * ix.G, hipMemcpyHostToDevice, s));
-  std::vector<int32_t> order(ix.G), nsr(ix.G);
-  HIP_TRY(hipMemcpy(order.data(), ix.gorder, sizeof(int32_t) * ix.G, hipMemcpyDeviceToHost));
-  for (uint32_t i = 0; i < ix.G; ++i) nsr[i] = ns[order[i]];
-  HIP_TRY(hipMemcpyAsync(pl->nsplit_rank, nsr.data(), sizeof(int32_t) * ix.G, hipMemcpyHostToDevice, s));
+  std::vector<int32_t> splits(split_stride(ix) + ix.G);  // by grain, then by rank
+  std::copy(ns.begin(), ns.end(), splits.begin());
+  for (uint32_t i = 0; i < ix.G; ++i) splits[split_stride(ix) + i] = ns[ix.gorder_h[i]];
+  HIP_TRY(hipMemcpyAsync(pl->nsplit, splits.data(), sizeof(int32_t) * splits.size(), hipMemcpyHostToDevice, s));
   FusedArgs a[4];
   for (int ph = 0; ph < 4; ++ph) {
     a[ph] = pl->make_args();

@@ -191,8 +191,8 @@ __global__ __launch_bounds__(256) void prune_pairs_dist_kernel(PruneArgs a, int 
 // rho = mean(||z_i||^2 + eps_i) from mu_g, thus sqrt(||mu_g - mu_h||^2 + rho) from mu_h, and its C-th
 // best score is near 1.5 rho.  kept[sample]: the other slots that the pruning's bound
 // would keep then (every one where g has at most C members and leaves no bound).
-constexpr int KEPT_BLOCKS = 16;  // blocks of a grain that rho is taken over (1,024 members; 64: 370 us of launch at r = 48)
-__global__ __launch_bounds__(256) void expected_kept_kernel(const int32_t* __restrict__ sample,
+constexpr int KEPT_BLOCKS = 16;  // blocks of a grain that rho is taken over, a wave each
+__global__ __launch_bounds__(64 * KEPT_BLOCKS) void expected_kept_kernel(const int32_t* __restrict__ sample,
                                                             const int32_t* __restrict__ near,
                                                             const float* __restrict__ near_dist, int P, int C, int G,
                                                             const float* __restrict__ codes,
@@ -201,22 +201,22 @@ __global__ __launch_bounds__(256) void expected_kept_kernel(const int32_t* __res
                                                             const int32_t* __restrict__ boff,
                                                             const float* __restrict__ rmax,
                                                             const float* __restrict__ emin, int* __restrict__ kept) {
-  __shared__ float red[256];
+  __shared__ float red[64 * KEPT_BLOCKS];
   const int g = sample[blockIdx.x];
   const int b0 = boff[g], ng = goff[g + 1] - goff[g], nb = min(boff[g + 1] - b0, KEPT_BLOCKS);
-  const int lane = lane_id();
+  const int lane = lane_id(), b = threadIdx.x >> 6;
   float sum = 0.f;
-  for (int b = threadIdx.x >> 6; b < nb; b += 4)
-    if (b * B + lane < ng) {
-      sum += eps[(size_t)(b0 + b) * B + lane];
-      for (int j = 0; j < r; ++j) {
-        const float v = codes[((size_t)(b0 + b) * rp + j) * B + lane];
-        sum = fmaf(v, v, sum);
-      }
+  if (b < nb && b * B + lane < ng) {
+    sum = eps[(size_t)(b0 + b) * B + lane];
+#pragma unroll 8
+    for (int j = 0; j < r; ++j) {
+      const float v = codes[((size_t)(b0 + b) * rp + j) * B + lane];
+      sum = fmaf(v, v, sum);
     }
+  }
   red[threadIdx.x] = sum;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
+  for (int o = 32 * KEPT_BLOCKS; o > 0; o >>= 1) {
     if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
     __syncthreads();
   }
@@ -296,7 +296,7 @@ void launch_grain_bounds(Index& ix, hipStream_t s) {
 }
 
 // Share of the pairs of slots 1 .. P - 1 that the pruning is expected to keep, over grains
-// sampled by their members (0.2 ms).  On fourteen built indexes (patches of several
+// sampled by their members.  On fourteen built indexes (patches of several
 // spreads, one to eight grains a patch, a single Gaussian cloud) it was within 0.07 of the share
 // that 2,000 queries kept.
 float expected_kept(const Index& ix, int P, int C, hipStream_t s) {
@@ -322,7 +322,7 @@ float expected_kept(const Index& ix, int P, int C, hipStream_t s) {
   launch_row_norms(A, S, d, an, s);
   launch_dist_matrix(A, an, S, ix.centroids, ix.cnorm, G, d, D, s);
   launch_topk_rows(D, S, G, P, near, near_dist, s, A, an, ix.centroids, ix.cnorm, ix.cnmax, d, route_err(ROUTE_F32));
-  hipLaunchKernelGGL(expected_kept_kernel, dim3(S), dim3(256), 0, s, rows, near, near_dist, P, C, G, ix.codes, ix.eps,
+  hipLaunchKernelGGL(expected_kept_kernel, dim3(S), dim3(64 * KEPT_BLOCKS), 0, s, rows, near, near_dist, P, C, G, ix.codes, ix.eps,
                      (int)ix.rp, (int)ix.r, ix.goff, ix.boff, ix.rmax, ix.emin, kept);
   HIP_TRY(hipGetLastError());
   std::vector<int> n(S);

@@ -66,6 +66,7 @@ __global__ __launch_bounds__(256) void grain_bounds_kernel(const float* __restri
   for (int b = w; b < nb; b += 4)
     if (b * B + lane < ng) {
       float acc = 0.f;
+#pragma unroll 8  // (one load at a time: 70 us more in an append to 64 grains of 1,560 x 64)
       for (int j = 0; j < r; ++j) {
         const float v = codes[((size_t)(b0 + b) * rp + j) * B + lane];
         acc = fmaf(v, v, acc);

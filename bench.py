@@ -69,7 +69,7 @@ _SHA = {
     "paper_2606_08813_amd/csrc/fused_impl.h": "cc7a956096383def329df3be57d11c244709ce7e",
     "paper_2606_08813_amd/csrc/scan_impl.h": "f97cb34bb38e6e3d726945d518f0bb2de9662595",
     "paper_2606_08813_amd/csrc/hntl_device.h": "9a2e28e36e0c5eee990e345deb0cfa9c90cbcacf",
-    "paper_2606_08813_amd/csrc/plan.hip": "e9c1dc661e3fb6e2a2c24516c7ecfa60987c8c47",
+    "paper_2606_08813_amd/csrc/plan.hip": "6b680ed6a268ae853dbde91b36c3d7ff0948484d",
     "paper_2606_08813_amd/csrc/bucket.hip": "693c51d4f08a5a1fc8bbc29376367b50a50acbee",
     "paper_2606_08813_amd/csrc/fused_ct0.hip": "dce4677b8d7025d96f78ce59f33911b619912e08",
     "paper_2606_08813_amd/csrc/fused_ct1.hip": "a15377c01ab0b4b06e0a90b3788ed3259d5aad97",
